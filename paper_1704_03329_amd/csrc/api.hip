@@ -1240,7 +1240,7 @@ mdpl_status mdpl_mlp_train_grad(const mdpl_mlp_weights* w, const float* G, const
   a.partial = scratch;
   a.inv_batch = 1.0f / (float)batch;
   HIP_TRY(mlp_train_grad(a, (hipStream_t)stream));
-  HIP_TRY(mlp_sum_partials(scratch, waves, grad, (hipStream_t)stream));
+  HIP_TRY(mlp_sum_partials(scratch, mlp_train_blocks(batch), grad, (hipStream_t)stream));
   return MDPL_OK;
 }
 

@@ -338,8 +338,9 @@ hipError_t desc_backward(const double* x, const double* y, const double* z,
 struct MlpArgs;
 hipError_t mlp_eval(const MlpArgs& a, hipStream_t st);
 hipError_t mlp_train_grad(const MlpArgs& a, hipStream_t st);
-int mlp_train_waves(int64_t n);
-hipError_t mlp_sum_partials(const float* partial, int nwaves, float* out, hipStream_t st);
+int mlp_train_waves(int64_t n);   // waves of the training pass (sizes the caller's scratch)
+int mlp_train_blocks(int64_t n);  // its workgroups, each of which leaves one partial
+hipError_t mlp_sum_partials(const float* partial, int nparts, float* out, hipStream_t st);
 hipError_t adam_step(float* p, const float* g, float* m, float* v, float lr, float b1, float b2,
                      float eps, int t, unsigned short* w1, unsigned short* w2, unsigned short* w3,
                      hipStream_t st);

@@ -233,6 +233,36 @@ def test_train_gradient_and_adam_match_oracle(config):
     np.testing.assert_allclose(after, want, rtol=1e-5, atol=1e-7)
 
 
+@pytest.mark.parametrize("batch", [1, 63, 64, 65, 1000, 4096, 16384 + 80])
+def test_train_gradient_over_batch_sizes(config, batch):
+    """One workgroup (64 rows) with and without a remainder, several, the
+    benchmark's batch and more tiles than the 256 workgroups take at once.
+    The targets lie about ten spreads from the outputs, so that a row's
+    residual is known to a few 1e-3 (BF16 activations) and the gradient to
+    the bar of the test above."""
+    from paper_1704_03329_amd import potential as P
+
+    pos, box = config
+    n = pos.shape[0]
+    print(f"train gradient, batch {batch}", flush=True)
+    Gd = P.descriptors(_sim(n, box), torch.from_numpy(pos).cuda())
+    e = torch.from_numpy(np.sin(np.arange(n) * 0.37) - 4.0).cuda()
+    m = _model(Gd, e, seed=4)
+    em, es = float(np.float32(m.e_mean)), float(np.float32(m.e_sd))
+    energy = (em + es * (10.0 + (e - e.mean()))).contiguous()
+    idx = torch.from_numpy(mdinputs.batch_indices(n, batch, 1, 12)[0]).cuda()
+    scratch = torch.full((P.mdpl_mlp_train_floats(batch),), float("nan"), device="cuda")
+    grad = torch.empty(P.NPARAM + 1, dtype=torch.float32, device="cuda")
+    P.mdpl_mlp_train_grad(m.weights(), Gd, idx, batch, energy, scratch, grad)
+    g = grad.cpu().numpy()
+    rows = idx.cpu().numpy()
+    gstd = OM.standardise(Gd.double().cpu().numpy()[rows], m.mu.double().cpu().numpy(),
+                          m.sd.double().cpu().numpy())
+    L, ref = OM.loss_and_grads(m.host_params(), gstd, ((energy - em) / es).cpu().numpy()[rows])
+    assert g[P.NPARAM] == pytest.approx(L, rel=2e-2)
+    assert _rel(g[: P.NPARAM], P.pack(ref).astype(np.float64)) <= 3e-2
+
+
 def test_standardisation_and_bf16_cast_in_the_library():
     """mdpl_mlp_standardise: FP64 means and population spreads of the
     features and energies (the definition, written out in numpy here);
