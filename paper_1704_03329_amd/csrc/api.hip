@@ -175,10 +175,23 @@ void lj_grid(const mdpl_lj_params* p, Grid* g, int* threads) {
   *threads = t < 64 ? 64 : (t > 1024 ? 1024 : t);
 }
 
+// Parts of a brick in the force passes and the descriptors (full lists only;
+// the other pair loops run one workgroup per brick).
+constexpr int kPartsWant = 512, kPartsMost = 8;
+int force_parts(const mdpl_lj_params* p, const Grid& g) {
+  return p->pairs == MDPL_PAIRS_FULL ? brick_parts(g, kPartsWant, kPartsMost) : 1;
+}
+
 // Workgroups of any drifting launch: k_vv (256 particles each) or the fused
-// force pass (the brick order, at most nbricks + 16 entries).
-int64_t track_slots(int64_t n, const Grid& g) {
-  const int64_t a = div_up(n, 256), b = (int64_t)g.nbricks + 16;
+// force pass (per part the brick order, at most nbricks + 16 entries).
+int64_t track_slots(int64_t n, const Grid& g, int parts) {
+  const int64_t a = div_up(n, 256), b = ((int64_t)g.nbricks + 16) * parts;
+  return a > b ? a : b;
+}
+
+// Rows of per-workgroup partials: of a particle loop or of a force pass.
+int64_t partial_rows(int64_t n, const Grid& g, int parts) {
+  const int64_t a = div_up(n, 256), b = (int64_t)g.nbricks * parts;
   return a > b ? a : b;
 }
 
@@ -186,7 +199,8 @@ size_t lj_ws_bytes(const mdpl_lj_params* p, const Grid& g) {
   const int64_t n = p->n;
   const int64_t npad = div_up(n, 256) * 256;
   const size_t fb = p->precision == MDPL_FP32 ? 4 : 8;
-  const int64_t nblk = div_up(n, 256) > g.nbricks ? div_up(n, 256) : g.nbricks;
+  const int parts = force_parts(p, g);
+  const int64_t nblk = partial_rows(n, g, parts);
   size_t b = sort_bytes(n);
   b += align256(4 * (size_t)(g.nkeys + 1));    // cell_start
   b += align256(4 * (size_t)n);                // perm
@@ -202,7 +216,7 @@ size_t lj_ws_bytes(const mdpl_lj_params* p, const Grid& g) {
   b += align256(4 * (size_t)(g.nkeys + 1));                 // lower-x-half counts
   b += align256(4 * (size_t)(n + 1));          // offsets
   b += align256(8 * (size_t)(3 * nblk + 2));   // partials
-  b += 2 * align256(8 * (size_t)track_slots(n, g));  // the rule's per-workgroup maxima
+  b += 2 * align256(8 * (size_t)track_slots(n, g, parts));  // the rule's per-workgroup maxima
   b += align256(256);                          // flags, maxcount, max_disp, pe_w_tmp, rule, last row
   b += align256(4 * 8 * (size_t)g.nbricks);   // brick order of the tile kernels
   return b;
@@ -428,9 +442,10 @@ mdpl_status mdpl_sim_create(const mdpl_lj_params* p, void* workspace, size_t byt
   if (s->tl.half || s->tl.cells || !(p->box[0] / s->g.nc[0] > rext * (1.0 + 1e-9)))
     s->tl.xlow = nullptr;
   s->offsets = take<int32_t>(w, 4 * (size_t)(n + 1));
-  s->nblk = (int)(div_up(n, 256) > s->g.nbricks ? div_up(n, 256) : s->g.nbricks);
+  s->tl.parts = force_parts(p, s->g);
+  s->nblk = (int)partial_rows(n, s->g, s->tl.parts);
   s->partials = take<double>(w, 8 * (size_t)(3 * s->nblk + 2));
-  s->nvpart = (int)track_slots(n, s->g);
+  s->nvpart = (int)track_slots(n, s->g, s->tl.parts);
   s->vpart[0] = take<double>(w, 8 * (size_t)s->nvpart);
   s->vpart[1] = take<double>(w, 8 * (size_t)s->nvpart);
   char* small = take<char>(w, 256);
@@ -848,7 +863,7 @@ mdpl_status run_loop(mdpl_sim* s, StateArrays user, int64_t nsteps, int32_t samp
     s->pend_step = s->track.step;
     s->track_cur ^= 1;
   };
-  const int force_groups = s->g.order ? s->g.norder : ((s->g.nbricks + 7) / 8) * 8;
+  const int force_groups = (s->g.order ? s->g.norder : ((s->g.nbricks + 7) / 8) * 8) * s->tl.parts;
 
   mdpl_status r = MDPL_OK;
   if (!cont) {

@@ -143,7 +143,8 @@ __global__ __launch_bounds__(512) void k_desc_fwd(const double* __restrict__ x,
   tile_load_f32(g, x, y, z, total, ox, oy, oz, s0, t, home);  // ends with a barrier
   const float rc2 = rc * rc;
   const float half_rev = 0.5f / rc;  // revolutions per unit r of cos(pi r / rc)
-  for (int s = s0 + (int)threadIdx.x; s < s1; s += blockDim.x) {
+  for (int s = s0 + (int)(blockIdx.y * blockDim.x + threadIdx.x); s < s1;
+       s += gridDim.y * blockDim.x) {
     const int hs = s - s0 < kBrickMax ? home[s - s0] : TileF32::kDummy;
     const float xi = t.px[hs], yi = t.py[hs], zi = t.pz[hs];
     float G[kNRad];
@@ -495,6 +496,7 @@ __global__ void k_zero3(float* __restrict__ a, float* __restrict__ b, float* __r
 // hiding there is; at 161 VGPRs three waves per SIMD fit (768 threads: 197 ->
 // 183 us against 512 at N = 262144).
 constexpr int kBwdThreads = 768;
+template <int LPP>
 __global__ __launch_bounds__(kBwdThreads) void k_desc_bwd(const double* __restrict__ x,
                                                    const double* __restrict__ y,
                                                    const double* __restrict__ z,
@@ -520,8 +522,10 @@ __global__ __launch_bounds__(kBwdThreads) void k_desc_bwd(const double* __restri
   const float rc2 = rc * rc;
   const float pi_rc = 3.14159265358979f / rc;
   const float half_rev = 0.5f / rc;
-  const int part = (int)threadIdx.x & 1;  // two lanes per particle, alternate list words
-  for (int s = s0 + ((int)threadIdx.x >> 1); s < s1; s += (int)(blockDim.x >> 1)) {
+  const int part = (int)threadIdx.x % LPP;  // lanes of a particle take every LPP-th list word
+  const int step = (int)blockDim.x / LPP;
+  for (int s = s0 + (int)blockIdx.y * step + (int)threadIdx.x / LPP; s < s1;
+       s += (int)gridDim.y * step) {
     // FP32 coordinates relative to the tile centre (the force pass's), own
     // position from the particle's own slot
     const int hs = s - s0 < kBrickMax ? home[s - s0] : TileF32::kDummy;
@@ -532,7 +536,7 @@ __global__ __launch_bounds__(kBwdThreads) void k_desc_bwd(const double* __restri
     float fx = 0.0f, fy = 0.0f, fz = 0.0f;
     const int ng = (tl.cnt[s] + 3) >> 2;
     const uint64_t* __restrict__ col = tl.nbr + s;
-    const int nw = ng > part ? (ng - part + 1) >> 1 : 0;  // this lane's words: part + 2 w
+    const int nw = ng > part ? (ng - part + LPP - 1) / LPP : 0;  // this lane's words: part + LPP w
     for (int w0 = 0; w0 < nw; w0 += 16) {
       // the in-range entries of up to 16 words as a bit mask (bit 4 w + q:
       // entry q of word w0 + w), so that the pair terms below run on the
@@ -545,7 +549,7 @@ __global__ __launch_bounds__(kBwdThreads) void k_desc_bwd(const double* __restri
         uint64_t wd[4];
 #pragma unroll
         for (int k = 0; k < 4; ++k)
-          wd[k] = col[(int64_t)(part + 2 * (w0 + (wg + k < wn ? wg + k : wn - 1))) * tl.stride];
+          wd[k] = col[(int64_t)(part + LPP * (w0 + (wg + k < wn ? wg + k : wn - 1))) * tl.stride];
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
           const int w = wg + k;
@@ -565,12 +569,12 @@ __global__ __launch_bounds__(kBwdThreads) void k_desc_bwd(const double* __restri
       // loaded a trip ahead
       // (the load goes to a valid row even when no bit is left)
       int b = mask ? __builtin_ctzll(mask) : 64;
-      uint64_t word = col[(int64_t)(part + 2 * (w0 + (b < 64 ? b >> 2 : 0))) * tl.stride];
+      uint64_t word = col[(int64_t)(part + LPP * (w0 + (b < 64 ? b >> 2 : 0))) * tl.stride];
       while (b < 64) {
         const int u = (int)((word >> (16 * (b & 3))) & 0xffff) >> kFullShift;
         mask &= mask - 1;
         b = mask ? __builtin_ctzll(mask) : 64;
-        word = col[(int64_t)(part + 2 * (w0 + (b < 64 ? b >> 2 : 0))) * tl.stride];
+        word = col[(int64_t)(part + LPP * (w0 + (b < 64 ? b >> 2 : 0))) * tl.stride];
         const float dx = t.px[u] - xi, dy = t.py[u] - yi, dz = t.pz[u] - zi;
         const float d2 = dx * dx + dy * dy + dz * dz;
         // 1/r from the hardware reciprocal square root (about 1 ulp), r = d2/r
@@ -622,8 +626,10 @@ hipError_t desc_forward(const double* x, const double* y, const double* z,
                         const int32_t* perm, float* G, float* mom, hipStream_t st, float* fx,
                         float* fy, float* fz) {
   DescIO io{G, mom, nullptr, perm, fx, fy, fz};
-  const unsigned threads = tl.threads < 512 ? tl.threads : 512;
-  hipLaunchKernelGGL(k_desc_fwd, dim3(tile_grid(g)), dim3(threads), 0, st, x, y,
+  // several parts share a brick's particles (small systems): one wave each and
+  // more, 256 threads for the tile load
+  const unsigned threads = tl.parts > 1 ? 256 : (tl.threads < 512 ? tl.threads : 512);
+  hipLaunchKernelGGL(k_desc_fwd, dim3(tile_grid(g), tl.parts), dim3(threads), 0, st, x, y,
                      z, cell_start, g, tl, rc, io);
   return hipGetLastError();
 }
@@ -635,8 +641,15 @@ hipError_t desc_backward(const double* x, const double* y, const double* z,
   DescIO io{nullptr, const_cast<float*>(mom), dEdG, perm, fx, fy, fz};
   if (!zeroed)
     hipLaunchKernelGGL(k_zero3, dim3((unsigned)div_up(n, 256)), dim3(256), 0, st, fx, fy, fz, n);
+  if (tl.parts > 1) {
+    const int per = (int)div_up(8 * (int64_t)tl.threads, tl.parts);
+    const unsigned threads = per < kBwdThreads ? (unsigned)((per + 63) & ~63) : kBwdThreads;
+    hipLaunchKernelGGL(k_desc_bwd<8>, dim3(tile_grid(g), tl.parts), dim3(threads), 0, st, x, y, z,
+                       cell_start, g, tl, rc, io);
+    return hipGetLastError();
+  }
   const unsigned threads = 2 * tl.threads < kBwdThreads ? 2 * tl.threads : kBwdThreads;
-  hipLaunchKernelGGL(k_desc_bwd, dim3(tile_grid(g)), dim3(threads), 0, st, x, y,
+  hipLaunchKernelGGL(k_desc_bwd<2>, dim3(tile_grid(g)), dim3(threads), 0, st, x, y,
                      z, cell_start, g, tl, rc, io);
   return hipGetLastError();
 }

@@ -147,12 +147,28 @@ struct TileList {
   int64_t stride;   // words per group row (>= n)
   int max_nb;       // multiple of 4
   int threads;      // workgroup size of the tile kernels
+  int parts;        // workgroups per brick of the force passes and the descriptors (brick_parts)
   int half;         // 1: each pair once (Newton's third law), tiles of kTileMaxHalf slots
   int cells;        // 1: no list; the pair loop scans the cell stencil (nbr and cnt unused)
   // per cell key, its particles in the lower half of the cell along x (they
   // come first in the cell); null: the list build scans whole stencil rows
   int32_t* xlow;
 };
+// Workgroups per brick, `most` at the most, that give the chip about `want`
+// workgroups.  A small system has few bricks (8 at N = 1000, 27 at 4096), so
+// that with one workgroup each most of the 256 CUs idle and one brick's
+// serial work sets the time; several workgroups then load the same tile and
+// share its particles (or, in the list build, its cells).  FP64 force pass,
+// one workgroup per brick against 8 parts of 8 lanes per particle: N = 1000
+// 18.0 -> 10.7 us, N = 4096 25.3 -> 11.2 us, N = 32768 23.8 -> 14.0 us;
+// descriptors and backward at N = 4096 59.5 -> 46.2 and 80.3 -> 34.8 us.  The
+// second load costs a few us from the L2, so that systems with more bricks
+// than `want` keep one.
+inline int brick_parts(const Grid& g, int want, int most) {
+  int p = want / g.nbricks;
+  p = p < most ? p : most;
+  return p < 1 ? 1 : p;
+}
 hipError_t build_tile_nlist(const double* x, const double* y, const double* z,
                             const int32_t* skeys, const int32_t* cell_start, const Grid& g,
                             double r2, TileList tl, uint32_t* flags, int32_t* maxcount,
@@ -199,12 +215,12 @@ struct KickTrack {
 // |v|^2 (0 without particles; a non-finite value counts as infinite).
 __device__ inline void kick_store(const KickTrack& kt, double m2) {
   if (!kt.ring) return;
-  kt.part[kt.cur][blockIdx.x] = m2 >= 0.0 ? m2 : __builtin_huge_val();
+  kt.part[kt.cur][blockIdx.y * gridDim.x + blockIdx.x] = m2 >= 0.0 ? m2 : __builtin_huge_val();
 }
 // Every thread of workgroup 0 of a drifting launch, before its other work
 // (no-op elsewhere): the pending record.  sh: one double per wave.
 __device__ inline void kick_publish(const KickTrack& kt, double* sh) {
-  if (!kt.ring || kt.pub_n <= 0 || blockIdx.x != 0) return;
+  if (!kt.ring || kt.pub_n <= 0 || (blockIdx.x | blockIdx.y) != 0) return;
   const double* p = kt.part[kt.cur ^ 1];
   double m = 0.0;
   for (int i = threadIdx.x; i < kt.pub_n; i += blockDim.x) m = p[i] > m ? p[i] : m;
@@ -244,7 +260,7 @@ struct ForceOut {
   uint32_t* flags;        // MDPL_FLAG_NONFINITE on a non-finite velocity; tile overflow (no list)
   KickTrack track;        // fused drift: the step's largest speed (rebuild rule)
 };
-// Partials are written per brick (nblocks_out = number of bricks).
+// Partials are written per brick and part (nblocks_out = bricks x parts).
 hipError_t lj_force(const double* x, const double* y, const double* z, const int32_t* cell_start,
                     const Grid& g, const TileList& tl, const LJConst& c, int precision, bool energy,
                     const ForceOut& out, int64_t n, hipStream_t st, int* nblocks_out);

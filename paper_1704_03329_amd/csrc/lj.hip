@@ -98,6 +98,31 @@ __device__ __forceinline__ void block_track(const KickTrack& kt, double v2, doub
   }
 }
 
+// The workgroup's sums, at its brick and part: {pe, w}, or {pe, w, 2 ke}
+// when the kicks are fused.
+__device__ __forceinline__ void store_partials(const ForceOut& out, const Grid& g, int brick,
+                                               double pe, double w, double ke) {
+  const int64_t b = (int64_t)blockIdx.y * g.nbricks + brick;
+  if (out.fuse) {
+    out.partials[3 * b] = pe;
+    out.partials[3 * b + 1] = w;
+    out.partials[3 * b + 2] = ke;
+  } else {
+    out.partials[2 * b] = pe;
+    out.partials[2 * b + 1] = w;
+  }
+}
+
+// Sum over an aligned group of T lanes (a power of two up to 16), butterflies:
+// lane ^ 1 and lane ^ 2 on DPP, wider ones through LDS.
+template <typename V>
+__device__ __forceinline__ V group_sum(V v, int T) {
+  if (T > 1) v += dpp_move<0xB1>(v);
+  if (T > 2) v += dpp_move<0x4E>(v);
+  for (int off = 4; off < T; off <<= 1) v += __shfl_xor(v, off, 64);
+  return v;
+}
+
 // One workgroup per brick: the tile holds the image positions of the brick's
 // neighbourhood, so a pair needs one LDS gather and plain FP64 differences.
 // MT: arithmetic type of the pair force; OT: stored force type.  The pair
@@ -105,7 +130,9 @@ __device__ __forceinline__ void block_track(const KickTrack& kt, double v2, doub
 // instead of three of the separation).
 // Both passes ask for 8 waves per SIMD (<= 64 VGPRs), so that two
 // 1024-thread workgroups (LDS: two tiles) share a CU.
-template <typename MT, typename OT, bool ENERGY>
+// LPP: lanes per particle, each taking every LPP-th list word.  blockIdx.y:
+// the workgroup's part of the brick's particles (brick_parts).
+template <typename MT, typename OT, bool ENERGY, int LPP>
 __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8)))
 void k_lj_force(const double* __restrict__ x, const double* __restrict__ y,
                 const double* __restrict__ z, const int32_t* __restrict__ cs, Grid g, TileList tl,
@@ -122,7 +149,8 @@ void k_lj_force(const double* __restrict__ x, const double* __restrict__ y,
     if (out.fuse && threadIdx.x == 0) kick_store(out.track, 0.0);
     return;
   }
-  const int total = tile_cells(g, brick, cs, t);
+  // the tile tables as the list build left them
+  const int total = tile_tables_load(g, tl.tab + (int64_t)brick * kTabInts, t);
   if constexpr (ENERGY) tile_load<true>(g, x, y, z, total, t);
   else tile_load_xy(g, x, y, z, total, t);
   const int s0 = cs[brick * g.V], s1 = cs[(brick + 1) * g.V];
@@ -132,10 +160,10 @@ void k_lj_force(const double* __restrict__ x, const double* __restrict__ y,
   double scale = out.scale;
   if (out.scale_dev) scale *= *out.scale_dev;
   double e = 0.0, w = 0.0, ke = 0.0, vmax2 = 0.0;
-  // two lanes per particle, each taking every other list word (more waves in flight)
-  constexpr int LPP = 2;
   const int part = (int)threadIdx.x % LPP;
-  for (int s = s0 + (int)threadIdx.x / LPP; s < s1; s += (int)blockDim.x / LPP) {
+  const int step = (int)blockDim.x / LPP;
+  for (int s = s0 + (int)blockIdx.y * step + (int)threadIdx.x / LPP; s < s1;
+       s += (int)gridDim.y * step) {
     const double xi = x[s], yi = y[s], zi = z[s];
     // velocities for the fused kick: the plain pass loads them early so that
     // the pair loop hides the latency; the energy pass, short of registers,
@@ -207,13 +235,11 @@ void k_lj_force(const double* __restrict__ x, const double* __restrict__ y,
         az = __builtin_fma(g, dz, az);
       }
     }
-    if (LPP == 2) {
-      ax += __shfl_xor(ax, 1, 64);
-      ay += __shfl_xor(ay, 1, 64);
-      az += __shfl_xor(az, 1, 64);
-      if (ENERGY) ei += __shfl_xor(ei, 1, 64);
-      if (part) continue;
-    }
+    ax = group_sum(ax, LPP);
+    ay = group_sum(ay, LPP);
+    az = group_sum(az, LPP);
+    if (ENERGY) ei = group_sum(ei, LPP);
+    if (part) continue;
     if (out.fuse) {
       if (ENERGY) {
         vxi = out.vx[s];
@@ -258,14 +284,7 @@ void k_lj_force(const double* __restrict__ x, const double* __restrict__ y,
         ww += red[16 + k];
         kk += red[32 + k];
       }
-      if (out.fuse) {
-        out.partials[3 * brick] = pe;
-        out.partials[3 * brick + 1] = ww;
-        out.partials[3 * brick + 2] = kk;
-      } else {
-        out.partials[2 * brick] = pe;
-        out.partials[2 * brick + 1] = ww;
-      }
+      store_partials(out, g, brick, pe, ww, kk);
     }
   }
 }
@@ -368,20 +387,12 @@ __device__ __forceinline__ bool lane_group(int p0, int npart, int t, LaneGroup& 
   lg.T = T;
   return true;
 }
-template <typename V>
-__device__ __forceinline__ V group_sum(V v, int T) {
-  // butterflies: lane ^ 1 and lane ^ 2 on DPP, wider ones through LDS
-  if (T > 1) v += dpp_move<0xB1>(v);
-  if (T > 2) v += dpp_move<0x4E>(v);
-  for (int off = 4; off < T; off <<= 1) v += __shfl_xor(v, off, 64);
-  return v;
-}
-
 // Workgroup size of the plain FP32 pass (its LDS fits three workgroups per CU).
 #ifndef MDPL_PLAIN_THREADS
 #define MDPL_PLAIN_THREADS 512
 #endif
 constexpr int kPlainThreads = MDPL_PLAIN_THREADS;
+constexpr int kPartThreads = 256;  // of a part, where a brick has several (lane slots in turns)
 
 // Plain FP32 pass: the pair loop of every particle of the brick (its own
 // coordinates from its tile slot); the lanes of a wave take the same number
@@ -406,10 +417,14 @@ void k_lj_force32_plain(const double* __restrict__ x, const double* __restrict__
     if (out.fuse && threadIdx.x == 0) kick_store(out.track, 0.0);
     return;
   }
-  // the tile tables as the list build left them
-  const int total = tile_tables_load(g, tl.tab + (int64_t)brick * kTabInts, t);
   const int s0 = cs[brick * g.V], s1 = cs[(brick + 1) * g.V];
   const int npart = s1 - s0 < kBrickMax ? s1 - s0 : kBrickMax;  // more: flagged by the build
+  if ((int)(blockIdx.y * blockDim.x / kGroupWidth) * (kGroupWidth >> 1) >= npart && blockIdx.y) {
+    if (out.fuse && threadIdx.x == 0) kick_store(out.track, 0.0);
+    return;  // no particle left for this part
+  }
+  // the tile tables as the list build left them
+  const int total = tile_tables_load(g, tl.tab + (int64_t)brick * kTabInts, t);
   double ox, oy, oz;
   tile_centre(g, brick, ox, oy, oz);
   // The wave's pass and its lanes per particle are the same for all its lanes
@@ -418,7 +433,8 @@ void k_lj_force32_plain(const double* __restrict__ x, const double* __restrict__
   // wave's longest list part, lanes past their own part read the dummy
   // word), so that the band flags of a trip are one wave mask.
   const int lane = (int)threadIdx.x & 63;
-  const int wbase = __builtin_amdgcn_readfirstlane((int)threadIdx.x & ~63);
+  const int wbase =
+      __builtin_amdgcn_readfirstlane((int)(blockIdx.y * blockDim.x) + ((int)threadIdx.x & ~63));
   constexpr uint64_t kDummyWord = 0x0001000100010001ull * (uint64_t)(4 * TileF32::kDummy);
   // the count and first list word of the wave's first pass, loaded before
   // the tile so that their latency overlaps the tile's
@@ -442,7 +458,7 @@ void k_lj_force32_plain(const double* __restrict__ x, const double* __restrict__
   double scale = out.scale;
   if (out.scale_dev) scale *= *out.scale_dev;
   double vmax2 = 0.0;
-  for (int base = wbase;; base += blockDim.x) {
+  for (int base = wbase;; base += gridDim.y * blockDim.x) {
     const int p0 = (base / kGroupWidth) * (kGroupWidth >> 1);
     if (p0 >= npart) break;
     int m;
@@ -591,7 +607,8 @@ void k_lj_force32_energy(const double* __restrict__ x, const double* __restrict_
   if (out.scale_dev) scale *= *out.scale_dev;
   double e = 0.0, w = 0.0, ke = 0.0, vmax2 = 0.0;
   const double w24 = 24.0 * c.eps, e2 = 2.0 * c.eps, hshift = 0.5 * c.shift_v;
-  for (int slot = threadIdx.x; slot < npart * 2 + kGroupWidth; slot += blockDim.x) {
+  for (int slot = blockIdx.y * blockDim.x + threadIdx.x; slot < npart * 2 + kGroupWidth;
+       slot += gridDim.y * blockDim.x) {
     const int p0 = (slot / kGroupWidth) * (kGroupWidth >> 1);
     if (p0 >= npart) break;
     LaneGroup lg;
@@ -680,14 +697,7 @@ void k_lj_force32_energy(const double* __restrict__ x, const double* __restrict_
       ww += red[16 + q];
       kk += red[32 + q];
     }
-    if (out.fuse) {
-      out.partials[3 * brick] = pe;
-      out.partials[3 * brick + 1] = ww;
-      out.partials[3 * brick + 2] = kk;
-    } else {
-      out.partials[2 * brick] = pe;
-      out.partials[2 * brick + 1] = ww;
-    }
+    store_partials(out, g, brick, pe, ww, kk);
   }
 }
 
@@ -722,23 +732,25 @@ static F32Const f32_const(const Grid& g, const LJConst& c) {
   return k;
 }
 
-template <typename MT, typename OT>
+template <typename MT, typename OT, int LPP>
 static void launch_force(bool energy, hipStream_t st, const double* x, const double* y,
                          const double* z, const int32_t* cs, const Grid& g, const TileList& tl,
                          const LJConst& c, const ForceOut& out) {
-  const dim3 grid(tile_grid(g));
-  const unsigned two = 2 * tl.threads < 1024 ? 2 * tl.threads : 1024;
+  const dim3 grid(tile_grid(g), tl.parts);
+  const int per = (int)div_up((int64_t)LPP * tl.threads, tl.parts);  // lanes of a part
+  const unsigned th = per < 1024 ? (unsigned)((per + 63) & ~63) : 1024u;
   if (energy)
-    hipLaunchKernelGGL((k_lj_force<MT, OT, true>), grid, dim3(two), 0, st, x, y, z, cs, g, tl, c, out);
+    hipLaunchKernelGGL((k_lj_force<MT, OT, true, LPP>), grid, dim3(th), 0, st, x, y, z, cs, g, tl,
+                       c, out);
   else
-    hipLaunchKernelGGL((k_lj_force<MT, OT, false>), grid, dim3(two), 0, st, x, y, z, cs, g, tl, c,
-                       out);
+    hipLaunchKernelGGL((k_lj_force<MT, OT, false, LPP>), grid, dim3(th), 0, st, x, y, z, cs, g, tl,
+                       c, out);
 }
 
 hipError_t lj_force(const double* x, const double* y, const double* z, const int32_t* cell_start,
                     const Grid& g, const TileList& tl, const LJConst& c, int precision, bool energy,
                     const ForceOut& out, int64_t n, hipStream_t st, int* nblocks_out) {
-  if (nblocks_out) *nblocks_out = g.nbricks;
+  if (nblocks_out) *nblocks_out = g.nbricks * tl.parts;
   if (tl.cells) return lj_force_cells(x, y, z, cell_start, g, c, precision, energy, out, st);
   if (tl.half) return lj_force_half(x, y, z, cell_start, g, tl, c, precision, energy, out, n, st);
   // precision: 0 FP64 math/double out, 1 FP32 math/float out,
@@ -746,21 +758,27 @@ hipError_t lj_force(const double* x, const double* y, const double* z, const int
   switch (precision) {
     case 0:
     case 2:
-      launch_force<double, double>(energy, st, x, y, z, cell_start, g, tl, c, out);
+      if (tl.parts > 1)
+        launch_force<double, double, 8>(energy, st, x, y, z, cell_start, g, tl, c, out);
+      else
+        launch_force<double, double, 2>(energy, st, x, y, z, cell_start, g, tl, c, out);
       break;
     case 1: {
       const F32Const k = f32_const(g, c);
-      const dim3 grid(tile_grid(g));
+      const dim3 grid(tile_grid(g), tl.parts);
+      const bool one = tl.parts == 1;
       if (energy)
-        hipLaunchKernelGGL((k_lj_force32_energy<float>), grid, dim3(kEnergyThreads), 0, st, x, y, z,
-                           cell_start, g, tl, c, k, out);
+        hipLaunchKernelGGL((k_lj_force32_energy<float>), grid,
+                           dim3(one ? kEnergyThreads : kPartThreads), 0, st, x, y, z, cell_start,
+                           g, tl, c, k, out);
       else
-        hipLaunchKernelGGL((k_lj_force32_plain<float>), grid, dim3(kPlainThreads), 0, st, x, y, z,
-                           cell_start, g, tl, c, k, out);
+        hipLaunchKernelGGL((k_lj_force32_plain<float>), grid,
+                           dim3(one ? kPlainThreads : kPartThreads), 0, st, x, y, z, cell_start, g,
+                           tl, c, k, out);
       break;
     }
     default:
-      launch_force<float, double>(energy, st, x, y, z, cell_start, g, tl, c, out);
+      launch_force<float, double, 2>(energy, st, x, y, z, cell_start, g, tl, c, out);
       break;
   }
   return hipGetLastError();
