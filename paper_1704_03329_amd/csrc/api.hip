@@ -1011,19 +1011,18 @@ mdpl_status mdpl_run_andersen(mdpl_sim* s, double* x, double* y, double* z, doub
 static size_t analysis_bytes(int64_t n, const Grid& g, int max_nb) {
   size_t b = sort_bytes(n);
   b += align256(4 * (size_t)(g.nkeys + 1));
-  b += align256(4 * (size_t)n);          // perm
   b += 3 * align256(8 * (size_t)n);      // sorted positions
-  b += align256(4 * (size_t)n * (size_t)max_nb);
-  b += align256(4 * (size_t)n);          // cnt
+  b += 2 * align256(4 * (size_t)n);      // their FP32 copies, the third
+  b += align256(4 * (size_t)n * (size_t)max_nb);  // in an area of max_nb rows
   b += align256(64);
   return b;
 }
 
+// Validates, carves the workspace, sorts the particles by cell and gathers
+// their positions; small: word 0 set if a position lies outside the box, word 1 zero.
 static mdpl_status analysis_prep(const double* x, const double* y, const double* z, int64_t n,
                                  const double* box, double rc, int max_nb, void* ws, size_t bytes,
-                                 hipStream_t st, Grid* g, SortBufs* sb, int32_t** cs,
-                                 int32_t** perm, double** sx, double** sy, double** sz,
-                                 int32_t** skeys, NList* nl, uint32_t** small) {
+                                 hipStream_t st, Grid* g, BondScan* q, int32_t** small) {
   if (!x || !y || !z || !box || !ws || n <= 0 || n > (1ll << 26)) return MDPL_EINVAL;
   if (!(rc > 0.0) || !isfinite(rc) || max_nb < 1 || max_nb > 1024) return MDPL_EINVAL;
   for (int k = 0; k < 3; ++k)
@@ -1034,22 +1033,21 @@ static mdpl_status analysis_prep(const double* x, const double* y, const double*
   if (v != MDPL_OK) return v;
   if (bytes < analysis_bytes(n, *g, max_nb)) return MDPL_EWORKSPACE;
   char* w = (char*)ws;
-  sort_carve(w, n, sb);
-  *cs = take<int32_t>(w, 4 * (size_t)(g->nkeys + 1));
-  *perm = take<int32_t>(w, 4 * (size_t)n);
-  *sx = take<double>(w, 8 * (size_t)n);
-  *sy = take<double>(w, 8 * (size_t)n);
-  *sz = take<double>(w, 8 * (size_t)n);
-  nl->nbr = take<int32_t>(w, 4 * (size_t)n * (size_t)max_nb);
-  nl->cnt = take<int32_t>(w, 4 * (size_t)n);
-  nl->stride = n;
-  nl->max_nb = max_nb;
-  nl->layout = 1;
-  *small = take<uint32_t>(w, 64);
-  int32_t* svals;
-  HIP_TRY(bin_particles(x, y, z, n, *g, *sb, *cs, skeys, &svals, st));
-  HIP_TRY(hipMemcpyAsync(*perm, svals, 4 * (size_t)n, hipMemcpyDeviceToDevice, st));
-  HIP_TRY(gather_positions(x, y, z, *perm, n, *sx, *sy, *sz, box, false, st));
+  SortBufs sb;
+  sort_carve(w, n, &sb);
+  int32_t* cs = take<int32_t>(w, 4 * (size_t)(g->nkeys + 1));
+  // the FP32 copies before the FP64 positions: the screen loads past their ends
+  float* f0 = take<float>(w, 4 * (size_t)n);
+  float* f1 = take<float>(w, 4 * (size_t)n);
+  float* f2 = take<float>(w, 4 * (size_t)n * (size_t)max_nb);
+  double* sx = take<double>(w, 8 * (size_t)n);
+  double* sy = take<double>(w, 8 * (size_t)n);
+  double* sz = take<double>(w, 8 * (size_t)n);
+  *small = take<int32_t>(w, 64);
+  int32_t *skeys, *svals;
+  HIP_TRY(bin_particles(x, y, z, n, *g, sb, cs, &skeys, &svals, st, nullptr, *small));
+  HIP_TRY(gather_analysis(x, y, z, svals, n, box, sx, sy, sz, f0, f1, f2, *small, st));
+  *q = BondScan{sx, sy, sz, f0, f1, f2, skeys, cs, svals};
   return MDPL_OK;
 }
 
@@ -1102,16 +1100,11 @@ mdpl_status mdpl_boa(const double* x, const double* y, const double* z, int64_t 
   if (!q4 || !q6 || !nnb) return MDPL_EINVAL;
   hipStream_t st = (hipStream_t)stream;
   Grid g;
-  SortBufs sb;
-  int32_t *cs, *perm, *skeys;
-  double *sx, *sy, *sz;
-  NList nl;
-  uint32_t* small;
-  // the bond-order pass walks the cells itself: no list is stored
-  mdpl_status v = analysis_prep(x, y, z, n, box, rc, 1, ws, bytes, st, &g, &sb, &cs, &perm, &sx,
-                                &sy, &sz, &skeys, &nl, &small);
+  BondScan q;
+  int32_t* small;
+  mdpl_status v = analysis_prep(x, y, z, n, box, rc, 1, ws, bytes, st, &g, &q, &small);
   if (v != MDPL_OK) return v;
-  HIP_TRY(boa_q(sx, sy, sz, skeys, cs, perm, n, g, rc * rc, q4, q5, q6, nnb, st));
+  HIP_TRY(boa_q(q, n, g, rc * rc, q4, q5, q6, nnb, st));
   return MDPL_OK;
 }
 
@@ -1135,17 +1128,11 @@ mdpl_status mdpl_cna(const double* x, const double* y, const double* z, int64_t 
   if (!trip || !nnb || !label || max_nb < 1 || max_nb > 64) return MDPL_EINVAL;
   hipStream_t st = (hipStream_t)stream;
   Grid g;
-  SortBufs sb;
-  int32_t *cs, *perm, *skeys;
-  double *sx, *sy, *sz;
-  NList nl;
-  uint32_t* small;
-  mdpl_status v = analysis_prep(x, y, z, n, box, rc, max_nb, ws, bytes, st, &g, &sb, &cs, &perm,
-                                &sx, &sy, &sz, &skeys, &nl, &small);
+  BondScan q;
+  int32_t* small;
+  mdpl_status v = analysis_prep(x, y, z, n, box, rc, max_nb, ws, bytes, st, &g, &q, &small);
   if (v != MDPL_OK) return v;
-  HIP_TRY(hipMemsetAsync(small, 0, 64, st));
-  HIP_TRY(build_nlist(sx, sy, sz, skeys, cs, n, g, rc * rc, nl, small, (int32_t*)(small + 1), st));
-  HIP_TRY(cna_signatures(nl, sx, sy, sz, g, rc * rc, perm, n, trip, nnb, label, max_nb, st));
+  HIP_TRY(cna_signatures(q, n, g, rc * rc, max_nb, trip, nnb, label, small, small + 1, st));
   if (max_count)
     HIP_TRY(hipMemcpyAsync(max_count, small + 1, 4, hipMemcpyDeviceToDevice, st));
   return MDPL_OK;

@@ -109,8 +109,10 @@ __global__ __launch_bounds__(256) void k_xhalf_partition(const int32_t* __restri
 
 __global__ void k_cell_keys(const double* __restrict__ x, const double* __restrict__ y,
                             const double* __restrict__ z, int64_t n, Grid g,
-                            int32_t* __restrict__ keys, int32_t* __restrict__ vals, int xbit) {
+                            int32_t* __restrict__ keys, int32_t* __restrict__ vals, int xbit,
+                            int32_t* __restrict__ clear) {
   int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (clear && i < 16) clear[i] = 0;
   if (i >= n) return;
   int cx = cell_coord(x[i], g.box[0], g.inv_side[0], g.nc[0]);
   // xbit: the top bit of the value marks the upper half of the cell along x
@@ -285,10 +287,10 @@ hipError_t exclusive_scan(const int32_t* in, int32_t* out, int64_t n, int32_t* b
 
 hipError_t bin_particles(const double* x, const double* y, const double* z, int64_t n,
                          const Grid& g, SortBufs& s, int32_t* cell_start, int32_t** keys_out,
-                         int32_t** vals_out, hipStream_t st, int32_t* xlow) {
+                         int32_t** vals_out, hipStream_t st, int32_t* xlow, int32_t* clear) {
   const unsigned nb = (unsigned)div_up(n, 256);
   hipLaunchKernelGGL(k_cell_keys, dim3(nb), dim3(256), 0, st, x, y, z, n, g, s.keys[0], s.vals[0],
-                     xlow ? 1 : 0);
+                     xlow ? 1 : 0, clear);
   int bits = 1;
   while ((1ll << bits) < (long long)g.nkeys) ++bits;
   const int passes = (bits + kRadixBits - 1) / kRadixBits;
@@ -344,6 +346,35 @@ hipError_t gather_positions(const double* x, const double* y, const double* z, c
                             bool do_fold, hipStream_t st) {
   hipLaunchKernelGGL(k_gather_pos, dim3((unsigned)div_up(n, 256)), dim3(256), 0, st, x, y, z, idx,
                      n, ox, oy, oz, box[0], box[1], box[2], do_fold ? 1 : 0);
+  return hipGetLastError();
+}
+
+__global__ void k_gather_analysis(const double* __restrict__ x, const double* __restrict__ y,
+                                  const double* __restrict__ z, const int32_t* __restrict__ idx,
+                                  int64_t n, double Lx, double Ly, double Lz,
+                                  double* __restrict__ ox, double* __restrict__ oy,
+                                  double* __restrict__ oz, float* __restrict__ px,
+                                  float* __restrict__ py, float* __restrict__ pz,
+                                  int32_t* __restrict__ outside) {
+  const int64_t s = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (s >= n) return;
+  const int32_t j = idx[s];
+  const double a = x[j], b = y[j], c = z[j];
+  ox[s] = a;
+  oy[s] = b;
+  oz[s] = c;
+  const double fa = fold(a, Lx), fb = fold(b, Ly), fc = fold(c, Lz);
+  px[s] = (float)fa;
+  py[s] = (float)fb;
+  pz[s] = (float)fc;
+  if (fa != a || fb != b || fc != c) *outside = 1;
+}
+
+hipError_t gather_analysis(const double* x, const double* y, const double* z, const int32_t* idx,
+                           int64_t n, const double* box, double* ox, double* oy, double* oz,
+                           float* px, float* py, float* pz, int32_t* outside, hipStream_t st) {
+  hipLaunchKernelGGL(k_gather_analysis, dim3((unsigned)div_up(n, 256)), dim3(256), 0, st, x, y, z,
+                     idx, n, box[0], box[1], box[2], ox, oy, oz, px, py, pz, outside);
   return hipGetLastError();
 }
 

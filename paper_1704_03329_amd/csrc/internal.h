@@ -67,9 +67,11 @@ void sort_carve(char*& p, int64_t n, SortBufs* s);
 // Sort particles by cell: keys computed from (folded) positions, values =
 // particle index.  On return keys_out/vals_out point at the sorted arrays
 // (one of the two ping-pong buffers) and cell_start[0..ncells] is filled.
+// clear (nullable): 16 words set to zero on the way.
 hipError_t bin_particles(const double* x, const double* y, const double* z, int64_t n,
                          const Grid& g, SortBufs& s, int32_t* cell_start, int32_t** keys_out,
-                         int32_t** vals_out, hipStream_t st, int32_t* xlow = nullptr);
+                         int32_t** vals_out, hipStream_t st, int32_t* xlow = nullptr,
+                         int32_t* clear = nullptr);
 
 // Exclusive prefix sum of n int32 values into out (may alias in).  Uses
 // blocksums scratch of at least div_up(n, 1024) + 1 entries.  Also writes
@@ -81,6 +83,12 @@ hipError_t exclusive_scan(const int32_t* in, int32_t* out, int64_t n, int32_t* b
 hipError_t gather_positions(const double* x, const double* y, const double* z, const int32_t* idx,
                             int64_t n, double* ox, double* oy, double* oz, const double* box,
                             bool fold, hipStream_t st);
+
+// The analyses' gather: positions as stored, and FP32 copies folded into the
+// box; *outside becomes 1 if folding moved any of them (zero beforehand).
+hipError_t gather_analysis(const double* x, const double* y, const double* z, const int32_t* idx,
+                           int64_t n, const double* box, double* ox, double* oy, double* oz,
+                           float* px, float* py, float* pz, int32_t* outside, hipStream_t st);
 
 // Like gather_positions, but each position is moved to the periodic image
 // nearest the centre of its cell in the sorted keys skeys.
@@ -103,20 +111,6 @@ hipError_t reorder_state(const StateArrays& src, const int32_t* idx, int64_t n, 
 // dst[a] = src[a] for each of the ten arrays whose pointers differ (one launch).
 hipError_t copy_state(const StateArrays& src, const StateArrays& dst, int64_t n, int fbytes,
                       hipStream_t st);
-
-// Neighbour list (ELL) of the analysis passes: row-major nbr[i * max_nb + m]
-// of sorted-slot indices; cnt[i] is the true count (may exceed max_nb).
-// Requires a grid with B = (1,1,1).
-struct NList {
-  int32_t* nbr;
-  int32_t* cnt;
-  int64_t stride;
-  int max_nb;
-  int layout;
-};
-hipError_t build_nlist(const double* sx, const double* sy, const double* sz,
-                       const int32_t* skeys, const int32_t* cell_start, int64_t n, const Grid& g,
-                       double r2, NList nl, uint32_t* flags, int32_t* maxcount, hipStream_t st);
 
 // Tiled neighbour list of the LJ path.  One workgroup per brick stages the
 // positions of the brick's (B+2)^3-cell neighbourhood (its "tile") in LDS;
@@ -326,18 +320,23 @@ hipError_t disp_partials(const double* x, const double* y, const double* z, cons
 hipError_t skin_check(const double* partials, int nblocks, double half_skin, double* max_disp,
                       uint32_t* flags, hipStream_t st);
 
-// Analysis kernels on sorted positions.
-hipError_t boa_q(const double* sx, const double* sy, const double* sz, const int32_t* skeys,
-                 const int32_t* cell_start, const int32_t* perm, int64_t n, const Grid& g,
-                 double rc2, float* q4, float* q5, float* q6, int32_t* nnb, hipStream_t st);
-
-// CNA of every particle from its complete list (adjacency among its
-// neighbours from the exact bond test on the sorted positions sx, sy, sz).
-hipError_t cna_signatures(const NList& nl, const double* sx, const double* sy, const double* sz,
-                          const Grid& g, double rc2, const int32_t* perm, int64_t n,
-                          uint32_t* trip, int32_t* nnb, uint8_t* label, int max_out,
-                          hipStream_t st);
-
+// What the structure analyses read: particles sorted by cell (a grid with
+// B = (1,1,1)): stored FP64 positions, FP32 copies folded into the box, the
+// cell of each slot, the cells' first slots and the caller's indices.
+struct BondScan {
+  const double *sx, *sy, *sz;
+  const float *px, *py, *pz;
+  const int32_t* skeys;
+  const int32_t* cs;
+  const int32_t* perm;
+};
+hipError_t boa_q(const BondScan& q, int64_t n, const Grid& g, double rc2, float* q4, float* q5,
+                 float* q6, int32_t* nnb, hipStream_t st);
+// outside (device): not zero if a stored position lies outside the box;
+// maxcount (device, zero beforehand) receives the largest bond count.
+hipError_t cna_signatures(const BondScan& q, int64_t n, const Grid& g, double rc2, int max_nb,
+                          uint32_t* trip, int32_t* nnb, uint8_t* label, const int32_t* outside,
+                          int32_t* maxcount, hipStream_t st);
 
 // Learned potential: descriptors (desc.hip) and dense layers (mlp.hip).
 // desc_forward also clears fx, fy, fz (caller order) when they are given, so

@@ -8,8 +8,7 @@
 // with floating-point contraction off, on the caller's FP64 values, so the
 // list is bit-identical to the all-pairs definition.
 //
-// Two builders:
-//  * the LJ list: one workgroup per brick stages its tile (stored positions,
+// The builder: one workgroup per brick stages its tile (stored positions,
 //    no images) in LDS, one wave per home cell tests the 27 tile cells of its
 //    stencil (a full list: each cell's particles of the lower half along x
 //    first, so that a particle skips the half of the next or previous cell
@@ -17,10 +16,7 @@
 //    pass reads one coalesced word per four neighbours.  A half list (each
 //    pair once, Newton's third law) keeps j in the list of i only if j's tile
 //    index is larger (tile.h): four of the nine stencil rows whole, and the
-//    row of i's cell from i on;
-//  * the analysis list (bond order / CNA): one thread per particle walks the
-//    9 rows of 3 consecutive cells in global memory, entries are sorted-slot
-//    indices, row-major so a whole list is one contiguous read.
+//    row of i's cell from i on.
 #include <math.h>
 
 #include <type_traits>
@@ -391,81 +387,6 @@ hipError_t export_tile_pairs(const TileList& tl, const int32_t* cell_start, cons
                              int32_t* j_out, int64_t cap, hipStream_t st) {
   hipLaunchKernelGGL(k_export_tile_pairs, dim3(tile_grid(g)), dim3(tl.threads), 0,
                      st, tl, cell_start, g, perm, offsets, i_out, j_out, cap);
-  return hipGetLastError();
-}
-
-// ------------------------------------------------------------ analysis list
-__global__ __launch_bounds__(256) void k_build_nlist(
-    const double* __restrict__ sx, const double* __restrict__ sy, const double* __restrict__ sz,
-    const int32_t* __restrict__ skeys, const int32_t* __restrict__ cs, int64_t n, Grid g, double r2,
-    NList nl, uint32_t* __restrict__ flags, int32_t* __restrict__ maxcount) {
-  const int64_t s = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  int count = 0;
-  if (s < n) {
-    const double xi = sx[s], yi = sy[s], zi = sz[s];
-    const double Lx = g.box[0], Ly = g.box[1], Lz = g.box[2];
-    const double hx = 0.5 * Lx, hy = 0.5 * Ly, hz = 0.5 * Lz;
-    const int n0 = g.nc[0], n1 = g.nc[1], n2 = g.nc[2];
-    const int key = skeys[s];  // B = (1,1,1): x-fastest cell index
-    const int cx = key % n0;
-    const int cy = (key / n0) % n1;
-    const int cz = key / (n0 * n1);
-    const int max_nb = nl.max_nb;
-    for (int oz = -1; oz <= 1; ++oz) {
-      int z2 = cz + oz;
-      z2 += (z2 < 0) ? n2 : 0;
-      z2 -= (z2 >= n2) ? n2 : 0;
-      for (int oy = -1; oy <= 1; ++oy) {
-        int y2 = cy + oy;
-        y2 += (y2 < 0) ? n1 : 0;
-        y2 -= (y2 >= n1) ? n1 : 0;
-        const int row = (z2 * n1 + y2) * n0;
-        int b[3], e[3], nr;
-        if (cx >= 1 && cx <= n0 - 2) {
-          b[0] = cs[row + cx - 1];
-          e[0] = cs[row + cx + 2];
-          nr = 1;
-        } else {
-          const int xm = (cx == 0) ? n0 - 1 : cx - 1;
-          const int xp = (cx == n0 - 1) ? 0 : cx + 1;
-          b[0] = cs[row + xm];
-          e[0] = cs[row + xm + 1];
-          b[1] = cs[row + cx];
-          e[1] = cs[row + cx + 1];
-          b[2] = cs[row + xp];
-          e[2] = cs[row + xp + 1];
-          nr = 3;
-        }
-        for (int r = 0; r < nr; ++r) {
-          for (int t = b[r]; t < e[r]; ++t) {
-            if (t == s) continue;
-            const double d2 = exact_d2(xi, yi, zi, sx[t], sy[t], sz[t], Lx, Ly, Lz, hx, hy, hz);
-            if (d2 < r2) {
-              if (count < max_nb) nl.nbr[s * (int64_t)max_nb + count] = t;
-              ++count;
-            }
-          }
-        }
-      }
-    }
-    nl.cnt[s] = count;  // true count: callers see an overflow per particle
-    if (count > max_nb) atomicOr(flags, MDPL_FLAG_NL_OVERFLOW);
-  }
-  int m = count;
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) {
-    const int o = __shfl_xor(m, off, 64);
-    m = o > m ? o : m;
-  }
-  if ((threadIdx.x & 63) == 0 && m > 0) atomicMax(maxcount, m);
-}
-
-hipError_t build_nlist(const double* sx, const double* sy, const double* sz,
-                       const int32_t* skeys, const int32_t* cell_start, int64_t n, const Grid& g,
-                       double r2, NList nl, uint32_t* flags, int32_t* maxcount, hipStream_t st) {
-  if (g.V != 1) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(k_build_nlist, dim3((unsigned)div_up(n, 256)), dim3(256), 0, st, sx, sy, sz,
-                     skeys, cell_start, n, g, r2, nl, flags, maxcount);
   return hipGetLastError();
 }
 
