@@ -313,7 +313,7 @@ hipError_t boa_q(const BondScan& q, int64_t n, const Grid& g, double rc2, float*
 }
 
 // ------------------------------------------------------------------- CNA
-constexpr int kCnaQueue = 24;  // noted candidates per lane, at most kept in registers
+constexpr int kCnaQueue = 32;  // noted candidates per lane, at most kept in registers
 
 __device__ __forceinline__ uint32_t pack_triplet(int ncn, int nb, int nlcb) {
   return ((uint32_t)ncn << 20) | ((uint32_t)nb << 10) | (uint32_t)nlcb;
@@ -360,7 +360,7 @@ __device__ __forceinline__ void sort_network(uint32_t (&c)[N]) {
 // (col[0 .. c), N a constant so that separations and masks stay in
 // registers); unfolded: some particle's stored position lies outside the
 // box.  Returns the bond count, or -1 where the exact test of a pair
-// of neighbours is needed (nothing is written then).
+// of neighbours is needed (nothing is written then, col stays as it was).
 template <int N>
 __device__ __forceinline__ int cna_lane(const BondScan& q, const Grid& g, double rc2, int s, int c,
                                         uint32_t* __restrict__ col, const CnaOut& out,
@@ -399,10 +399,11 @@ __device__ __forceinline__ int cna_lane(const BondScan& q, const Grid& g, double
     }
     __builtin_amdgcn_sched_barrier(0);
   }
-  // The members bonded to each other, from the FP32 separations (each within
-  // 2^-24 rc of the FP64 one, so that a squared distance near rc^2 is within
-  // 2 sqrt(3) rc 2^-22 rc + 5 2^-24 rc^2 < 1.2 10^-6 rc^2).  A pair within
-  // 5 10^-6 rc^2 of the cutoff needs the exact test, as do positions outside
+  // The members bonded to each other, from the FP32 separations (each
+  // component within 2^-24 rc of the FP64 one, their difference within 3 2^-24
+  // rc, so that a squared distance near rc^2 is within (6 sqrt(3) + 4) 2^-24
+  // rc^2 < 9 10^-7 rc^2 of the exact one).  A pair within 2 10^-6 rc^2 of the
+  // cutoff needs the exact test, as do positions outside
   // the box (whose images the conditional wrap of the definition may miss).
   const float r2 = (float)rc2;
   // Every member takes the sign bits of its pairs one by one, partners in
@@ -424,6 +425,11 @@ __device__ __forceinline__ int cna_lane(const BondScan& q, const Grid& g, double
       if ((b - a) % 4 == 1) __builtin_amdgcn_sched_barrier(0);  // few pairs in flight
     }
   }
+  // (the masks are to be complete here: moved below the return, their inputs
+  // would all have to live until then)
+#pragma unroll
+  for (int k = 0; k < N; ++k) asm volatile("" : "+v"(adj[k]));
+  if (near <= 2e-6f * r2 || odd) return -1;
   // the masks in the lane's column: row b is bond b's common neighbours until
   // its triplet replaces them
 #pragma unroll
@@ -432,7 +438,6 @@ __device__ __forceinline__ int cna_lane(const BondScan& q, const Grid& g, double
     adj[k] &= bonds;
     col[k * kQPitch] = adj[k];
   }
-  if (near <= 5e-6f * r2 || odd) return -1;
   const int ni = __popc(bonds);
   int b = 0;
   for (uint32_t rest = bonds; rest; rest &= rest - 1) {
@@ -516,6 +521,8 @@ __device__ __forceinline__ void wave_lds_fence() {
 
 // All bonds of slot s by the whole wave (exact test of every stencil
 // candidate): their number, and the slots of the first 64 in list (LDS).
+// The 27 cells' ranges are laid end to end over the lanes, so that a stencil
+// takes one or two rounds of loads.
 __device__ inline int bonds_of(const BondScan& q, const Grid& g, double rc2, int s,
                                uint32_t* __restrict__ list) {
   const int lane = (int)threadIdx.x & 63;
@@ -524,25 +531,56 @@ __device__ inline int bonds_of(const BondScan& q, const Grid& g, double rc2, int
   const int n0 = g.nc[0], n1 = g.nc[1], n2 = g.nc[2];
   const int key = q.skeys[s];
   const int cx = key % n0, cy = (key / n0) % n1, cz = key / (n0 * n1);
+  // lane c < 27: its cell's first slot and the candidates before it
+  const int x2 = (cx + lane % 3 - 1 + n0) % n0, y2 = (cy + (lane / 3) % 3 - 1 + n1) % n1;
+  const int z2 = (cz + (lane / 9) % 3 - 1 + n2) % n2;
+  const int cell = (z2 * n1 + y2) * n0 + x2;
+  const int start = q.cs[cell];
+  int upto = lane < 27 ? q.cs[cell + 1] - start : 0;
+#pragma unroll
+  for (int off = 1; off < 32; off <<= 1) {
+    const int o = __shfl_up(upto, off, 64);
+    if (lane >= off) upto += o;
+  }
+  const int total = __shfl(upto, 26, 64);
   int found = 0;
   wave_lds_fence();
-  for (int c = 0; c < 27; ++c) {
-    const int x2 = (cx + c % 3 - 1 + n0) % n0, y2 = (cy + (c / 3) % 3 - 1 + n1) % n1;
-    const int z2 = (cz + c / 9 - 1 + n2) % n2;
-    const int cell = (z2 * n1 + y2) * n0 + x2;
-    const int e = q.cs[cell + 1];
-    for (int t0 = q.cs[cell]; t0 < e; t0 += 64) {
-      const int t = t0 + lane < e ? t0 + lane : s;
-      const bool in = t != s && exact_d2(xi, yi, zi, q.sx[t], q.sy[t], q.sz[t], Lx, Ly, Lz,
-                                         0.5 * Lx, 0.5 * Ly, 0.5 * Lz) < rc2;
-      const uint64_t m = __ballot(in);
-      const int at = found + __popcll(m & ((1ull << lane) - 1));
-      if (in && at < 64) list[at] = (uint32_t)t;
-      found += __popcll(m);
+  for (int u0 = 0; u0 < total; u0 += 64) {
+    const int u = u0 + lane;
+    int c = 0;  // the cell of candidate u: the first with upto > u
+#pragma unroll
+    for (int step = 16; step; step >>= 1) {
+      const int below = __shfl(upto, c + step - 1, 64);  // lanes past 26 hold the total
+      c += below <= u ? step : 0;
     }
+    c = c < 26 ? c : 26;
+    const int before = __shfl(upto, c > 0 ? c - 1 : 0, 64), first = __shfl(start, c, 64);
+    const int t = u < total ? first + u - (c > 0 ? before : 0) : s;
+    const bool in = t != s && exact_d2(xi, yi, zi, q.sx[t], q.sy[t], q.sz[t], Lx, Ly, Lz,
+                                       0.5 * Lx, 0.5 * Ly, 0.5 * Lz) < rc2;
+    const uint64_t m = __ballot(in);
+    const int at = found + __popcll(m & ((1ull << lane) - 1));
+    if (in && at < 64) list[at] = (uint32_t)t;
+    found += __popcll(m);
   }
   wave_lds_fence();
   return found;
+}
+
+// The bonds of slot s among its noted candidates (c of them, lane k's in
+// row k of the column): their number, their slots in list.
+__device__ inline int bonds_noted(const BondScan& q, const Grid& g, double rc2, int s, int c,
+                                  const uint32_t* __restrict__ col, uint32_t* __restrict__ list) {
+  const int lane = (int)threadIdx.x & 63;
+  const double Lx = g.box[0], Ly = g.box[1], Lz = g.box[2];
+  const uint32_t t = lane < c ? col[lane * kQPitch] : (uint32_t)s;
+  const bool in = lane < c && exact_d2(q.sx[s], q.sy[s], q.sz[s], q.sx[t], q.sy[t], q.sz[t], Lx, Ly,
+                                       Lz, 0.5 * Lx, 0.5 * Ly, 0.5 * Lz) < rc2;
+  const uint64_t m = __ballot(in);
+  wave_lds_fence();
+  if (in) list[__popcll(m & ((1ull << lane) - 1))] = t;
+  wave_lds_fence();
+  return __popcll(m);
 }
 
 // The signature of slot s by the whole wave, lane b its bond b (ni <= 64 of
@@ -622,10 +660,11 @@ __device__ inline void cna_wave(const BondScan& q, const Grid& g, double rc2, in
 // lane per particle with its masks in LDS (2413), whose loops over ragged
 // lists and graphs kept most lanes waiting.
 constexpr int kCnaThreads = 256;
-__global__ __launch_bounds__(kCnaThreads) __attribute__((amdgpu_waves_per_eu(4)))
+__global__ __launch_bounds__(kCnaThreads) __attribute__((amdgpu_waves_per_eu(3)))
 void k_cna(BondScan q, int64_t n, Grid g, double rc2, float r2s, CnaOut out,
            const int32_t* __restrict__ outside, int32_t* __restrict__ maxcount) {
   __shared__ uint32_t queue[kCnaThreads / 64][kCnaQueue * kQPitch];
+  __shared__ uint32_t lists[kCnaThreads / 64][64];
   const int lane = (int)threadIdx.x & 63;
   const int base = (int)(blockIdx.x * kCnaThreads + ((int)threadIdx.x & ~63));
   if (base >= n) return;
@@ -644,6 +683,7 @@ void k_cna(BondScan q, int64_t n, Grid g, double rc2, float r2s, CnaOut out,
     if (cm <= 12) ni = cna_lane<12>(q, g, rc2, s, c, wq + lane, out, unfolded);
     else if (cm <= 14) ni = cna_lane<14>(q, g, rc2, s, c, wq + lane, out, unfolded);
     else if (cm <= 18) ni = cna_lane<18>(q, g, rc2, s, c, wq + lane, out, unfolded);
+    else if (cm <= 24) ni = cna_lane<24>(q, g, rc2, s, c, wq + lane, out, unfolded);
     else ni = cna_lane<kCnaQueue>(q, g, rc2, s, c, wq + lane, out, unfolded);
   }
   int most = ni > 0 ? ni : 0;
@@ -651,9 +691,12 @@ void k_cna(BondScan q, int64_t n, Grid g, double rc2, float r2s, CnaOut out,
   while (todo) {
     const int p = __builtin_ctzll(todo);
     todo &= todo - 1;
-    const int nw = bonds_of(q, g, rc2, base + p, wq);
+    const int cp = __shfl(kept, p, 64);
+    uint32_t* const list = lists[threadIdx.x >> 6];
+    const int nw = cp < kCnaQueue ? bonds_noted(q, g, rc2, base + p, cp, wq + p, list)
+                                  : bonds_of(q, g, rc2, base + p, list);
     if (nw <= 64) {
-      cna_wave(q, g, rc2, base + p, nw, wq, out);
+      cna_wave(q, g, rc2, base + p, nw, list, out);
     } else if (lane == 0) {
       const int32_t o = q.perm[base + p];
       out.nnb[o] = nw;
