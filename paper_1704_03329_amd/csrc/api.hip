@@ -528,14 +528,10 @@ mdpl_status mdpl_sim_destroy(mdpl_sim* s) {
 mdpl_status mdpl_build(mdpl_sim* s, const double* x, const double* y, const double* z) {
   if (!s || !x || !y || !z) return MDPL_EINVAL;
   s->resume.valid = false;
-  int32_t *skeys, *svals;
-  HIP_TRY(bin_particles(x, y, z, s->n, s->g, s->sort, s->cell_start, &skeys, &svals, s->st,
-                        list_xlow(s)));
-  HIP_TRY(hipMemcpyAsync(s->perm, svals, 4 * (size_t)s->n, hipMemcpyDeviceToDevice, s->st));
-  s->skeys = skeys;
-  HIP_TRY(gather_positions(x, y, z, s->perm, s->n, s->sx, s->sy, s->sz, s->p.box, true, s->st));
+  HIP_TRY(sort_build(x, y, z, s->n, s->g, s->sort, s->cell_start, list_xlow(s), &s->skeys, s->perm,
+                     s->sx, s->sy, s->sz, s->st));
   if (!s->tl.cells)
-    HIP_TRY(build_tile_nlist(s->sx, s->sy, s->sz, skeys, s->cell_start, s->g, s->r2ext, s->tl,
+    HIP_TRY(build_tile_nlist(s->sx, s->sy, s->sz, s->cell_start, s->g, s->r2ext, s->tl,
                              s->flags, s->maxcount, s->st));
   s->built = true;
   s->have_list = !s->tl.cells;
@@ -766,6 +762,12 @@ mdpl_status rule_decide(mdpl_sim* s, bool* need) {
   return MDPL_OK;
 }
 
+// The displacement check of positions x, y, z against the last list build.
+MoveCheck move_check(mdpl_sim* s, const double* x, const double* y, const double* z,
+                     double half_skin) {
+  return MoveCheck{x, y, z, s->xb, s->yb, s->zb, s->partials, half_skin, s->max_disp, s->flags};
+}
+
 bool same_arrays(const StateArrays& a, const StateArrays& b) {
   return a.x == b.x && a.y == b.y && a.z == b.z && a.vx == b.vx && a.vy == b.vy && a.vz == b.vz &&
          a.fx == b.fx && a.fy == b.fy && a.fz == b.fz && a.ids == b.ids;
@@ -812,22 +814,15 @@ mdpl_status run_loop(mdpl_sim* s, StateArrays user, int64_t nsteps, int32_t samp
   // check: the displacement of the last force pass with the old list (in
   // spare, the drift's other buffer) against half the skin
   auto rebuild = [&](bool check, bool early) -> mdpl_status {
-    if (check && s->have_ref) {
-      int nb = 0;
-      HIP_TRY(disp_partials(spare[0], spare[1], spare[2], s->xb, s->yb, s->zb, n, s->partials,
-                            s->st, &nb));
-      HIP_TRY(skin_check(s->partials, nb, half_skin, s->max_disp, s->flags, s->st));
-    }
-    int32_t *skeys, *svals;
-    HIP_TRY(bin_particles(cur.x, cur.y, cur.z, n, s->g, s->sort, s->cell_start, &skeys, &svals,
-                          s->st, list_xlow(s)));
-    HIP_TRY(reorder_state(cur, svals, n, s->fbytes, s->p.box, other, s->xb, s->yb, s->zb,
-                          s->bound, s->st));
+    MoveCheck mc{};
+    if (check && s->have_ref) mc = move_check(s, spare[0], spare[1], spare[2], half_skin);
+    HIP_TRY(sort_state(cur, other, n, s->fbytes, s->g, s->sort, s->cell_start, list_xlow(s), s->xb,
+                       s->yb, s->zb, s->bound, mc, s->st));
     StateArrays t = cur;
     cur = other;
     other = t;
     if (!s->tl.cells)
-      HIP_TRY(build_tile_nlist(cur.x, cur.y, cur.z, skeys, s->cell_start, s->g, s->r2ext, s->tl,
+      HIP_TRY(build_tile_nlist(cur.x, cur.y, cur.z, s->cell_start, s->g, s->r2ext, s->tl,
                                s->flags, s->maxcount, s->st));
     s->have_ref = true;
     s->have_list = !s->tl.cells;
@@ -945,8 +940,7 @@ mdpl_status run_loop(mdpl_sim* s, StateArrays user, int64_t nsteps, int32_t samp
                     &nb, collide(nsteps)));
     if (ke) HIP_TRY(reduce_partials(s->partials, nb, 1, 1, row(nsteps), ke_scale, s->st));
     // close the last reuse period: the final positions were used by the last pass
-    HIP_TRY(disp_partials(cur.x, cur.y, cur.z, s->xb, s->yb, s->zb, n, s->partials, s->st, &nb));
-    HIP_TRY(skin_check(s->partials, nb, half_skin, s->max_disp, s->flags, s->st));
+    HIP_TRY(skin_check(move_check(s, cur.x, cur.y, cur.z, half_skin), n, s->st));
   }
   // the state ends wherever the ping-pong left it: copy back what is not in the caller's arrays
   HIP_TRY(copy_state(cur, user, n, s->fbytes, s->st));
@@ -1044,10 +1038,9 @@ static mdpl_status analysis_prep(const double* x, const double* y, const double*
   double* sy = take<double>(w, 8 * (size_t)n);
   double* sz = take<double>(w, 8 * (size_t)n);
   *small = take<int32_t>(w, 64);
-  int32_t *skeys, *svals;
-  HIP_TRY(bin_particles(x, y, z, n, *g, sb, cs, &skeys, &svals, st, nullptr, *small));
-  HIP_TRY(gather_analysis(x, y, z, svals, n, box, sx, sy, sz, f0, f1, f2, *small, st));
-  *q = BondScan{sx, sy, sz, f0, f1, f2, skeys, cs, svals};
+  int32_t *skeys, *perm;
+  HIP_TRY(sort_analysis(x, y, z, n, *g, sb, cs, &skeys, &perm, sx, sy, sz, f0, f1, f2, *small, st));
+  *q = BondScan{sx, sy, sz, f0, f1, f2, skeys, cs, perm};
   return MDPL_OK;
 }
 

@@ -1,11 +1,16 @@
-// Cell binning by counting sort (Sec. 3.5: every particle belongs to exactly
-// one cell of side >= the list radius; the GPU cell-occupancy idea of the
-// "Threading and GPU parallelisation" paragraph is realised here as a stable
-// LSD radix sort of cell keys).
+// Cell binning (Sec. 3.5: every particle belongs to exactly one cell of side
+// >= the list radius) by counting sort, and the moves of the particles into
+// the sorted order.
 //
-// Atomics stay in LDS: per-tile digit histograms use LDS atomics, ranks
-// inside a tile come from wavefront ballots, tile offsets from a
-// device-wide exclusive scan.  No global atomics, results are deterministic.
+// The particles of a cell are counted with one atomic per run of equal keys
+// in a wave, placed behind their cell's start in order of arrival, and each
+// then finds its final place by counting the smaller values in its cell (the
+// lower half of the cell along x first where the list build wants that, then
+// the caller's order), so that the result is deterministic and independent of
+// the arrival.  Systems of up to kSmallN particles do all of it in one
+// workgroup and one launch.  Grids with many more cells than particles use a
+// stable LSD radix sort of the keys instead, whose cost does not grow with
+// the cells.
 #include <math.h>
 
 #include "device_util.h"
@@ -71,6 +76,16 @@ __device__ __forceinline__ int cell_coord(double x, double L, double inv_side, i
   return q >= (double)nc ? nc - 1 : 0;
 }
 
+// Cell key of a particle; upper (xbit only): the upper half of its cell along
+// x, decided on the quotient that gave the cell index.
+__device__ __forceinline__ int cell_of(double x, double y, double z, const Grid& g, bool xbit,
+                                       bool& upper) {
+  const int cx = cell_coord(x, g.box[0], g.inv_side[0], g.nc[0]);
+  upper = xbit && !(fold(x, g.box[0]) * g.inv_side[0] - (double)cx < 0.5);
+  return cell_key(g, cx, cell_coord(y, g.box[1], g.inv_side[1], g.nc[1]),
+                  cell_coord(z, g.box[2], g.inv_side[2], g.nc[2]));
+}
+
 // The particles of each cell in two runs, the lower half of the cell along x
 // first (each run in sorted order, so the order stays deterministic), and
 // the length of the first run.  The half comes with each sorted value (its
@@ -114,13 +129,8 @@ __global__ void k_cell_keys(const double* __restrict__ x, const double* __restri
   int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (clear && i < 16) clear[i] = 0;
   if (i >= n) return;
-  int cx = cell_coord(x[i], g.box[0], g.inv_side[0], g.nc[0]);
-  // xbit: the top bit of the value marks the upper half of the cell along x
-  // (decided on the quotient that gave the cell index)
-  const bool upper = xbit && !(fold(x[i], g.box[0]) * g.inv_side[0] - (double)cx < 0.5);
-  int cy = cell_coord(y[i], g.box[1], g.inv_side[1], g.nc[1]);
-  int cz = cell_coord(z[i], g.box[2], g.inv_side[2], g.nc[2]);
-  keys[i] = cell_key(g, cx, cy, cz);
+  bool upper;
+  keys[i] = cell_of(x[i], y[i], z[i], g, xbit != 0, upper);
   vals[i] = (int32_t)((uint32_t)i | (upper ? 0x80000000u : 0u));
 }
 
@@ -261,6 +271,58 @@ __global__ __launch_bounds__(1024) void k_scan_sums(int32_t* __restrict__ sums, 
   if (tid == 0) sums[nb] = carry;
 }
 
+// The whole exclusive scan of up to 16 C x 256 values, in place, by one
+// workgroup: each wave holds its consecutive piece in registers, C loads of
+// four values per lane in flight at once.  Against the three launches of the
+// general scan 14 -> 7.6 us at 59,320 cells.
+constexpr int kScanOneMost = 65536;
+template <int C>
+__global__ __launch_bounds__(1024) void k_scan_one(int32_t* __restrict__ a, int n) {
+  __shared__ int wsum[16];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int base = wave * C * 256 + lane * 4;
+  int4 v[C];
+  int total = 0;
+#pragma unroll
+  for (int k = 0; k < C; ++k) {
+    const int i = base + k * 256;
+    if (i + 3 < n) {
+      v[k] = *(const int4*)(a + i);
+    } else {
+      v[k].x = i < n ? a[i] : 0;
+      v[k].y = i + 1 < n ? a[i + 1] : 0;
+      v[k].z = i + 2 < n ? a[i + 2] : 0;
+      v[k].w = 0;
+    }
+  }
+#pragma unroll
+  for (int k = 0; k < C; ++k) total += v[k].x + v[k].y + v[k].z + v[k].w;
+  total = wave_sum_i32(total);
+  if (lane == 0) wsum[wave] = total;
+  __syncthreads();
+  int run = 0;
+  for (int w = 0; w < wave; ++w) run += wsum[w];
+#pragma unroll
+  for (int k = 0; k < C; ++k) {
+    const int t = v[k].x + v[k].y + v[k].z + v[k].w;
+    const int incl = wave_scan_i32(t);
+    int4 o;
+    o.x = run + incl - t;
+    o.y = o.x + v[k].x;
+    o.z = o.y + v[k].y;
+    o.w = o.z + v[k].z;
+    const int i = base + k * 256;
+    if (i + 3 < n) {
+      *(int4*)(a + i) = o;
+    } else {
+      if (i < n) a[i] = o.x;
+      if (i + 1 < n) a[i + 1] = o.y;
+      if (i + 2 < n) a[i + 2] = o.z;
+    }
+    run += __builtin_amdgcn_readlane(incl, 63);
+  }
+}
+
 __global__ __launch_bounds__(256) void k_scan_add(int32_t* __restrict__ out, int64_t n,
                                                   const int32_t* __restrict__ sums,
                                                   int write_total) {
@@ -285,9 +347,10 @@ hipError_t exclusive_scan(const int32_t* in, int32_t* out, int64_t n, int32_t* b
   return hipGetLastError();
 }
 
-hipError_t bin_particles(const double* x, const double* y, const double* z, int64_t n,
-                         const Grid& g, SortBufs& s, int32_t* cell_start, int32_t** keys_out,
-                         int32_t** vals_out, hipStream_t st, int32_t* xlow, int32_t* clear) {
+// The radix path (sparse grids).
+static hipError_t radix_bin(const double* x, const double* y, const double* z, int64_t n,
+                            const Grid& g, SortBufs& s, int32_t* cell_start, int32_t** keys_out,
+                            int32_t** vals_out, hipStream_t st, int32_t* xlow, int32_t* clear) {
   const unsigned nb = (unsigned)div_up(n, 256);
   hipLaunchKernelGGL(k_cell_keys, dim3(nb), dim3(256), 0, st, x, y, z, n, g, s.keys[0], s.vals[0],
                      xlow ? 1 : 0, clear);
@@ -322,60 +385,396 @@ hipError_t bin_particles(const double* x, const double* y, const double* z, int6
   return hipGetLastError();
 }
 
-// ----------------------------------------------------------------- gathers
-__global__ void k_gather_pos(const double* __restrict__ x, const double* __restrict__ y,
-                             const double* __restrict__ z, const int32_t* __restrict__ idx,
-                             int64_t n, double* __restrict__ ox, double* __restrict__ oy,
-                             double* __restrict__ oz, double Lx, double Ly, double Lz, int do_fold) {
-  int64_t s = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (s >= n) return;
-  const int32_t j = idx[s];
-  double a = x[j], b = y[j], c = z[j];
-  if (do_fold) {
-    a = fold(a, Lx);
-    b = fold(b, Ly);
-    c = fold(c, Lz);
+// ------------------------------------------------------- counting sort
+// Squared displacement of particle i since the last list build (a
+// non-finite one counts as 1e300).
+__device__ __forceinline__ double moved2(const MoveCheck& c, int64_t i) {
+  const double a = c.x[i] - c.xb[i], b = c.y[i] - c.yb[i], e = c.z[i] - c.zb[i];
+  const double d = a * a + b * b + e * e;
+  return d < 1e300 ? d : 1e300;
+}
+__device__ __forceinline__ void skin_result(const MoveCheck& c, double m2) {
+  const double d = sqrt(m2);
+  if (d > *c.max_disp) *c.max_disp = d;
+  if (d >= c.half_skin) atomicOr(c.flags, MDPL_FLAG_SKIN);
+}
+
+__global__ __launch_bounds__(256) void k_zero_cells(int32_t* __restrict__ cs, int nkeys,
+                                                    int32_t* __restrict__ xlow,
+                                                    int32_t* __restrict__ clear) {
+  const int i = (int)(blockIdx.x * 256 + threadIdx.x);
+  if (clear && i < 16) clear[i] = 0;
+  if (i > nkeys) return;
+  cs[i] = 0;
+  if (xlow) xlow[i] = 0;
+}
+
+// keys[i] = cell, ranks[i] = arrival rank in the cell (top bit: upper x
+// half).  Runs of equal keys in a wave share one atomic: the particles of a
+// run that continues arrive nearly sorted.
+__global__ __launch_bounds__(256) void k_count_cells(const double* __restrict__ x,
+                                                     const double* __restrict__ y,
+                                                     const double* __restrict__ z, int64_t n,
+                                                     Grid g, int xbit, int32_t* __restrict__ cs,
+                                                     int32_t* __restrict__ keys,
+                                                     uint32_t* __restrict__ ranks, MoveCheck mc) {
+  __shared__ double sh[4];
+  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  const int lane = threadIdx.x & 63;
+  const bool has = i < n;
+  bool upper = false;
+  const int key = has ? cell_of(x[i], y[i], z[i], g, xbit != 0, upper) : -1;
+  const int before = __shfl_up(key, 1, 64);
+  const uint64_t heads = __ballot(lane == 0 || key != before);
+  const uint64_t upto = ~0ull >> (63 - lane);
+  const int head = 63 - __builtin_clzll(heads & upto);
+  const uint64_t after = heads & ~upto;
+  int base = 0;
+  if (has && lane == head)
+    base = atomicAdd(&cs[key], (after ? __builtin_ctzll(after) : 64) - lane);
+  base = __shfl(base, head, 64);
+  if (has) {
+    keys[i] = key;
+    ranks[i] = (uint32_t)(base + lane - head) | (upper ? 0x80000000u : 0u);
   }
-  ox[s] = a;
-  oy[s] = b;
-  oz[s] = c;
+  if (mc.part) {
+    const double m = block_max256(has ? moved2(mc, i) : 0.0, sh);
+    if (threadIdx.x == 0) mc.part[blockIdx.x] = m;
+  }
 }
 
-hipError_t gather_positions(const double* x, const double* y, const double* z, const int32_t* idx,
-                            int64_t n, double* ox, double* oy, double* oz, const double* box,
-                            bool do_fold, hipStream_t st) {
-  hipLaunchKernelGGL(k_gather_pos, dim3((unsigned)div_up(n, 256)), dim3(256), 0, st, x, y, z, idx,
-                     n, ox, oy, oz, box[0], box[1], box[2], do_fold ? 1 : 0);
-  return hipGetLastError();
+// Value (index, top bit: upper x half) and key of every particle to its
+// cell, in order of arrival.
+__global__ __launch_bounds__(256) void k_place_cells(const int32_t* __restrict__ cs,
+                                                     const int32_t* __restrict__ keys,
+                                                     const uint32_t* __restrict__ ranks, int64_t n,
+                                                     uint32_t* __restrict__ tv,
+                                                     int32_t* __restrict__ tk) {
+  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (i >= n) return;
+  const int key = keys[i];
+  const uint32_t r = ranks[i];
+  const int32_t s = cs[key] + (int32_t)(r & 0x7fffffffu);
+  tv[s] = (uint32_t)i | (r & 0x80000000u);
+  tk[s] = key;
 }
 
-__global__ void k_gather_analysis(const double* __restrict__ x, const double* __restrict__ y,
-                                  const double* __restrict__ z, const int32_t* __restrict__ idx,
-                                  int64_t n, double Lx, double Ly, double Lz,
-                                  double* __restrict__ ox, double* __restrict__ oy,
-                                  double* __restrict__ oz, float* __restrict__ px,
-                                  float* __restrict__ py, float* __restrict__ pz,
-                                  int32_t* __restrict__ outside) {
-  const int64_t s = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+// Number of values below v among p[b .. e), and of those in the upper half.
+template <typename P>
+__device__ __forceinline__ int place_in_cell(const P* p, int b, int e, uint32_t v, int& upper) {
+  int r = 0, up = 0;
+#pragma unroll 4
+  for (int t = b; t < e; ++t) {
+    const uint32_t w = p[t];
+    r += w < v ? 1 : 0;
+    up += (int)(w >> 31);
+  }
+  upper = up;
+  return r;
+}
+
+// Final places, keys, values and the move of every particle.  A cell of more
+// than kOrderMost particles (far beyond any tile) keeps its order of arrival,
+// which bounds the work; xlow 0 makes the list build scan whole rows for it.
+constexpr int kOrderMost = 4096;
+template <typename Move>
+__global__ __launch_bounds__(256) void k_order_cells(const int32_t* __restrict__ cs,
+                                                     const uint32_t* __restrict__ tv,
+                                                     const int32_t* __restrict__ tk, int64_t n,
+                                                     int32_t* __restrict__ xlow,
+                                                     int32_t* __restrict__ keys_out, Move move,
+                                                     MoveCheck mc, int nparts) {
+  __shared__ double sh[4];
+  if (mc.part && blockIdx.x == 0) {
+    double v = 0.0;
+    for (int k = threadIdx.x; k < nparts; k += 256) v = mc.part[k] > v ? mc.part[k] : v;
+    v = block_max256(v, sh);
+    if (threadIdx.x == 0) skin_result(mc, v);
+  }
+  const int64_t s = (int64_t)blockIdx.x * 256 + threadIdx.x;
   if (s >= n) return;
-  const int32_t j = idx[s];
-  const double a = x[j], b = y[j], c = z[j];
-  ox[s] = a;
-  oy[s] = b;
-  oz[s] = c;
-  const double fa = fold(a, Lx), fb = fold(b, Ly), fc = fold(c, Lz);
-  px[s] = (float)fa;
-  py[s] = (float)fb;
-  pz[s] = (float)fc;
-  if (fa != a || fb != b || fc != c) *outside = 1;
+  const uint32_t v = tv[s];
+  const int key = tk[s];
+  const int b = cs[key], e = cs[key + 1];
+  int r = (int)s - b, upper = e - b;
+  if (e - b <= kOrderMost) r = place_in_cell(tv, b, e, v, upper);
+  if (xlow && r == 0) xlow[key] = e - b - upper;
+  if (keys_out) keys_out[b + r] = key;
+  move((int64_t)b + r, (int32_t)(v & 0x7fffffffu));
 }
 
-hipError_t gather_analysis(const double* x, const double* y, const double* z, const int32_t* idx,
-                           int64_t n, const double* box, double* ox, double* oy, double* oz,
-                           float* px, float* py, float* pz, int32_t* outside, hipStream_t st) {
-  hipLaunchKernelGGL(k_gather_analysis, dim3((unsigned)div_up(n, 256)), dim3(256), 0, st, x, y, z,
-                     idx, n, box[0], box[1], box[2], ox, oy, oz, px, py, pz, outside);
+// The whole sort in one workgroup, and the move too unless vals_out is given
+// (a few thousand particles' ten arrays are more than one CU moves in the
+// time of another launch): at these sizes every launch of the general path
+// takes its minimum of some 3 us.  N = 1000 45 -> 12 us, N = 4096 48 -> 20 us a
+// rebuild (13 launches before).
+constexpr int kSmallN = 8192, kSmallKeys = 8192, kSmallThreads = 1024, kSmallMove = 2048;
+template <typename Move>
+__global__ __launch_bounds__(kSmallThreads) void k_sort_small(
+    const double* __restrict__ x, const double* __restrict__ y, const double* __restrict__ z,
+    int n, Grid g, int32_t* __restrict__ cs, int32_t* __restrict__ xlow,
+    int32_t* __restrict__ keys_out, int32_t* __restrict__ vals_out, int32_t* __restrict__ clear,
+    Move move, MoveCheck mc) {
+  constexpr int kItems = kSmallN / kSmallThreads, kKeys = kSmallKeys / kSmallThreads;
+  __shared__ int cnt[kSmallKeys + 1];
+  __shared__ uint32_t tv[kSmallN];
+  __shared__ int wsum[kSmallThreads / 64];
+  __shared__ double sh[kSmallThreads / 64];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  if (clear && tid < 16) clear[tid] = 0;
+  for (int c = tid; c <= kSmallKeys; c += kSmallThreads) cnt[c] = 0;
+  __syncthreads();
+  int key[kItems];
+  uint32_t rank[kItems];
+  double m2 = 0.0;
+#pragma unroll
+  for (int k = 0; k < kItems; ++k) {
+    const int i = tid + k * kSmallThreads;
+    if (i >= n) continue;
+    bool upper;
+    key[k] = cell_of(x[i], y[i], z[i], g, xlow != nullptr, upper);
+    rank[k] = (uint32_t)atomicAdd(&cnt[key[k]], 1) | (upper ? 0x80000000u : 0u);
+    if (mc.part) {
+      const double d = moved2(mc, i);
+      m2 = d > m2 ? d : m2;
+    }
+  }
+  if (mc.part) {
+    m2 = wave_max_nonneg(m2);
+    if (lane == 0) sh[wave] = m2;
+  }
+  __syncthreads();
+  if (mc.part && tid == 0) {
+    for (int w = 1; w < kSmallThreads / 64; ++w) m2 = sh[w] > m2 ? sh[w] : m2;
+    skin_result(mc, m2);
+  }
+  // exclusive scan of the counts, kKeys consecutive ones per thread
+  int c[kKeys], sum = 0;
+#pragma unroll
+  for (int k = 0; k < kKeys; ++k) {
+    c[k] = cnt[tid * kKeys + k];
+    sum += c[k];
+  }
+  int incl = sum;
+#pragma unroll
+  for (int off = 1; off < 64; off <<= 1) {
+    const int o = __shfl_up(incl, off, 64);
+    if (lane >= off) incl += o;
+  }
+  if (lane == 63) wsum[wave] = incl;
+  __syncthreads();
+  int run = incl - sum;
+  for (int w = 0; w < wave; ++w) run += wsum[w];
+#pragma unroll
+  for (int k = 0; k < kKeys; ++k) {
+    const int cell = tid * kKeys + k;
+    cnt[cell] = run;
+    if (cell <= g.nkeys) cs[cell] = run;
+    if (xlow && cell < g.nkeys && c[k] == 0) xlow[cell] = 0;
+    run += c[k];
+  }
+  if (tid == kSmallThreads - 1) {
+    cnt[kSmallKeys] = run;
+    if (g.nkeys == kSmallKeys) cs[kSmallKeys] = run;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < kItems; ++k) {
+    const int i = tid + k * kSmallThreads;
+    if (i < n) tv[cnt[key[k]] + (int)(rank[k] & 0x7fffffffu)] = (uint32_t)i | (rank[k] & 0x80000000u);
+  }
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < kItems; ++k) {
+    const int i = tid + k * kSmallThreads;
+    if (i >= n) continue;
+    const int b = cnt[key[k]], e = cnt[key[k] + 1];
+    int r = (int)(rank[k] & 0x7fffffffu), upper = e - b;
+    if (e - b <= kOrderMost)
+      r = place_in_cell(tv, b, e, (uint32_t)i | (rank[k] & 0x80000000u), upper);
+    if (xlow && r == 0) xlow[key[k]] = e - b - upper;
+    if (keys_out) keys_out[b + r] = key[k];
+    if (vals_out) vals_out[b + r] = i;
+    else move((int64_t)b + r, i);
+  }
+}
+
+template <typename Move>
+__global__ __launch_bounds__(256) void k_move(const int32_t* idx, int64_t n,
+                                              Move move) {
+  const int64_t s = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (s < n) move(s, idx[s]);
+}
+
+// The displacement check alone (the radix path and the end of a run).
+__global__ __launch_bounds__(256) void k_moved_max(int64_t n, MoveCheck mc) {
+  __shared__ double sh[4];
+  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  const double m = block_max256(i < n ? moved2(mc, i) : 0.0, sh);
+  if (threadIdx.x == 0) mc.part[blockIdx.x] = m;
+}
+__global__ __launch_bounds__(256) void k_skin_check(MoveCheck mc, int nparts) {
+  __shared__ double sh[4];
+  double v = 0.0;
+  for (int k = threadIdx.x; k < nparts; k += 256) v = mc.part[k] > v ? mc.part[k] : v;
+  v = block_max256(v, sh);
+  if (threadIdx.x == 0) skin_result(mc, v);
+}
+
+hipError_t skin_check(const MoveCheck& mc, int64_t n, hipStream_t st) {
+  const unsigned nb = (unsigned)div_up(n, 256);
+  hipLaunchKernelGGL(k_moved_max, dim3(nb), dim3(256), 0, st, n, mc);
+  hipLaunchKernelGGL(k_skin_check, dim3(1), dim3(256), 0, st, mc, (int)nb);
   return hipGetLastError();
+}
+
+// Sorts the particles by cell and moves them: cell_start, xlow and clear as
+// declared for sort_*; *keys_out (nullable): the sorted keys, in the sort
+// buffers.
+template <typename Move>
+static hipError_t sort_and_move(const double* x, const double* y, const double* z, int64_t n,
+                                const Grid& g, SortBufs& s, int32_t* cs, int32_t* xlow,
+                                int32_t* clear, int32_t** keys_out, const Move& move,
+                                const MoveCheck& mc, hipStream_t st) {
+  const unsigned nb = (unsigned)div_up(n, 256);
+  if (n <= kSmallN && g.nkeys <= kSmallKeys) {
+    int32_t* keys = keys_out ? s.keys[0] : nullptr;
+    int32_t* vals = n > kSmallMove ? s.vals[1] : nullptr;
+    hipLaunchKernelGGL(k_sort_small<Move>, dim3(1), dim3(kSmallThreads), 0, st, x, y, z, (int)n, g,
+                       cs, xlow, keys, vals, clear, move, mc);
+    if (vals) hipLaunchKernelGGL(k_move<Move>, dim3(nb), dim3(256), 0, st, vals, n, move);
+    if (keys_out) *keys_out = keys;
+    return hipGetLastError();
+  }
+  // up to 8 cells per particle the scan over the cells is cheap (and its
+  // block sums fit the radix path's histogram area)
+  if ((int64_t)g.nkeys <= 8 * n) {
+    uint32_t *ranks = (uint32_t*)s.vals[0], *tv = (uint32_t*)s.vals[1];
+    int32_t* keys = keys_out ? s.keys[0] : nullptr;  // the unsorted keys are done with by then
+    const int64_t nk1 = (int64_t)g.nkeys + 1;
+    hipLaunchKernelGGL(k_zero_cells, dim3((unsigned)div_up(nk1, 256)), dim3(256), 0, st, cs,
+                       g.nkeys, xlow, clear);
+    hipLaunchKernelGGL(k_count_cells, dim3(nb), dim3(256), 0, st, x, y, z, n, g, xlow ? 1 : 0, cs,
+                       s.keys[0], ranks, mc);
+    if (nk1 <= kScanOneMost) {
+      // (cs is 256-byte aligned: a piece of the workspace)
+      if (nk1 <= kScanOneMost / 4)
+        hipLaunchKernelGGL(k_scan_one<4>, dim3(1), dim3(1024), 0, st, cs, (int)nk1);
+      else
+        hipLaunchKernelGGL(k_scan_one<16>, dim3(1), dim3(1024), 0, st, cs, (int)nk1);
+    } else {
+      const hipError_t e = exclusive_scan(cs, cs, nk1, s.hist, false, st);
+      if (e != hipSuccess) return e;
+    }
+    hipLaunchKernelGGL(k_place_cells, dim3(nb), dim3(256), 0, st, cs, s.keys[0], ranks, n, tv,
+                       s.keys[1]);
+    hipLaunchKernelGGL(k_order_cells<Move>, dim3(nb), dim3(256), 0, st, cs, tv, s.keys[1], n, xlow,
+                       keys, move, mc, (int)nb);
+    if (keys_out) *keys_out = keys;
+    return hipGetLastError();
+  }
+  int32_t *keys, *vals;
+  if (mc.part) {
+    const hipError_t e = skin_check(mc, n, st);
+    if (e != hipSuccess) return e;
+  }
+  const hipError_t e = radix_bin(x, y, z, n, g, s, cs, &keys, &vals, st, xlow, clear);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(k_move<Move>, dim3(nb), dim3(256), 0, st, vals, n, move);
+  if (keys_out) *keys_out = keys;
+  return hipGetLastError();
+}
+
+// ------------------------------------------------------- moves and gathers
+// The build's move: folded positions and the caller's index of each slot.
+struct MoveBuild {
+  const double *x, *y, *z;
+  double *ox, *oy, *oz;
+  int32_t* perm;
+  double L[3];
+  __device__ __forceinline__ void operator()(int64_t s, int32_t j) const {
+    perm[s] = j;
+    ox[s] = fold(x[j], L[0]);
+    oy[s] = fold(y[j], L[1]);
+    oz[s] = fold(z[j], L[2]);
+  }
+};
+
+hipError_t sort_build(const double* x, const double* y, const double* z, int64_t n, const Grid& g,
+                      SortBufs& s, int32_t* cell_start, int32_t* xlow, int32_t** skeys,
+                      int32_t* perm, double* ox, double* oy, double* oz, hipStream_t st) {
+  const MoveBuild m{x, y, z, ox, oy, oz, perm, {g.box[0], g.box[1], g.box[2]}};
+  return sort_and_move(x, y, z, n, g, s, cell_start, xlow, nullptr, skeys, m, MoveCheck{}, st);
+}
+
+// The analyses' move.
+struct MoveAnalysis {
+  const double *x, *y, *z;
+  double *ox, *oy, *oz;
+  float *px, *py, *pz;
+  int32_t *perm, *outside;
+  double L[3];
+  __device__ __forceinline__ void operator()(int64_t s, int32_t j) const {
+    const double a = x[j], b = y[j], c = z[j];
+    const double fa = fold(a, L[0]), fb = fold(b, L[1]), fc = fold(c, L[2]);
+    perm[s] = j;
+    ox[s] = a;
+    oy[s] = b;
+    oz[s] = c;
+    px[s] = (float)fa;
+    py[s] = (float)fb;
+    pz[s] = (float)fc;
+    if (fa != a || fb != b || fc != c) *outside = 1;
+  }
+};
+
+hipError_t sort_analysis(const double* x, const double* y, const double* z, int64_t n,
+                         const Grid& g, SortBufs& s, int32_t* cell_start, int32_t** skeys,
+                         int32_t** perm, double* ox, double* oy, double* oz, float* px, float* py,
+                         float* pz, int32_t* small, hipStream_t st) {
+  // the values' second buffer: free again when the move writes it (the radix
+  // path may have sorted the values into it: each slot reads its own first)
+  *perm = s.vals[0];
+  const MoveAnalysis m{x, y, z, ox, oy, oz, px, py, pz, *perm, small, {g.box[0], g.box[1], g.box[2]}};
+  return sort_and_move(x, y, z, n, g, s, cell_start, nullptr, small, skeys, m, MoveCheck{}, st);
+}
+
+// A run's move: all ten arrays, positions folded; xb/yb/zb receive a copy of
+// them, *bound becomes zero (a new list: nothing has moved since).
+template <typename FT>
+struct MoveState {
+  StateArrays src, dst;
+  double *xb, *yb, *zb, *bound;
+  double L[3];
+  __device__ __forceinline__ void operator()(int64_t s, int32_t j) const {
+    if (s == 0) *bound = 0.0;
+    const double a = fold(src.x[j], L[0]), b = fold(src.y[j], L[1]), c = fold(src.z[j], L[2]);
+    dst.x[s] = a;
+    dst.y[s] = b;
+    dst.z[s] = c;
+    xb[s] = a;
+    yb[s] = b;
+    zb[s] = c;
+    dst.vx[s] = src.vx[j];
+    dst.vy[s] = src.vy[j];
+    dst.vz[s] = src.vz[j];
+    ((FT*)dst.fx)[s] = ((const FT*)src.fx)[j];
+    ((FT*)dst.fy)[s] = ((const FT*)src.fy)[j];
+    ((FT*)dst.fz)[s] = ((const FT*)src.fz)[j];
+    dst.ids[s] = src.ids[j];
+  }
+};
+
+hipError_t sort_state(const StateArrays& src, const StateArrays& dst, int64_t n, int fbytes,
+                      const Grid& g, SortBufs& s, int32_t* cell_start, int32_t* xlow, double* xb,
+                      double* yb, double* zb, double* bound, const MoveCheck& mc,
+                      hipStream_t st) {
+  if (fbytes == 4) {
+    const MoveState<float> m{src, dst, xb, yb, zb, bound, {g.box[0], g.box[1], g.box[2]}};
+    return sort_and_move(src.x, src.y, src.z, n, g, s, cell_start, xlow, nullptr, nullptr, m, mc, st);
+  }
+  const MoveState<double> m{src, dst, xb, yb, zb, bound, {g.box[0], g.box[1], g.box[2]}};
+  return sort_and_move(src.x, src.y, src.z, n, g, s, cell_start, xlow, nullptr, nullptr, m, mc, st);
 }
 
 // Positions of the last build's slots, each moved to the periodic image
@@ -414,45 +813,6 @@ hipError_t gather_canonical(const double* x, const double* y, const double* z, c
                             double* oz, hipStream_t st) {
   hipLaunchKernelGGL(k_gather_canonical, dim3((unsigned)div_up(n, 256)), dim3(256), 0, st, x, y, z,
                      idx, skeys, n, g, ox, oy, oz);
-  return hipGetLastError();
-}
-
-template <typename FT>
-__global__ void k_reorder(StateArrays src, const int32_t* __restrict__ idx, int64_t n, double Lx,
-                          double Ly, double Lz, StateArrays dst, double* xb, double* yb,
-                          double* zb, double* bound) {
-  int64_t s = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (bound && s == 0) *bound = 0.0;
-  if (s >= n) return;
-  const int32_t j = idx[s];
-  const double a = fold(src.x[j], Lx), b = fold(src.y[j], Ly), c = fold(src.z[j], Lz);
-  dst.x[s] = a;
-  dst.y[s] = b;
-  dst.z[s] = c;
-  if (xb) {
-    xb[s] = a;
-    yb[s] = b;
-    zb[s] = c;
-  }
-  dst.vx[s] = src.vx[j];
-  dst.vy[s] = src.vy[j];
-  dst.vz[s] = src.vz[j];
-  ((FT*)dst.fx)[s] = ((const FT*)src.fx)[j];
-  ((FT*)dst.fy)[s] = ((const FT*)src.fy)[j];
-  ((FT*)dst.fz)[s] = ((const FT*)src.fz)[j];
-  dst.ids[s] = src.ids[j];
-}
-
-hipError_t reorder_state(const StateArrays& src, const int32_t* idx, int64_t n, int fbytes,
-                         const double* box, StateArrays& dst, double* xb, double* yb, double* zb,
-                         double* bound, hipStream_t st) {
-  const unsigned nb = (unsigned)div_up(n, 256);
-  if (fbytes == 4)
-    hipLaunchKernelGGL(k_reorder<float>, dim3(nb), dim3(256), 0, st, src, idx, n, box[0], box[1],
-                       box[2], dst, xb, yb, zb, bound);
-  else
-    hipLaunchKernelGGL(k_reorder<double>, dim3(nb), dim3(256), 0, st, src, idx, n, box[0], box[1],
-                       box[2], dst, xb, yb, zb, bound);
   return hipGetLastError();
 }
 

@@ -27,9 +27,12 @@ __device__ __forceinline__ double fix_value(unsigned long long a) {
 }
 
 // Fold a coordinate into [0, L): x - L floor(x / L), each operation rounded
-// (no contraction), then one correction step against rounding to L.
+// (no contraction), then one correction step against rounding to L.  A
+// coordinate already there is its own fold (the corrections undo a quotient
+// that rounds to 1), so that the division is only made for the others.
 __device__ __forceinline__ double fold(double x, double L) {
 #pragma clang fp contract(off)
+  if (x >= 0.0 && x < L) return x + 0.0;  // +0 for -0, as below
   double w = x - L * floor(x / L);
   if (w >= L) w -= L;
   if (w < 0.0) w += L;
@@ -141,6 +144,28 @@ __device__ __forceinline__ T wave_sum(T v) {
   v += dpp_move<0x142, 0xa>(v);  // row_bcast:15 into rows 1 and 3
   v += dpp_move<0x143, 0xc>(v);  // row_bcast:31 into rows 2 and 3
   return readlane63(v);
+}
+
+__device__ __forceinline__ int wave_sum_i32(int v) {
+  v += dpp_i32<0xB1>(v);
+  v += dpp_i32<0x4E>(v);
+  v += dpp_i32<0x124>(v);
+  v += dpp_i32<0x128>(v);
+  v += dpp_i32<0x142, 0xa>(v);
+  v += dpp_i32<0x143, 0xc>(v);
+  return __builtin_amdgcn_readlane(v, 63);
+}
+
+// Inclusive prefix sum over the 64 lanes of a wave (all active): shifts
+// within each row of 16 lanes, then the rows below by the row broadcasts.
+__device__ __forceinline__ int wave_scan_i32(int v) {
+  v += dpp_i32<0x111>(v);
+  v += dpp_i32<0x112>(v);
+  v += dpp_i32<0x114>(v);
+  v += dpp_i32<0x118>(v);
+  v += dpp_i32<0x142, 0xa>(v);
+  v += dpp_i32<0x143, 0xc>(v);
+  return v;
 }
 
 // Sum over a 256-thread block; the result is valid in thread 0.  Fixed

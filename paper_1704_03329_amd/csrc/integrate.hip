@@ -1,7 +1,6 @@
 // Particle loops of the time integration: velocity Verlet (Alg.
 // VelocityVerlet), the Andersen thermostat of the crystallisation run
-// (Sec. 5.2), fixed-order reductions of per-block partials, and the skin
-// check of the list reuse (Sec. 3.5).
+// (Sec. 5.2), and fixed-order reductions of per-block partials.
 #include "device_util.h"
 #include "internal.h"
 
@@ -189,60 +188,6 @@ hipError_t reduce_row(const double* partials, int nblocks, int stride, int ncomp
                       hipStream_t st) {
   if (ncomp < 0 || ncomp > 3) return hipErrorInvalidValue;
   hipLaunchKernelGGL(k_reduce_row, dim3(1), dim3(256), 0, st, partials, nblocks, stride, ncomp, o);
-  return hipGetLastError();
-}
-
-}  // namespace mdpl
-
-namespace mdpl {
-
-// ------------------------------------------------------------ skin check
-// Largest squared displacement since the last list build, per block.
-__global__ __launch_bounds__(256) void k_disp_partials(
-    const double* __restrict__ x, const double* __restrict__ y, const double* __restrict__ z,
-    const double* __restrict__ xb, const double* __restrict__ yb, const double* __restrict__ zb,
-    int64_t n, double* __restrict__ part) {
-  __shared__ double sh[4];
-  const int64_t s = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  double d = 0.0;
-  if (s < n) {
-    const double a = x[s] - xb[s], b = y[s] - yb[s], c = z[s] - zb[s];
-    d = a * a + b * b + c * c;
-    if (!(d < 1e300)) d = 1e300;
-  }
-  const double m = block_max256(d, sh);
-  if (threadIdx.x == 0) part[blockIdx.x] = m;
-}
-
-hipError_t disp_partials(const double* x, const double* y, const double* z, const double* xb,
-                         const double* yb, const double* zb, int64_t n, double* partials,
-                         hipStream_t st, int* nblocks_out) {
-  const unsigned nb = (unsigned)div_up(n, 256);
-  *nblocks_out = (int)nb;
-  hipLaunchKernelGGL(k_disp_partials, dim3(nb), dim3(256), 0, st, x, y, z, xb, yb, zb, n, partials);
-  return hipGetLastError();
-}
-
-// max over the partials -> displacement; record the largest; flag when it
-// reaches half the skin (a pair inside rc could then be missing from the list).
-__global__ __launch_bounds__(256) void k_skin_check(const double* __restrict__ part, int nb,
-                                                    double half_skin, double* max_disp,
-                                                    uint32_t* flags) {
-  __shared__ double sh[4];
-  double v = 0.0;
-  for (int k = threadIdx.x; k < nb; k += 256) v = part[k] > v ? part[k] : v;
-  const double m2 = block_max256(v, sh);
-  if (threadIdx.x == 0) {
-    const double d = sqrt(m2);
-    if (d > *max_disp) *max_disp = d;
-    if (d >= half_skin) atomicOr(flags, MDPL_FLAG_SKIN);
-  }
-}
-
-hipError_t skin_check(const double* partials, int nblocks, double half_skin, double* max_disp,
-                      uint32_t* flags, hipStream_t st) {
-  hipLaunchKernelGGL(k_skin_check, dim3(1), dim3(256), 0, st, partials, nblocks, half_skin,
-                     max_disp, flags);
   return hipGetLastError();
 }
 

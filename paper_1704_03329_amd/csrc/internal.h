@@ -64,34 +64,14 @@ struct SortBufs {
 size_t sort_bytes(int64_t n);
 void sort_carve(char*& p, int64_t n, SortBufs* s);
 
-// Sort particles by cell: keys computed from (folded) positions, values =
-// particle index.  On return keys_out/vals_out point at the sorted arrays
-// (one of the two ping-pong buffers) and cell_start[0..ncells] is filled.
-// clear (nullable): 16 words set to zero on the way.
-hipError_t bin_particles(const double* x, const double* y, const double* z, int64_t n,
-                         const Grid& g, SortBufs& s, int32_t* cell_start, int32_t** keys_out,
-                         int32_t** vals_out, hipStream_t st, int32_t* xlow = nullptr,
-                         int32_t* clear = nullptr);
-
 // Exclusive prefix sum of n int32 values into out (may alias in).  Uses
 // blocksums scratch of at least div_up(n, 1024) + 1 entries.  Also writes
 // the total to out[n] if write_total.
 hipError_t exclusive_scan(const int32_t* in, int32_t* out, int64_t n, int32_t* blocksums,
                           bool write_total, hipStream_t st);
 
-// Gathers: dst[k] = src[idx[k]] for double / float / int arrays.
-hipError_t gather_positions(const double* x, const double* y, const double* z, const int32_t* idx,
-                            int64_t n, double* ox, double* oy, double* oz, const double* box,
-                            bool fold, hipStream_t st);
-
-// The analyses' gather: positions as stored, and FP32 copies folded into the
-// box; *outside becomes 1 if folding moved any of them (zero beforehand).
-hipError_t gather_analysis(const double* x, const double* y, const double* z, const int32_t* idx,
-                           int64_t n, const double* box, double* ox, double* oy, double* oz,
-                           float* px, float* py, float* pz, int32_t* outside, hipStream_t st);
-
-// Like gather_positions, but each position is moved to the periodic image
-// nearest the centre of its cell in the sorted keys skeys.
+// Positions of the sorted slots (idx: caller indices), each moved to the periodic
+// image nearest the centre of its cell in the sorted keys skeys.
 hipError_t gather_canonical(const double* x, const double* y, const double* z, const int32_t* idx,
                             const int32_t* skeys, int64_t n, const Grid& g, double* ox, double* oy,
                             double* oz, hipStream_t st);
@@ -101,12 +81,40 @@ struct StateArrays {
   void *fx, *fy, *fz;
   int32_t* ids;
 };
-// dst[s] = src[idx[s]] for all ten arrays, positions folded into the box;
-// xb/yb/zb (nullable) receive a copy of the folded positions; bound
-// (nullable) is set to zero (a new list: nothing has moved since).
-hipError_t reorder_state(const StateArrays& src, const int32_t* idx, int64_t n, int fbytes,
-                         const double* box, StateArrays& dst, double* xb, double* yb, double* zb,
-                         double* bound, hipStream_t st);
+// The displacement check of the list reuse (Sec. 3.5): x, y, z the positions
+// of the last force pass with the old list, xb, yb, zb those of its build.
+// *max_disp is raised to the largest displacement; MDPL_FLAG_SKIN if that
+// reaches half_skin (a pair inside rc could then be missing).  part null: none.
+struct MoveCheck {
+  const double *x, *y, *z, *xb, *yb, *zb;
+  double* part;  // per 256 particles
+  double half_skin;
+  double* max_disp;
+  uint32_t* flags;
+};
+hipError_t skin_check(const MoveCheck& mc, int64_t n, hipStream_t st);
+
+// The sorts by cell, each with the move of the particles into the sorted
+// order.  cell_start[0 .. nkeys] is filled; with xlow each cell's particles
+// of its lower half along x come first and xlow[cell] is their number; inside
+// that the caller's order is kept.
+// Build: folded positions to ox, oy, oz, caller indices to perm, sorted keys
+// in the sort buffers (*skeys).
+hipError_t sort_build(const double* x, const double* y, const double* z, int64_t n, const Grid& g,
+                      SortBufs& s, int32_t* cell_start, int32_t* xlow, int32_t** skeys,
+                      int32_t* perm, double* ox, double* oy, double* oz, hipStream_t st);
+// Analyses: positions as stored, FP32 copies folded into the box, keys and
+// caller indices in the sort buffers; small (16 words) is cleared, word 0
+// then set if folding moved any position.
+hipError_t sort_analysis(const double* x, const double* y, const double* z, int64_t n,
+                         const Grid& g, SortBufs& s, int32_t* cell_start, int32_t** skeys,
+                         int32_t** perm, double* ox, double* oy, double* oz, float* px, float* py,
+                         float* pz, int32_t* small, hipStream_t st);
+// Runs: all ten arrays, positions folded and copied to xb, yb, zb; *bound
+// becomes zero; mc: the displacement check, made before xb changes.
+hipError_t sort_state(const StateArrays& src, const StateArrays& dst, int64_t n, int fbytes,
+                      const Grid& g, SortBufs& s, int32_t* cell_start, int32_t* xlow, double* xb,
+                      double* yb, double* zb, double* bound, const MoveCheck& mc, hipStream_t st);
 
 // dst[a] = src[a] for each of the ten arrays whose pointers differ (one launch).
 hipError_t copy_state(const StateArrays& src, const StateArrays& dst, int64_t n, int fbytes,
@@ -164,8 +172,7 @@ inline int brick_parts(const Grid& g, int want, int most) {
   return p < 1 ? 1 : p;
 }
 hipError_t build_tile_nlist(const double* x, const double* y, const double* z,
-                            const int32_t* skeys, const int32_t* cell_start, const Grid& g,
-                            double r2, TileList tl, uint32_t* flags, int32_t* maxcount,
+                            const int32_t* cell_start, const Grid& g, double r2, TileList tl, uint32_t* flags, int32_t* maxcount,
                             hipStream_t st);
 hipError_t export_tile_pairs(const TileList& tl, const int32_t* cell_start, const Grid& g,
                              const int32_t* perm, const int32_t* offsets, int32_t* i_out,
@@ -211,10 +218,16 @@ __device__ inline void kick_store(const KickTrack& kt, double m2) {
   if (!kt.ring) return;
   kt.part[kt.cur][blockIdx.y * gridDim.x + blockIdx.x] = m2 >= 0.0 ? m2 : __builtin_huge_val();
 }
-// Every thread of workgroup 0 of a drifting launch, before its other work
-// (no-op elsewhere): the pending record.  sh: one double per wave.
+// Every thread of one workgroup of a drifting launch, before its other work
+// (no-op elsewhere): the pending record.  sh: one double per wave.  Full-size
+// launches give it to workgroup 0, which starts first; where several parts
+// share a brick all workgroups start together, and the last one, of a thin
+// brick's last part, has the least else to do (the write to the host takes
+// a microsecond or two: N = 1000 15.9 -> 15.4 us a step).
 __device__ inline void kick_publish(const KickTrack& kt, double* sh) {
-  if (!kt.ring || kt.pub_n <= 0 || (blockIdx.x | blockIdx.y) != 0) return;
+  const bool mine = gridDim.y > 1 ? blockIdx.x == gridDim.x - 1 && blockIdx.y == gridDim.y - 1
+                                  : blockIdx.x == 0;
+  if (!kt.ring || kt.pub_n <= 0 || !mine) return;
   const double* p = kt.part[kt.cur ^ 1];
   double m = 0.0;
   for (int i = threadIdx.x; i < kt.pub_n; i += blockDim.x) m = p[i] > m ? p[i] : m;
@@ -227,11 +240,13 @@ __device__ inline void kick_publish(const KickTrack& kt, double* sh) {
     const double vmax = sqrt(m);
     const double b = *kt.bound + kt.dt * vmax;
     *kt.bound = b;
+    // the fields go straight to host memory (system scope), the stamp after
+    // they have arrived: a release fence would also write back the whole L2
     KickRecord* r = kt.ring + (kt.pub_step & (kRing - 1));
-    r->bound = b;
-    r->vmax = vmax;
-    __threadfence_system();
-    __hip_atomic_store(&r->stamp, kt.pub_step, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+    __hip_atomic_store(&r->bound, b, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    __hip_atomic_store(&r->vmax, vmax, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __hip_atomic_store(&r->stamp, kt.pub_step, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
   }
   __syncthreads();
 }
@@ -310,15 +325,6 @@ struct RowOut {
 // copy/zero of RowOut in one launch.
 hipError_t reduce_row(const double* partials, int nblocks, int stride, int ncomp, const RowOut& o,
                       hipStream_t st);
-
-// Per-block maxima of |r - r_build|^2 into partials.
-hipError_t disp_partials(const double* x, const double* y, const double* z, const double* xb,
-                         const double* yb, const double* zb, int64_t n, double* partials,
-                         hipStream_t st, int* nblocks_out);
-
-// d = sqrt(max partials); *max_disp = max(*max_disp, d); flags |= SKIN if d >= half_skin.
-hipError_t skin_check(const double* partials, int nblocks, double half_skin, double* max_disp,
-                      uint32_t* flags, hipStream_t st);
 
 // What the structure analyses read: particles sorted by cell (a grid with
 // B = (1,1,1)): stored FP64 positions, FP32 copies folded into the box, the

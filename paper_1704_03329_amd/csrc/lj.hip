@@ -133,7 +133,7 @@ __device__ __forceinline__ V group_sum(V v, int T) {
 // LPP: lanes per particle, each taking every LPP-th list word.  blockIdx.y:
 // the workgroup's part of the brick's particles (brick_parts).
 template <typename MT, typename OT, bool ENERGY, int LPP>
-__global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8)))
+__global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(LPP == 8 ? 4 : 8)))
 void k_lj_force(const double* __restrict__ x, const double* __restrict__ y,
                 const double* __restrict__ z, const int32_t* __restrict__ cs, Grid g, TileList tl,
                 LJConst c, ForceOut out) {
@@ -149,21 +149,35 @@ void k_lj_force(const double* __restrict__ x, const double* __restrict__ y,
     if (out.fuse && threadIdx.x == 0) kick_store(out.track, 0.0);
     return;
   }
+  const int s0 = cs[brick * g.V], s1 = cs[(brick + 1) * g.V];
+  const int part = (int)threadIdx.x % LPP;
+  const int step = (int)blockDim.x / LPP;
+  // LPP = 8 (few bricks, one particle per lane group): the lane's list words
+  // (three hold the fluid's 76 entries) and count are loaded before the tile,
+  // so that their latency overlaps the tile's; a longer list's later words
+  // follow in the loop
+  constexpr int kHeld = LPP == 8 ? 3 : 1;
+  const int sf = s0 + (int)blockIdx.y * step + (int)threadIdx.x / LPP;
+  int cnt0 = 0;
+  uint64_t held[kHeld] = {0};
+  if (LPP == 8 && sf < s1) {
+    cnt0 = tl.cnt[sf];
+#pragma unroll
+    for (int k = 0; k < kHeld; ++k)
+      if (4 * (part + k * LPP) < tl.max_nb)
+        held[k] = tl.nbr[sf + (int64_t)(part + k * LPP) * tl.stride];
+  }
   // the tile tables as the list build left them
   const int total = tile_tables_load(g, tl.tab + (int64_t)brick * kTabInts, t);
   if constexpr (ENERGY) tile_load<true>(g, x, y, z, total, t);
   else tile_load_xy(g, x, y, z, total, t);
-  const int s0 = cs[brick * g.V], s1 = cs[(brick + 1) * g.V];
   // plain pass: f_ij / dr_ij = x^4 (A x^3 - B) with x = 1 / d2, A = 48 eps s^12, B = 24 eps s^6
   const double sig6 = c.sigma2 * c.sigma2 * c.sigma2;
   const MT fa = (MT)(48.0 * c.eps * sig6 * sig6), fb = (MT)(24.0 * c.eps * sig6);
   double scale = out.scale;
   if (out.scale_dev) scale *= *out.scale_dev;
   double e = 0.0, w = 0.0, ke = 0.0, vmax2 = 0.0;
-  const int part = (int)threadIdx.x % LPP;
-  const int step = (int)blockDim.x / LPP;
-  for (int s = s0 + (int)blockIdx.y * step + (int)threadIdx.x / LPP; s < s1;
-       s += (int)gridDim.y * step) {
+  for (int s = sf; s < s1; s += (int)gridDim.y * step) {
     const double xi = x[s], yi = y[s], zi = z[s];
     // velocities for the fused kick: the plain pass loads them early so that
     // the pair loop hides the latency; the energy pass, short of registers,
@@ -174,13 +188,19 @@ void k_lj_force(const double* __restrict__ x, const double* __restrict__ y,
       vyi = out.vy[s];
       vzi = out.vz[s];
     }
-    const int ngroups = (tl.cnt[s] + 3) >> 2;
+    const bool first = LPP == 8 && s == sf;
+    const int ngroups = ((first ? cnt0 : tl.cnt[s]) + 3) >> 2;
     const uint64_t* __restrict__ col = tl.nbr + s;
     double ax = 0.0, ay = 0.0, az = 0.0, ei = 0.0;
-    uint64_t next = part < ngroups ? col[(int64_t)part * tl.stride] : 0;
+    uint64_t next = first ? held[0] : (part < ngroups ? col[(int64_t)part * tl.stride] : 0);
     for (int gi = part; gi < ngroups; gi += LPP) {
       const uint64_t word = next;
-      if (gi + LPP < ngroups) next = col[(int64_t)(gi + LPP) * tl.stride];
+      if (first && gi < part + (kHeld - 1) * LPP) {
+        next = held[1 % kHeld];  // held words move up
+        held[1 % kHeld] = held[2 % kHeld];
+      } else if (gi + LPP < ngroups) {
+        next = col[(int64_t)(gi + LPP) * tl.stride];
+      }
       // FP32 plain pass: entry k + 1's tile position is read while entry k is
       // computed (the other variants have no registers to spare for it)
       constexpr bool kAhead = !ENERGY && sizeof(MT) == 4;
@@ -392,7 +412,7 @@ __device__ __forceinline__ bool lane_group(int p0, int npart, int t, LaneGroup& 
 #define MDPL_PLAIN_THREADS 512
 #endif
 constexpr int kPlainThreads = MDPL_PLAIN_THREADS;
-constexpr int kPartThreads = 256;  // of a part, where a brick has several (lane slots in turns)
+constexpr int kPartThreads = 512;  // of a part, where a brick has several (lane slots in turns)
 
 // Plain FP32 pass: the pair loop of every particle of the brick (its own
 // coordinates from its tile slot); the lanes of a wave take the same number

@@ -127,6 +127,82 @@ __device__ __forceinline__ int scan_range(const TS& t, int ub, int ue, const Row
   return found;
 }
 
+// One stencil row of up to 128 candidates against one particle per lane, the
+// decisions kept as a bit per candidate, so that a second pass over the
+// accepted ones can store them without testing again.  The same screen and
+// exact test as scan_range.  Candidates past the row (within the tile's
+// arrays or just behind them in LDS) are masked out.
+constexpr int kRowWords = 4;
+struct RowBits {
+  uint32_t w[kRowWords];
+};
+template <typename TS>
+__device__ __forceinline__ int row_bits(const TS& t, int ub, int n, const RowScan& q, float r2,
+                                        float guard, RowBits& bits) {
+  int found = 0;
+#pragma unroll
+  for (int c = 0; c < kRowWords; ++c) {
+    uint32_t word = 0;
+    const int left = n - 32 * c, u0 = ub + 32 * c;
+    if (__any(left > 0)) {
+      const int u = left > 0 ? u0 : 0;
+      const float *px = t.x + u, *py = t.y + u, *pz = t.z + u;
+      float near = 3e38f;
+#pragma unroll
+      for (int b = 31; b >= 0; --b) {
+        const float dx = q.xi - px[b], dy = q.yi - py[b], dz = q.zi - pz[b];
+        const float e =
+            __builtin_fmaf(dz, dz, __builtin_fmaf(dy, dy, __builtin_fmaf(dx, dx, -r2)));
+        near = fminf(near, __builtin_fabsf(e));
+        word = (word << 1) | (e < 0.0f ? 1u : 0u);
+        if (b % 8 == 0) __builtin_amdgcn_sched_barrier(0);
+      }
+      if (near <= guard) {  // the definition decides those inside the guard band
+        for (int b = 0; b < 32 && b < left; ++b) {
+          const float dx = q.xi - px[b], dy = q.yi - py[b], dz = q.zi - pz[b];
+          const float e =
+              __builtin_fmaf(dz, dz, __builtin_fmaf(dy, dy, __builtin_fmaf(dx, dx, -r2)));
+          if (!(__builtin_fabsf(e) <= guard)) continue;
+          const int cell = t.cell[u0 + b];
+          const int sj = t.src[cell] + (u0 + b - t.prefix[cell]);
+          const bool in = exact_d2(q.xs, q.ys, q.zs, q.x[sj], q.y[sj], q.z[sj], q.Lx, q.Ly, q.Lz,
+                                   q.hx, q.hy, q.hz) < q.r2;
+          word = (word & ~(1u << b)) | (in ? 1u << b : 0u);
+        }
+      }
+      word &= left >= 32 ? ~0u : (left > 0 ? (1u << left) - 1u : 0u);
+      const int self = q.self - u0;
+      word &= self >= 0 && self < 32 ? ~(1u << self) : ~0u;
+    }
+    bits.w[c] = word;
+    found += __popc(word);
+  }
+  return found;
+}
+
+// Stores the accepted candidates of a row as entries m, m + 1, ... of the
+// particle's list, in the order of scan_range with K = 1 (ascending) or K = 2
+// lanes per particle (of every eight the even ones first).
+__device__ __forceinline__ void row_store(const RowBits& bits, int ub, uint32_t m,
+                                          const RowScan& q) {
+#pragma unroll
+  for (int c = 0; c < kRowWords; ++c) {
+    uint32_t w = bits.w[c];
+    if (q.K == 2) {  // even bits of each byte to its low half, odd bits to its high half
+      uint32_t x = (w ^ (w >> 1)) & 0x22222222u;
+      w ^= x ^ (x << 1);
+      x = (w ^ (w >> 2)) & 0x0c0c0c0cu;
+      w ^= x ^ (x << 2);
+    }
+    for (; w && m < (uint32_t)q.max_nb; w &= w - 1, ++m) {
+      int b = __builtin_ctz(w);
+      if (q.K == 2) b = (b & ~7) | ((b & 3) << 1) | ((b >> 2) & 1);
+      *(uint16_t*)((char*)q.base + (__umul24(m >> 2, q.pitch) + ((m & 3u) << 1))) =
+          (uint16_t)((ub + 32 * c + b) << kFullShift);
+    }
+  }
+}
+
 // One wave per home cell (up to 16 per workgroup); at most 64 VGPRs so that
 // two 1024-thread workgroups share a CU.  TS: the tile (full or half list).
 //
@@ -136,12 +212,13 @@ __device__ __forceinline__ int scan_range(const TS& t, int ub, int ue, const Row
 // that each knows where its rows' entries start in the list, and then scan
 // again and store; the lists are the same, entry for entry, as those of one
 // wave.  One wave's scan of all nine rows, a serial chain, is what such
-// builds wait for: N = 1000 118 -> 33 us, N = 4096 73 -> 18 us, N = 32768
+// builds wait for: N = 1000 118 -> 22 us, N = 4096 73 -> 18 us, N = 32768
 // 82 -> 42 us.
 template <typename TS, bool HALF, bool A24, int RW>
-__global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8))) void k_build_tile_nlist(
+__global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(RW == 9 ? 4 : 8))) void
+k_build_tile_nlist(
     const double* __restrict__ x, const double* __restrict__ y, const double* __restrict__ z,
-    const int32_t* __restrict__ skeys, const int32_t* __restrict__ cs, Grid g, double r2,
+    const int32_t* __restrict__ cs, Grid g, double r2,
     float guard, TileList tl, uint32_t* __restrict__ flags, int32_t* __restrict__ maxcount,
     int cells) {
   __shared__ TS t;
@@ -185,6 +262,8 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8))) void 
       t.y[TS::kDummy] = kFarF;
       t.z[TS::kDummy] = kFarF;
     }
+    // (several slots per thread in flight where the workgroups are small)
+#pragma unroll RW == 9 ? 4 : 1
     for (int u = threadIdx.x; u < nt; u += blockDim.x) {
       const int c = t.cell[u];
       const int src = t.src[c] + (u - t.prefix[c]);
@@ -271,7 +350,56 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8))) void 
   };
   if constexpr (RW > 1) {
     const int lc = lc0 + wave / RW, r = wave % RW;  // one cell per RW waves (cells * RW waves)
-    if (lc < lc1) scan_cell(lc, 9 / RW * r, 9 / RW * (r + 1), rcnt[r], std::true_type());
+    // A cell of 22 to 64 particles takes a lane each (K below is at most 2) and
+    // a row's decisions fit registers, unless the row is very long
+    RowScan q;
+    RowBits bits;
+    int row_ub = 0, row_la = -1;
+    bool direct = false;
+    if constexpr (RW == 9) {
+      const int lx = lc % g.B[0], ly = (lc / g.B[0]) % g.B[1], lz = lc / (g.B[0] * g.B[1]);
+      const int tc0 = ((lz + 1) * (g.B[1] + 2) + (ly + 1)) * TX + (lx + 1);
+      const int na = lc < lc1 ? t.prefix[tc0 + 1] - t.prefix[tc0] : 0;
+      if (na > 21 && na <= 64) {
+        const int self = t.prefix[tc0] + lane, s = t.src[tc0] + lane;
+        const bool ok = lane < na && self < TS::kCap && s - s0 >= 0 && s - s0 < kBrickMax && s < s1;
+        const int tcl = tc0 + (r / 3 - 1) * TXY + (r % 3 - 1) * TX - 1;
+        const bool lower = xh && lane < tlow[tc0], upper = xh && !lower;
+        row_ub = t.prefix[tcl] + (upper ? tlow[tcl] : 0);
+        int ue = lower ? t.prefix[tcl + 2] + tlow[tcl + 2] : t.prefix[tcl + 3];
+        ue = ue < TS::kCap ? ue : TS::kCap;
+        const int n = ok ? ue - row_ub : 0;
+        direct = !__any(n > 32 * kRowWords);
+        if (direct) {
+          q.self = self;
+          q.K = 64 / na;
+          q.max_nb = max_nb;
+          q.xi = ok ? t.x[self] : 0.0f;
+          q.yi = ok ? t.y[self] : 0.0f;
+          q.zi = ok ? t.z[self] : 0.0f;
+          q.xs = ok ? x[s] : 0.0;
+          q.ys = ok ? y[s] : 0.0;
+          q.zs = ok ? z[s] : 0.0;
+          q.x = x;
+          q.y = y;
+          q.z = z;
+          q.r2 = r2;
+          q.Lx = Lx;
+          q.Ly = Ly;
+          q.Lz = Lz;
+          q.hx = 0.5 * Lx;
+          q.hy = 0.5 * Ly;
+          q.hz = 0.5 * Lz;
+          q.base = half + (int64_t)(ok ? s : 0) * 4;
+          q.pitch = (uint32_t)(tl.stride * 8);
+          row_la = ok ? s - s0 : -1;
+          const int found = row_bits(t, row_ub, n, q, (float)r2, guard, bits);
+          if (ok) rcnt[r][row_la] = found;
+        }
+      }
+    }
+    if (!direct && lc < lc1)
+      scan_cell(lc, 9 / RW * r, 9 / RW * (r + 1), rcnt[r], std::true_type());
     __syncthreads();
     // where each row group's entries start, and the particle's count
     for (int la = p0 - s0 + threadIdx.x; la < p1 - s0 && la < kBrickMax; la += blockDim.x) {
@@ -284,7 +412,11 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8))) void 
       acnt[la] = sum;
     }
     __syncthreads();
-    if (lc < lc1) scan_cell(lc, 9 / RW * r, 9 / RW * (r + 1), rcnt[r], std::false_type());
+    if (direct) {
+      if (row_la >= 0) row_store(bits, row_ub, (uint32_t)rcnt[r][row_la], q);
+    } else if (lc < lc1) {
+      scan_cell(lc, 9 / RW * r, 9 / RW * (r + 1), rcnt[r], std::false_type());
+    }
   } else {
     for (int lc = wave; lc < g.V; lc += nwaves) scan_cell(lc, 0, 9, acnt, std::false_type());
   }
@@ -311,7 +443,7 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8))) void 
 }
 
 hipError_t build_tile_nlist(const double* x, const double* y, const double* z,
-                            const int32_t* skeys, const int32_t* cell_start, const Grid& g,
+                            const int32_t* cell_start, const Grid& g,
                             double r2, TileList tl, uint32_t* flags, int32_t* maxcount,
                             hipStream_t st) {
   const unsigned threads = g.V * 64 < 1024 ? (unsigned)g.V * 64 : 1024u;
@@ -328,7 +460,7 @@ hipError_t build_tile_nlist(const double* x, const double* y, const double* z,
   const dim3 grid(tile_grid(g));
   if (tl.half) {
     hipLaunchKernelGGL((k_build_tile_nlist<TileHalf32, true, false, 1>), grid, dim3(threads), 0, st,
-                       x, y, z, skeys, cell_start, g, r2, guard, tl, flags, maxcount, g.V);
+                       x, y, z, cell_start, g, r2, guard, tl, flags, maxcount, g.V);
     return hipGetLastError();
   }
   // few bricks: the cells of a brick shared by several workgroups, the rows
@@ -340,18 +472,18 @@ hipError_t build_tile_nlist(const double* x, const double* y, const double* z,
   const bool a24 = tl.stride * 8 < (int64_t)(1 << 24);
   if (a24 && parts > 1 && rw == 9)
     hipLaunchKernelGGL((k_build_tile_nlist<TileShared32, false, true, 9>), dim3(grid.x, parts),
-                       dim3(cells * 9 * 64), 0, st, x, y, z, skeys, cell_start, g, r2, guard, tl,
+                       dim3(cells * 9 * 64), 0, st, x, y, z, cell_start, g, r2, guard, tl,
                        flags, maxcount, cells);
   else if (a24 && parts > 1 && rw == 3)
     hipLaunchKernelGGL((k_build_tile_nlist<TileShared32, false, true, 3>), dim3(grid.x, parts),
-                       dim3(cells * 3 * 64), 0, st, x, y, z, skeys, cell_start, g, r2, guard, tl,
+                       dim3(cells * 3 * 64), 0, st, x, y, z, cell_start, g, r2, guard, tl,
                        flags, maxcount, cells);
   else if (a24)
     hipLaunchKernelGGL((k_build_tile_nlist<TileShared32, false, true, 1>), grid, dim3(threads), 0,
-                       st, x, y, z, skeys, cell_start, g, r2, guard, tl, flags, maxcount, g.V);
+                       st, x, y, z, cell_start, g, r2, guard, tl, flags, maxcount, g.V);
   else
     hipLaunchKernelGGL((k_build_tile_nlist<TileShared32, false, false, 1>), grid, dim3(threads), 0,
-                       st, x, y, z, skeys, cell_start, g, r2, guard, tl, flags, maxcount, g.V);
+                       st, x, y, z, cell_start, g, r2, guard, tl, flags, maxcount, g.V);
   return hipGetLastError();
 }
 
