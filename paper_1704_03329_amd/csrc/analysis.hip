@@ -513,12 +513,6 @@ __device__ __forceinline__ int cna_lane(const BondScan& q, const Grid& g, double
   return ni;
 }
 
-__device__ __forceinline__ void wave_lds_fence() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 // All bonds of slot s by the whole wave (exact test of every stencil
 // candidate): their number, and the slots of the first 64 in list (LDS).
 // The 27 cells' ranges are laid end to end over the lanes, so that a stencil
@@ -544,7 +538,7 @@ __device__ inline int bonds_of(const BondScan& q, const Grid& g, double rc2, int
   }
   const int total = __shfl(upto, 26, 64);
   int found = 0;
-  wave_lds_fence();
+  wave_lds_sync();
   for (int u0 = 0; u0 < total; u0 += 64) {
     const int u = u0 + lane;
     int c = 0;  // the cell of candidate u: the first with upto > u
@@ -563,7 +557,7 @@ __device__ inline int bonds_of(const BondScan& q, const Grid& g, double rc2, int
     if (in && at < 64) list[at] = (uint32_t)t;
     found += __popcll(m);
   }
-  wave_lds_fence();
+  wave_lds_sync();
   return found;
 }
 
@@ -577,9 +571,9 @@ __device__ inline int bonds_noted(const BondScan& q, const Grid& g, double rc2, 
   const bool in = lane < c && exact_d2(q.sx[s], q.sy[s], q.sz[s], q.sx[t], q.sy[t], q.sz[t], Lx, Ly,
                                        Lz, 0.5 * Lx, 0.5 * Ly, 0.5 * Lz) < rc2;
   const uint64_t m = __ballot(in);
-  wave_lds_fence();
+  wave_lds_sync();
   if (in) list[__popcll(m & ((1ull << lane) - 1))] = t;
-  wave_lds_fence();
+  wave_lds_sync();
   return __popcll(m);
 }
 

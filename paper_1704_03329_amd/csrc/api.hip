@@ -1151,7 +1151,7 @@ mdpl_status mdpl_desc_fwd(mdpl_sim* s, const double* x, const double* y, const d
   if (!s || !x || !y || !z || !G || s->tl.half || s->tl.cells) return MDPL_EINVAL;
   if (!s->built) return MDPL_ESTATE;
   HIP_TRY(gather_canonical(x, y, z, s->perm, s->skeys, s->n, s->g, s->sx, s->sy, s->sz, s->st));
-  HIP_TRY(desc_forward(s->sx, s->sy, s->sz, s->cell_start, s->g, s->tl, (float)s->p.rc, s->perm, G,
+  HIP_TRY(desc_forward(s->sx, s->sy, s->sz, s->cell_start, s->g, s->tl, (float)s->p.rc, s->perm, s->n, G,
                        mom, s->st));
   return MDPL_OK;
 }
@@ -1220,7 +1220,7 @@ mdpl_status mdpl_mlp_forces(mdpl_sim* s, const mdpl_mlp_weights* w, const double
   float* e = mom + 50 * n;
   float* dG = e + n;
   HIP_TRY(gather_canonical(x, y, z, s->perm, s->skeys, n, s->g, s->sx, s->sy, s->sz, s->st));
-  HIP_TRY(desc_forward(s->sx, s->sy, s->sz, s->cell_start, s->g, s->tl, (float)s->p.rc, s->perm, G,
+  HIP_TRY(desc_forward(s->sx, s->sy, s->sz, s->cell_start, s->g, s->tl, (float)s->p.rc, s->perm, s->n, G,
                        mom, s->st, fx, fy, fz));
   MlpArgs a = mlp_args(w, G, n);
   a.energy = energy ? energy : e;
@@ -1309,7 +1309,7 @@ mdpl_status mdpl_run_mlp(mdpl_sim* s, const mdpl_mlp_weights* w, float* ws, int6
                       HIP_TRY(hipEventRecord(e0, s->st));
                     }
                     HIP_TRY(desc_forward(cur.x, cur.y, cur.z, s->cell_start, s->g, s->tl, rc,
-                                         nullptr, G, mom, s->st, (float*)cur.fx, (float*)cur.fy,
+                                         nullptr, n, G, mom, s->st, (float*)cur.fx, (float*)cur.fy,
                                          (float*)cur.fz));
                     MlpArgs a = mlp_args(w, G, n);
                     a.energy = e;

@@ -48,6 +48,7 @@ namespace mdpl {
 constexpr int kNRad = 16;
 constexpr int kNFeat = 24;
 constexpr int kNMom = 25;
+constexpr int kNCoef = 84;  // adjoint coefficients of a particle
 constexpr float kEtaR = 41.32231404958678f;  // 1 / (2 * 0.11^2)
 
 // exp(x) on the hardware base-2 exponential
@@ -123,6 +124,123 @@ __device__ __forceinline__ int next_bit(uint64_t& m0, uint64_t& m1) {
   m0 = lo ? cl : m0;
   m1 = lo ? m1 : cl;
   return b;
+}
+
+// What one in-range pair adds to the sums of its centre.
+struct PairBasis {
+  float eb[kNRad];   // radial Gaussians
+  float q[kNMom];    // z^k Re/Im (x+iy)^m, k <= 4 - m (the order below)
+  float fc;          // cutoff function
+  float g0, g1;      // exp(-eta r^2), eta = 0.5, 2
+  float w0, w1;      // times fc
+};
+__device__ __forceinline__ void pair_basis(float dx, float dy, float dz, float half_rev,
+                                           PairBasis& p) {
+  const float d2f = dx * dx + dy * dy + dz * dz;
+  // 1/r from the hardware reciprocal square root (about 1 ulp), r = d2/r
+  const float ir = __builtin_amdgcn_rsqf(d2f);
+  const float r = d2f * ir;
+  const float ux = dx * ir, uy = dy * ir, uz = dz * ir;
+  p.fc = 0.5f * (__builtin_amdgcn_cosf(r * half_rev) + 1.0f);  // cos(pi r / rc)
+  radial_basis(r, p.eb);
+  // per eta the sums of w z^k Re/Im (x+iy)^m, k <= 4 - m (the moments
+  // follow from them by the coefficients of P~_l^m, once per particle)
+  const float z2 = uz * uz, z3 = z2 * uz, z4 = z2 * z2;
+  const float c2 = ux * ux - uy * uy, s2 = 2.0f * ux * uy;
+  const float c3 = c2 * ux - s2 * uy, s3 = c2 * uy + s2 * ux;
+  const float c4 = c3 * ux - s3 * uy, s4 = c3 * uy + s3 * ux;
+  const float q[kNMom] = {1.0f, uz,      z2,      z3, z4,      ux,      ux * uz, ux * z2, ux * z3,
+                          uy,   uy * uz, uy * z2, uy * z3, c2, c2 * uz, c2 * z2, s2,      s2 * uz,
+                          s2 * z2, c3, c3 * uz, s3, s3 * uz, c4, s4};
+#pragma unroll
+  for (int k = 0; k < kNMom; ++k) p.q[k] = q[k];
+  p.g0 = exp_hw(-0.5f * r * r);
+  p.g1 = (p.g0 * p.g0) * (p.g0 * p.g0);
+  p.w0 = p.g0 * p.fc;
+  p.w1 = p.g1 * p.fc;
+}
+
+// The features and moments of slot s from its radial sums G, its z-power sums
+// M per eta and diag = sum w^2 per eta.  Every rounding is written out, so
+// that the two forward passes agree to the last bit.
+__device__ __forceinline__ void desc_finish(const DescIO& io, int s, const float (&G)[kNRad],
+                                            float (&M)[2][kNMom], const float (&diag)[2]) {
+#pragma clang fp contract(off)
+  // z-power sums (order of q above) -> C_lm, S_lm in the moment layout
+#pragma unroll
+  for (int e = 0; e < 2; ++e) {
+    const float* N = M[e];
+    auto two = [](float a, float x, float b, float y) { return __builtin_fmaf(b, y, a * x); };
+    float C[kNMom];
+    C[0] = N[0];
+    C[1] = N[1];
+    C[4] = __builtin_fmaf(1.5f, N[2], -(0.5f * N[0]));
+    C[9] = two(2.5f, N[3], -1.5f, N[1]);
+    C[16] = __builtin_fmaf(0.375f, N[0], two(4.375f, N[4], -3.75f, N[2]));
+    C[2] = N[5];                             // C_11
+    C[3] = N[9];                             // S_11
+    C[5] = 3.0f * N[6];                      // C_21
+    C[6] = 3.0f * N[10];                     // S_21
+    C[10] = two(7.5f, N[7], -1.5f, N[5]);    // C_31
+    C[11] = two(7.5f, N[11], -1.5f, N[9]);   // S_31
+    C[17] = two(17.5f, N[8], -7.5f, N[6]);   // C_41
+    C[18] = two(17.5f, N[12], -7.5f, N[10]); // S_41
+    C[7] = 3.0f * N[13];                     // C_22
+    C[8] = 3.0f * N[16];                     // S_22
+    C[12] = 15.0f * N[14];                   // C_32
+    C[13] = 15.0f * N[17];                   // S_32
+    C[19] = two(52.5f, N[15], -7.5f, N[13]); // C_42
+    C[20] = two(52.5f, N[18], -7.5f, N[16]); // S_42
+    C[14] = 15.0f * N[19];                   // C_33
+    C[15] = 15.0f * N[21];                   // S_33
+    C[21] = 105.0f * N[20];                  // C_43
+    C[22] = 105.0f * N[22];                  // S_43
+    C[23] = 105.0f * N[23];                  // C_44
+    C[24] = 105.0f * N[24];                  // S_44
+#pragma unroll
+    for (int k = 0; k < kNMom; ++k) M[e][k] = C[k];
+  }
+  float T[2][5];
+#pragma unroll
+  for (int e = 0; e < 2; ++e) {
+    T[e][0] = __builtin_fmaf(M[e][0], M[e][0], -diag[e]);
+#pragma unroll
+    for (int l = 1; l <= 4; ++l) {
+      float acc = 0.0f;
+#pragma unroll
+      for (int m = 1; m <= l; ++m) {
+        const float a = M[e][l * l + 2 * m - 1], b = M[e][l * l + 2 * m];
+        const float sq = __builtin_fmaf(a, a, b * b), om = omega(l * (l + 1) / 2 + m);
+        acc = m == 1 ? __builtin_fmaf(M[e][l * l], M[e][l * l], om * sq)
+                     : __builtin_fmaf(om, sq, acc);
+      }
+      T[e][l] = acc - diag[e];
+    }
+  }
+  const int64_t o = io.perm ? (int64_t)io.perm[s] : (int64_t)s;
+  if (io.fx) {  // the backward's outputs, cleared for its atomics
+    io.fx[o] = 0.0f;
+    io.fy[o] = 0.0f;
+    io.fz[o] = 0.0f;
+  }
+  float* __restrict__ Go = io.G + o * kNFeat;
+#pragma unroll
+  for (int k = 0; k < kNRad; ++k) Go[k] = G[k];
+#pragma unroll
+  for (int a = 0; a < 8; ++a) {
+    const int e = a & 1;
+    float acc = 0.0f;
+#pragma unroll
+    for (int l = 0; l <= 4; ++l) acc = __builtin_fmaf(ang_coef(a, l), T[e][l], acc);
+    Go[kNRad + a] = acc;
+  }
+  if (io.mom) {
+    float* __restrict__ Mo = io.mom + o * (2 * kNMom);
+#pragma unroll
+    for (int e = 0; e < 2; ++e)
+#pragma unroll
+      for (int k = 0; k < kNMom; ++k) Mo[e * kNMom + k] = M[e][k];
+  }
 }
 
 // ------------------------------------------------------------- forward
@@ -201,110 +319,24 @@ __global__ __launch_bounds__(512) void k_desc_fwd(const double* __restrict__ x,
         // keep the load here, a trip ahead of its use (no memory operation
         // may move across this point)
         asm volatile("" ::: "memory");
-        const float dx = t.px[u] - xi, dy = t.py[u] - yi, dz = t.pz[u] - zi;
-        const float d2f = dx * dx + dy * dy + dz * dz;
-        // 1/r from the hardware reciprocal square root (about 1 ulp), r = d2/r
-        const float ir = __builtin_amdgcn_rsqf(d2f);
-        const float r = d2f * ir;
-        const float ux = dx * ir, uy = dy * ir, uz = dz * ir;
-        const float fc = 0.5f * (__builtin_amdgcn_cosf(r * half_rev) + 1.0f);  // cos(pi r / rc)
-        float eb[kNRad];
-        radial_basis(r, eb);
+        PairBasis p;
+        pair_basis(t.px[u] - xi, t.py[u] - yi, t.pz[u] - zi, half_rev, p);
 #pragma unroll
-        for (int k = 0; k < kNRad; ++k) G[k] += eb[k] * fc;
-        // per eta the sums of w z^k Re/Im (x+iy)^m, k <= 4 - m (the moments
-        // follow from them by the coefficients of P~_l^m, once per particle)
-        const float z2 = uz * uz, z3 = z2 * uz, z4 = z2 * z2;
-        const float c2 = ux * ux - uy * uy, s2 = 2.0f * ux * uy;
-        const float c3 = c2 * ux - s2 * uy, s3 = c2 * uy + s2 * ux;
-        const float c4 = c3 * ux - s3 * uy, s4 = c3 * uy + s3 * ux;
-        const float q[kNMom] = {1.0f, uz,      z2,      z3, z4,      ux,      ux * uz, ux * z2, ux * z3,
-                                uy,   uy * uz, uy * z2, uy * z3, c2, c2 * uz, c2 * z2, s2,      s2 * uz,
-                                s2 * z2, c3, c3 * uz, s3, s3 * uz, c4, s4};
-        const float g0 = exp_hw(-0.5f * r * r);
-        const float g1 = (g0 * g0) * (g0 * g0);  // exp(-2 r^2)
-        const float w0 = g0 * fc;
-        const float w1 = g1 * fc;
-        diag[0] += w0 * w0;
-        diag[1] += w1 * w1;
+        for (int k = 0; k < kNRad; ++k) G[k] = __builtin_fmaf(p.eb[k], p.fc, G[k]);
+        const float w0 = p.w0, w1 = p.w1;
+        diag[0] = __builtin_fmaf(w0, w0, diag[0]);
+        diag[1] = __builtin_fmaf(w1, w1, diag[1]);
+        // the first monomial is 1: one rounding for g fc
+        M[0][0] = __builtin_fmaf(p.g0, p.fc, M[0][0]);
+        M[1][0] = __builtin_fmaf(p.g1, p.fc, M[1][0]);
 #pragma unroll
-        for (int k = 0; k < kNMom; ++k) {
-          M[0][k] += w0 * q[k];
-          M[1][k] += w1 * q[k];
+        for (int k = 1; k < kNMom; ++k) {
+          M[0][k] = __builtin_fmaf(w0, p.q[k], M[0][k]);
+          M[1][k] = __builtin_fmaf(w1, p.q[k], M[1][k]);
         }
       }
     }
-    // z-power sums (order of q above) -> C_lm, S_lm in the moment layout
-#pragma unroll
-    for (int e = 0; e < 2; ++e) {
-      const float* N = M[e];
-      float C[kNMom];
-      C[0] = N[0];
-      C[1] = N[1];
-      C[4] = 1.5f * N[2] - 0.5f * N[0];
-      C[9] = 2.5f * N[3] - 1.5f * N[1];
-      C[16] = 4.375f * N[4] - 3.75f * N[2] + 0.375f * N[0];
-      C[2] = N[5];                          // C_11
-      C[3] = N[9];                          // S_11
-      C[5] = 3.0f * N[6];                   // C_21
-      C[6] = 3.0f * N[10];                  // S_21
-      C[10] = 7.5f * N[7] - 1.5f * N[5];    // C_31
-      C[11] = 7.5f * N[11] - 1.5f * N[9];   // S_31
-      C[17] = 17.5f * N[8] - 7.5f * N[6];   // C_41
-      C[18] = 17.5f * N[12] - 7.5f * N[10]; // S_41
-      C[7] = 3.0f * N[13];                  // C_22
-      C[8] = 3.0f * N[16];                  // S_22
-      C[12] = 15.0f * N[14];                // C_32
-      C[13] = 15.0f * N[17];                // S_32
-      C[19] = 52.5f * N[15] - 7.5f * N[13]; // C_42
-      C[20] = 52.5f * N[18] - 7.5f * N[16]; // S_42
-      C[14] = 15.0f * N[19];                // C_33
-      C[15] = 15.0f * N[21];                // S_33
-      C[21] = 105.0f * N[20];               // C_43
-      C[22] = 105.0f * N[22];               // S_43
-      C[23] = 105.0f * N[23];               // C_44
-      C[24] = 105.0f * N[24];               // S_44
-#pragma unroll
-      for (int k = 0; k < kNMom; ++k) M[e][k] = C[k];
-    }
-    float T[2][5];
-#pragma unroll
-    for (int e = 0; e < 2; ++e) {
-#pragma unroll
-      for (int l = 0; l <= 4; ++l) {
-        float acc = M[e][l * l] * M[e][l * l];
-#pragma unroll
-        for (int m = 1; m <= l; ++m) {
-          const float a = M[e][l * l + 2 * m - 1], b = M[e][l * l + 2 * m];
-          acc += omega(l * (l + 1) / 2 + m) * (a * a + b * b);
-        }
-        T[e][l] = acc - diag[e];
-      }
-    }
-    const int64_t o = io.perm ? (int64_t)io.perm[s] : (int64_t)s;
-    if (io.fx) {  // the backward's outputs, cleared for its atomics
-      io.fx[o] = 0.0f;
-      io.fy[o] = 0.0f;
-      io.fz[o] = 0.0f;
-    }
-    float* __restrict__ Go = io.G + o * kNFeat;
-#pragma unroll
-    for (int k = 0; k < kNRad; ++k) Go[k] = G[k];
-#pragma unroll
-    for (int a = 0; a < 8; ++a) {
-      const int e = a & 1;
-      float acc = 0.0f;
-#pragma unroll
-      for (int l = 0; l <= 4; ++l) acc += ang_coef(a, l) * T[e][l];
-      Go[kNRad + a] = acc;
-    }
-    if (io.mom) {
-      float* __restrict__ Mo = io.mom + o * (2 * kNMom);
-#pragma unroll
-      for (int e = 0; e < 2; ++e)
-#pragma unroll
-        for (int k = 0; k < kNMom; ++k) Mo[e * kNMom + k] = M[e][k];
-    }
+    desc_finish(io, s, G, M, diag);
   }
 }
 
@@ -350,7 +382,7 @@ __device__ __forceinline__ void zpoly_of(const float* __restrict__ al, float* __
 //      dE/dG_k for the 16 radial features, k dE/dG_k) of one particle, from its
 // dE/dG (24) and moments (50); formed where the backward needs them.
 __device__ __forceinline__ void adjoint_coef(const float* __restrict__ d,
-                                             const float* __restrict__ mm, float out[84]) {
+                                             const float* __restrict__ mm, float out[kNCoef]) {
 #pragma unroll
   for (int e = 0; e < 2; ++e) {
     float b[5];
@@ -491,12 +523,60 @@ __global__ void k_zero3(float* __restrict__ a, float* __restrict__ b, float* __r
   }
 }
 
+// The term of the pair of own tile slot hs and neighbour slot u with the
+// centre's coefficients K: returned for the centre, subtracted from the
+// neighbour's accumulator (or, too large for it, from the output).
+__device__ __forceinline__ void scatter_pair(const TileF32& t, const Grid& g, const DescIO& io,
+                                             unsigned long long (&acc)[3][kTileMax],
+                                             const float* __restrict__ K, int hs, int u, float rc,
+                                             float& gx, float& gy, float& gz) {
+  const float pi_rc = 3.14159265358979f / rc, half_rev = 0.5f / rc;
+  const float dx = t.px[u] - t.px[hs], dy = t.py[u] - t.py[hs], dz = t.pz[u] - t.pz[hs];
+  const float d2 = dx * dx + dy * dy + dz * dz;
+  // 1/r from the hardware reciprocal square root (about 1 ulp), r = d2/r
+  const float ir = __builtin_amdgcn_rsqf(d2);
+  const float r = d2 * ir;
+  const float fc = 0.5f * (__builtin_amdgcn_cosf(r * half_rev) + 1.0f);
+  const float dfc = -0.5f * pi_rc * __builtin_amdgcn_sinf(r * half_rev);
+  gx = gy = gz = 0.0f;
+  pair_grad(K, r, ir, dx * ir, dy * ir, dz * ir, fc, dfc, gx, gy, gz);
+  if (fix_fits((double)(__builtin_fabsf(gx) + __builtin_fabsf(gy) + __builtin_fabsf(gz)))) {
+    atomicAdd(&acc[0][u], fix_of(-(double)gx));
+    atomicAdd(&acc[1][u], fix_of(-(double)gy));
+    atomicAdd(&acc[2][u], fix_of(-(double)gz));
+  } else {
+    const int lo = tile_cell_of(t, (g.B[0] + 2) * (g.B[1] + 2) * (g.B[2] + 2), u);
+    const int sj = t.src[lo] + (u - t.prefix[lo]);
+    const int64_t oj = io.perm ? (int64_t)io.perm[sj] : (int64_t)sj;
+    unsafeAtomicAdd(&io.fx[oj], -gx);
+    unsafeAtomicAdd(&io.fy[oj], -gy);
+    unsafeAtomicAdd(&io.fz[oj], -gz);
+  }
+}
+
+// The accumulators of the tile's slots to the outputs.
+__device__ __forceinline__ void add_reactions(const TileF32& t, const Grid& g, const DescIO& io,
+                                              const unsigned long long (&acc)[3][kTileMax],
+                                              int nt) {
+  const int ntc = (g.B[0] + 2) * (g.B[1] + 2) * (g.B[2] + 2);
+  for (int u = threadIdx.x; u < nt; u += blockDim.x) {
+    const unsigned long long qx = acc[0][u], qy = acc[1][u], qz = acc[2][u];
+    if (qx | qy | qz) {
+      const int lo = tile_cell_of(t, ntc, u);
+      const int sj = t.src[lo] + (u - t.prefix[lo]);
+      const int64_t oj = io.perm ? (int64_t)io.perm[sj] : (int64_t)sj;
+      unsafeAtomicAdd(&io.fx[oj], (float)fix_value(qx));
+      unsafeAtomicAdd(&io.fy[oj], (float)fix_value(qy));
+      unsafeAtomicAdd(&io.fz[oj], (float)fix_value(qz));
+    }
+  }
+}
+
 // Workgroups of up to kBwdThreads: the fixed-point accumulators make the LDS
 // of one workgroup fill most of a CU, so its own waves are all the latency
 // hiding there is; at 161 VGPRs three waves per SIMD fit (768 threads: 197 ->
 // 183 us against 512 at N = 262144).
-constexpr int kBwdThreads = 768;
-template <int LPP>
+constexpr int kBwdThreads = 768, kBwdLanes = 2;
 __global__ __launch_bounds__(kBwdThreads) void k_desc_bwd(const double* __restrict__ x,
                                                    const double* __restrict__ y,
                                                    const double* __restrict__ z,
@@ -508,7 +588,6 @@ __global__ __launch_bounds__(kBwdThreads) void k_desc_bwd(const double* __restri
   const int brick = brick_of_block(g);
   if (brick >= g.nbricks) return;
   const int total = tile_cells(g, brick, cs, t);
-  const int ntc = (g.B[0] + 2) * (g.B[1] + 2) * (g.B[2] + 2);
   const int nt = total < TileF32::kCap ? total : TileF32::kCap;
   for (int u = threadIdx.x; u < nt; u += blockDim.x) {
     acc[0][u] = 0;
@@ -520,23 +599,21 @@ __global__ __launch_bounds__(kBwdThreads) void k_desc_bwd(const double* __restri
   tile_centre(g, brick, ox, oy, oz);
   tile_load_f32(g, x, y, z, total, ox, oy, oz, s0, t, home);  // ends with a barrier
   const float rc2 = rc * rc;
-  const float pi_rc = 3.14159265358979f / rc;
-  const float half_rev = 0.5f / rc;
-  const int part = (int)threadIdx.x % LPP;  // lanes of a particle take every LPP-th list word
-  const int step = (int)blockDim.x / LPP;
-  for (int s = s0 + (int)blockIdx.y * step + (int)threadIdx.x / LPP; s < s1;
+  const int part = (int)threadIdx.x % kBwdLanes;  // lanes of a particle take every kBwdLanes-th list word
+  const int step = (int)blockDim.x / kBwdLanes;
+  for (int s = s0 + (int)blockIdx.y * step + (int)threadIdx.x / kBwdLanes; s < s1;
        s += (int)gridDim.y * step) {
     // FP32 coordinates relative to the tile centre (the force pass's), own
     // position from the particle's own slot
     const int hs = s - s0 < kBrickMax ? home[s - s0] : TileF32::kDummy;
     const float xi = t.px[hs], yi = t.py[hs], zi = t.pz[hs];
     const int64_t oi = io.perm ? (int64_t)io.perm[s] : (int64_t)s;
-    float Ki[84];
+    float Ki[kNCoef];
     adjoint_coef(io.dEdG + oi * kNFeat, io.mom + oi * (2 * kNMom), Ki);
     float fx = 0.0f, fy = 0.0f, fz = 0.0f;
     const int ng = (tl.cnt[s] + 3) >> 2;
     const uint64_t* __restrict__ col = tl.nbr + s;
-    const int nw = ng > part ? (ng - part + LPP - 1) / LPP : 0;  // this lane's words: part + LPP w
+    const int nw = ng > part ? (ng - part + kBwdLanes - 1) / kBwdLanes : 0;  // this lane's words: part + kBwdLanes w
     for (int w0 = 0; w0 < nw; w0 += 16) {
       // the in-range entries of up to 16 words as a bit mask (bit 4 w + q:
       // entry q of word w0 + w), so that the pair terms below run on the
@@ -549,7 +626,7 @@ __global__ __launch_bounds__(kBwdThreads) void k_desc_bwd(const double* __restri
         uint64_t wd[4];
 #pragma unroll
         for (int k = 0; k < 4; ++k)
-          wd[k] = col[(int64_t)(part + LPP * (w0 + (wg + k < wn ? wg + k : wn - 1))) * tl.stride];
+          wd[k] = col[(int64_t)(part + kBwdLanes * (w0 + (wg + k < wn ? wg + k : wn - 1))) * tl.stride];
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
           const int w = wg + k;
@@ -569,37 +646,17 @@ __global__ __launch_bounds__(kBwdThreads) void k_desc_bwd(const double* __restri
       // loaded a trip ahead
       // (the load goes to a valid row even when no bit is left)
       int b = mask ? __builtin_ctzll(mask) : 64;
-      uint64_t word = col[(int64_t)(part + LPP * (w0 + (b < 64 ? b >> 2 : 0))) * tl.stride];
+      uint64_t word = col[(int64_t)(part + kBwdLanes * (w0 + (b < 64 ? b >> 2 : 0))) * tl.stride];
       while (b < 64) {
         const int u = (int)((word >> (16 * (b & 3))) & 0xffff) >> kFullShift;
         mask &= mask - 1;
         b = mask ? __builtin_ctzll(mask) : 64;
-        word = col[(int64_t)(part + LPP * (w0 + (b < 64 ? b >> 2 : 0))) * tl.stride];
-        const float dx = t.px[u] - xi, dy = t.py[u] - yi, dz = t.pz[u] - zi;
-        const float d2 = dx * dx + dy * dy + dz * dz;
-        // 1/r from the hardware reciprocal square root (about 1 ulp), r = d2/r
-        const float ir = __builtin_amdgcn_rsqf(d2);
-        const float r = d2 * ir;
-        const float ux = dx * ir, uy = dy * ir, uz = dz * ir;
-        const float fc = 0.5f * (__builtin_amdgcn_cosf(r * half_rev) + 1.0f);
-        const float dfc = -0.5f * pi_rc * __builtin_amdgcn_sinf(r * half_rev);
-        float gx = 0.0f, gy = 0.0f, gz = 0.0f;
-        pair_grad(Ki, r, ir, ux, uy, uz, fc, dfc, gx, gy, gz);
+        word = col[(int64_t)(part + kBwdLanes * (w0 + (b < 64 ? b >> 2 : 0))) * tl.stride];
+        float gx, gy, gz;
+        scatter_pair(t, g, io, acc, Ki, hs, u, rc, gx, gy, gz);
         fx += gx;
         fy += gy;
         fz += gz;
-        if (fix_fits((double)(__builtin_fabsf(gx) + __builtin_fabsf(gy) + __builtin_fabsf(gz)))) {
-          atomicAdd(&acc[0][u], fix_of(-(double)gx));
-          atomicAdd(&acc[1][u], fix_of(-(double)gy));
-          atomicAdd(&acc[2][u], fix_of(-(double)gz));
-        } else {
-          const int lo = tile_cell_of(t, ntc, u);
-          const int sj = t.src[lo] + (u - t.prefix[lo]);
-          const int64_t oj = io.perm ? (int64_t)io.perm[sj] : (int64_t)sj;
-          unsafeAtomicAdd(&io.fx[oj], -gx);
-          unsafeAtomicAdd(&io.fy[oj], -gy);
-          unsafeAtomicAdd(&io.fz[oj], -gz);
-        }
       }
     }
     unsafeAtomicAdd(&io.fx[oi], fx);
@@ -607,29 +664,280 @@ __global__ __launch_bounds__(kBwdThreads) void k_desc_bwd(const double* __restri
     unsafeAtomicAdd(&io.fz[oi], fz);
   }
   __syncthreads();
-  for (int u = threadIdx.x; u < nt; u += blockDim.x) {
-    const unsigned long long qx = acc[0][u], qy = acc[1][u], qz = acc[2][u];
-    if (qx | qy | qz) {
-      const int lo = tile_cell_of(t, ntc, u);
-      const int sj = t.src[lo] + (u - t.prefix[lo]);
-      const int64_t oj = io.perm ? (int64_t)io.perm[sj] : (int64_t)sj;
-      const float ax = (float)fix_value(qx), ay = (float)fix_value(qy), az = (float)fix_value(qz);
-      unsafeAtomicAdd(&io.fx[oj], ax);
-      unsafeAtomicAdd(&io.fy[oj], ay);
-      unsafeAtomicAdd(&io.fz[oj], az);
-    }
+  add_reactions(t, g, io, acc, nt);
+}
+
+// ---------------------------------------------- small systems: wave kernels
+// With few bricks the passes above wait for one lane's serial walk over its
+// ~57 neighbours (46 and 35 us at N = 4096 whatever the launch).  Here a wave
+// takes a particle: its list entries are tested side by side, the in-range
+// ones packed in list order, and each lane forms the terms of one neighbour.
+// A particle costs several times the serial passes' share of a CU (450 vector
+// and 170 LDS instructions of a whole wave in the forward pass, half of its
+// time on the LDS), so that it pays while latency and not throughput sets the
+// time.  Whole evaluation of the potential, serial passes in parts -> these:
+// N = 1728 138 -> 64 us, 4096 138 -> 77, 10648 152 -> 133, 13824 150 -> 125,
+// but 15625 147 -> 155 and 19683 168 -> 214: hence kWaveN.
+constexpr int kWaveThreads = 512, kWaves = kWaveThreads / 64;
+constexpr int kWaveN = 14000;     // largest system
+constexpr int kWaveBatch = 40;    // particles of a workgroup at a time (forward)
+constexpr int kWaveList = 1024;   // in-range entries of a particle (at most max_nb)
+
+// A slot's count and the lane's word of its first 64, loaded while the
+// particle before is computed.
+struct WaveList {
+  int cnt;
+  uint64_t word;
+};
+__device__ __forceinline__ WaveList wave_list(const TileList& tl, int s, bool has) {
+  const int lane = (int)threadIdx.x & 63;
+  WaveList w{0, 0};
+  if (has) {
+    w.cnt = tl.cnt[s];
+    if (4 * lane < tl.max_nb) w.word = tl.nbr[s + (int64_t)lane * tl.stride];
   }
+  return w;
+}
+// The in-range entries of slot s (own tile slot hs), packed in list order
+// into list (LDS, the wave's own); returns their number.
+template <typename TS>
+__device__ __forceinline__ int wave_in_range(const TS& t, const TileList& tl, int s,
+                                             const WaveList& first, int hs, float rc2, int nt,
+                                             uint16_t* __restrict__ list) {
+  const int lane = (int)threadIdx.x & 63;
+  const float xi = t.px[hs], yi = t.py[hs], zi = t.pz[hs];
+  const int ng = (first.cnt + 3) >> 2;
+  int found = 0;
+  wave_lds_sync();
+  for (int g0 = 0; g0 < ng; g0 += 64) {
+    const bool has = g0 + lane < ng;
+    const uint64_t word =
+        g0 == 0 ? first.word : (has ? tl.nbr[s + (int64_t)(g0 + lane) * tl.stride] : 0);
+    int u[4], in[4], c = 0;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const int e = (int)((word >> (16 * k)) & 0xffff) >> kFullShift;
+      u[k] = has && e < nt ? e : TS::kDummy;  // padding: the far-away dummy slot
+      const float dx = t.px[u[k]] - xi, dy = t.py[u[k]] - yi, dz = t.pz[u[k]] - zi;
+      in[k] = dx * dx + dy * dy + dz * dz < rc2 ? 1 : 0;
+      c += in[k];
+    }
+    const int upto = wave_scan_i32(c);
+    int at = found + upto - c;
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+      if (in[k]) list[at++] = (uint16_t)u[k];
+    found += __builtin_amdgcn_readlane(upto, 63);
+  }
+  wave_lds_sync();
+  return found;
+}
+
+// The particles [p0, p1) of a part (parts of equal size).
+__device__ __forceinline__ void part_range(int s0, int s1, int& p0, int& p1) {
+  const int per = (s1 - s0 + (int)gridDim.y - 1) / (int)gridDim.y;
+  p0 = s0 + (int)blockIdx.y * per;
+  p0 = p0 < s1 ? p0 : s1;
+  p1 = p0 + per < s1 ? p0 + per : s1;
+}
+
+// Forward: the neighbours' terms go to LDS, one row per quantity, and lane f
+// adds its sum's products in list order (the serial pass's operations in its
+// order, so that the features are bit-identical); the features are formed
+// from the sums by one thread per particle at the end.
+constexpr int kFwdRows = kNRad + kNMom + 4, kFwdPitch = 65, kFwdSums = kNRad + 2 * kNMom + 2;
+__global__ __launch_bounds__(kWaveThreads) void k_desc_fwd_wave(
+    const double* __restrict__ x, const double* __restrict__ y, const double* __restrict__ z,
+    const int32_t* __restrict__ cs, Grid g, TileList tl, float rc, DescIO io) {
+  __shared__ TileF32 t;
+  __shared__ uint16_t home[kBrickMax];
+  __shared__ uint16_t lists[kWaves][kWaveList];
+  __shared__ float terms[kWaves][kFwdRows * kFwdPitch];
+  __shared__ float sums[kWaveBatch][kFwdSums + 1];
+  const int brick = brick_of_block(g);
+  if (brick >= g.nbricks) return;
+  const int s0 = cs[brick * g.V], s1 = cs[(brick + 1) * g.V];
+  int p0, p1;
+  part_range(s0, s1, p0, p1);
+  if (p0 >= p1) return;
+  const int total = tile_tables_load(g, tl.tab + (int64_t)brick * kTabInts, t);
+  const int nt = total < TileF32::kCap ? total : TileF32::kCap;
+  double ox, oy, oz;
+  tile_centre(g, brick, ox, oy, oz);
+  tile_load_f32(g, x, y, z, total, ox, oy, oz, s0, t, home);  // ends with a barrier
+  const float rc2 = rc * rc, half_rev = 0.5f / rc;
+  const int lane = (int)threadIdx.x & 63, wave = (int)threadIdx.x >> 6;
+  uint16_t* const list = lists[wave];
+  float* const T = terms[wave];
+  // rows of T: radial Gaussians, monomials (row of the first, which is 1: g0),
+  // fc, w0, w1, g1.  Lane f: sum f of 16 (Gaussian x fc), 25 (monomial x w0; the
+  // first g0 x fc), 25 (monomial x w1; the first g1 x fc), w0 w0, w1 w1; lanes
+  // 0 - 3 also the four sums past the 64th
+  constexpr int kFc = kNRad + kNMom, kW0 = kFc + 1, kW1 = kFc + 2, kG1 = kFc + 3;
+  constexpr int kM1 = kNRad + kNMom, kD0 = kM1 + kNMom;  // first sums of eta = 2 and of diag
+  auto row_a = [&](int f) {
+    if (f < kM1) return f;
+    if (f == kM1) return kG1;
+    return f < kD0 ? f - kNMom : (f == kD0 ? kW0 : kW1);
+  };
+  auto row_b = [&](int f) {
+    if (f <= kNRad || f == kM1) return kFc;
+    return f < kM1 ? kW0 : (f < kD0 ? kW1 : row_a(f));
+  };
+  const float *a0 = T + row_a(lane) * kFwdPitch, *b0 = T + row_b(lane) * kFwdPitch;
+  const int f1 = 64 + (lane & 3);
+  const float *a1 = T + row_a(f1) * kFwdPitch, *b1 = T + row_b(f1) * kFwdPitch;
+  for (int base = p0; base < p1; base += kWaveBatch) {
+    const int nb = p1 - base < kWaveBatch ? p1 - base : kWaveBatch;
+    WaveList next = wave_list(tl, base + wave, wave < nb);
+    for (int i = wave; i < nb; i += kWaves) {
+      const int s = base + i, hs = s - s0 < kBrickMax ? home[s - s0] : TileF32::kDummy;
+      const float xi = t.px[hs], yi = t.py[hs], zi = t.pz[hs];
+      const WaveList now = next;
+      next = wave_list(tl, s + kWaves, i + kWaves < nb);
+      const int found = wave_in_range(t, tl, s, now, hs, rc2, nt, list);
+      float A0 = 0.0f, A1 = 0.0f;
+      for (int c0 = 0; c0 < found; c0 += 64) {
+        const int m = found - c0 < 64 ? found - c0 : 64;
+        if (lane < m) {
+          const int u = list[c0 + lane];
+          PairBasis p;
+          pair_basis(t.px[u] - xi, t.py[u] - yi, t.pz[u] - zi, half_rev, p);
+#pragma unroll
+          for (int k = 0; k < kNRad; ++k) T[k * kFwdPitch + lane] = p.eb[k];
+#pragma unroll
+          for (int k = 1; k < kNMom; ++k) T[(kNRad + k) * kFwdPitch + lane] = p.q[k];
+          T[kNRad * kFwdPitch + lane] = p.g0;
+          T[kG1 * kFwdPitch + lane] = p.g1;
+          T[kFc * kFwdPitch + lane] = p.fc;
+          T[kW0 * kFwdPitch + lane] = p.w0;
+          T[kW1 * kFwdPitch + lane] = p.w1;
+        }
+        wave_lds_sync();
+#pragma unroll 8
+        for (int j = 0; j < m; ++j) {
+          A0 = __builtin_fmaf(a0[j], b0[j], A0);
+          A1 = __builtin_fmaf(a1[j], b1[j], A1);
+        }
+        wave_lds_sync();
+      }
+      sums[i][lane] = A0;
+      if (lane < kFwdSums - 64) sums[i][64 + lane] = A1;
+    }
+    __syncthreads();
+    for (int i = threadIdx.x; i < nb; i += kWaveThreads) {
+      float G[kNRad], M[2][kNMom], diag[2];
+#pragma unroll
+      for (int k = 0; k < kNRad; ++k) G[k] = sums[i][k];
+#pragma unroll
+      for (int e = 0; e < 2; ++e) {
+#pragma unroll
+        for (int k = 0; k < kNMom; ++k) M[e][k] = sums[i][kNRad + e * kNMom + k];
+        diag[e] = sums[i][kNRad + 2 * kNMom + e];
+      }
+      desc_finish(io, base + i, G, M, diag);
+    }
+    __syncthreads();
+  }
+}
+
+// Backward: the coefficients of every particle once by one thread, then lane
+// k the gradient of neighbour k; own sums by a wave reduction (k_desc_bwd for
+// the reactions and the outputs).
+constexpr int kBwdBatch = 64;
+__global__ __launch_bounds__(kWaveThreads) void k_desc_bwd_wave(
+    const double* __restrict__ x, const double* __restrict__ y, const double* __restrict__ z,
+    const int32_t* __restrict__ cs, Grid g, TileList tl, float rc, DescIO io) {
+  __shared__ TileF32 t;
+  __shared__ uint16_t home[kBrickMax];
+  __shared__ uint16_t lists[kWaves][kWaveList];
+  __shared__ float coef[kBwdBatch][kNCoef + 1];
+  __shared__ unsigned long long acc[3][kTileMax];
+  const int brick = brick_of_block(g);
+  if (brick >= g.nbricks) return;
+  const int s0 = cs[brick * g.V], s1 = cs[(brick + 1) * g.V];
+  int p0, p1;
+  part_range(s0, s1, p0, p1);
+  if (p0 >= p1) return;
+  const int total = tile_tables_load(g, tl.tab + (int64_t)brick * kTabInts, t);
+  const int nt = total < TileF32::kCap ? total : TileF32::kCap;
+  for (int u = threadIdx.x; u < nt; u += kWaveThreads) {
+    acc[0][u] = 0;
+    acc[1][u] = 0;
+    acc[2][u] = 0;
+  }
+  double ox, oy, oz;
+  tile_centre(g, brick, ox, oy, oz);
+  tile_load_f32(g, x, y, z, total, ox, oy, oz, s0, t, home);  // ends with a barrier
+  const float rc2 = rc * rc;
+  const int lane = (int)threadIdx.x & 63, wave = (int)threadIdx.x >> 6;
+  uint16_t* const list = lists[wave];
+  for (int base = p0; base < p1; base += kBwdBatch) {
+    const int nb = p1 - base < kBwdBatch ? p1 - base : kBwdBatch;
+    for (int i = threadIdx.x; i < nb; i += kWaveThreads) {
+      const int64_t o = io.perm ? (int64_t)io.perm[base + i] : (int64_t)(base + i);
+      float K[kNCoef];
+      adjoint_coef(io.dEdG + o * kNFeat, io.mom + o * (2 * kNMom), K);
+#pragma unroll
+      for (int k = 0; k < kNCoef; ++k) coef[i][k] = K[k];
+    }
+    __syncthreads();
+    WaveList next = wave_list(tl, base + wave, wave < nb);
+    for (int i = wave; i < nb; i += kWaves) {
+      const int s = base + i, hs = s - s0 < kBrickMax ? home[s - s0] : TileF32::kDummy;
+      const WaveList now = next;
+      next = wave_list(tl, s + kWaves, i + kWaves < nb);
+      const int found = wave_in_range(t, tl, s, now, hs, rc2, nt, list);
+      float fx = 0.0f, fy = 0.0f, fz = 0.0f;
+      for (int k = lane; k < found; k += 64) {
+        float gx, gy, gz;
+        scatter_pair(t, g, io, acc, coef[i], hs, list[k], rc, gx, gy, gz);
+        fx += gx;
+        fy += gy;
+        fz += gz;
+      }
+      fx = wave_sum(fx);
+      fy = wave_sum(fy);
+      fz = wave_sum(fz);
+      if (lane == 0) {
+        const int64_t o = io.perm ? (int64_t)io.perm[s] : (int64_t)s;
+        unsafeAtomicAdd(&io.fx[o], fx);
+        unsafeAtomicAdd(&io.fy[o], fy);
+        unsafeAtomicAdd(&io.fz[o], fz);
+      }
+    }
+    __syncthreads();
+  }
+  add_reactions(t, g, io, acc, nt);
+}
+
+// Parts per brick, `most` at the most, of the kernels with a workgroup to a
+// CU (by their LDS): no more than the CUs hold at once, counted with the
+// empty blocks of tile_grid, since an XCD with more than its 32 would take a
+// second turn (wave forward pass of 27 bricks, 8 -> 9 parts: 38 -> 64 us).
+// Serial backward pass, one part -> these: 64 bricks (N = 32768) 84 -> 57 us,
+// 128 bricks (N = 64000) 90 -> 78 us.
+static unsigned lds_parts(const Grid& g, int most) {
+  const int p = 256 / (int)tile_grid(g);
+  return (unsigned)(p < 1 ? 1 : (p < most ? p : most));
 }
 
 hipError_t desc_forward(const double* x, const double* y, const double* z,
                         const int32_t* cell_start, const Grid& g, const TileList& tl, float rc,
-                        const int32_t* perm, float* G, float* mom, hipStream_t st, float* fx,
-                        float* fy, float* fz) {
+                        const int32_t* perm, int64_t n, float* G, float* mom, hipStream_t st,
+                        float* fx, float* fy, float* fz) {
   DescIO io{G, mom, nullptr, perm, fx, fy, fz};
-  // several parts share a brick's particles (small systems): one wave each and
-  // more, 256 threads for the tile load
-  const unsigned threads = tl.parts > 1 ? 256 : (tl.threads < 512 ? tl.threads : 512);
-  hipLaunchKernelGGL(k_desc_fwd, dim3(tile_grid(g), tl.parts), dim3(threads), 0, st, x, y,
+  if (tl.parts > 1 && n <= kWaveN) {
+    hipLaunchKernelGGL(k_desc_fwd_wave, dim3(tile_grid(g), lds_parts(g, tl.threads / kWaves)), dim3(kWaveThreads), 0, st, x,
+                       y, z, cell_start, g, tl, rc, io);
+    return hipGetLastError();
+  }
+  // Several parts share a brick's particles, 256 threads each for the tile
+  // load (a CU holds three): 128 bricks, 1 -> 4 parts: 65 -> 53 us; two parts
+  // of 216 bricks only load the tile twice (70 -> 72 us).
+  const unsigned parts = tl.parts > 2 ? tl.parts : 1;
+  const unsigned threads = parts > 1 ? 256 : (tl.threads < 512 ? tl.threads : 512);
+  hipLaunchKernelGGL(k_desc_fwd, dim3(tile_grid(g), parts), dim3(threads), 0, st, x, y,
                      z, cell_start, g, tl, rc, io);
   return hipGetLastError();
 }
@@ -641,16 +949,15 @@ hipError_t desc_backward(const double* x, const double* y, const double* z,
   DescIO io{nullptr, const_cast<float*>(mom), dEdG, perm, fx, fy, fz};
   if (!zeroed)
     hipLaunchKernelGGL(k_zero3, dim3((unsigned)div_up(n, 256)), dim3(256), 0, st, fx, fy, fz, n);
-  if (tl.parts > 1) {
-    const int per = (int)div_up(8 * (int64_t)tl.threads, tl.parts);
-    const unsigned threads = per < kBwdThreads ? (unsigned)((per + 63) & ~63) : kBwdThreads;
-    hipLaunchKernelGGL(k_desc_bwd<8>, dim3(tile_grid(g), tl.parts), dim3(threads), 0, st, x, y, z,
-                       cell_start, g, tl, rc, io);
+  if (tl.parts > 1 && n <= kWaveN) {
+    hipLaunchKernelGGL(k_desc_bwd_wave, dim3(tile_grid(g), lds_parts(g, tl.threads / kWaves)), dim3(kWaveThreads), 0, st, x,
+                       y, z, cell_start, g, tl, rc, io);
     return hipGetLastError();
   }
-  const unsigned threads = 2 * tl.threads < kBwdThreads ? 2 * tl.threads : kBwdThreads;
-  hipLaunchKernelGGL(k_desc_bwd<2>, dim3(tile_grid(g)), dim3(threads), 0, st, x, y,
-                     z, cell_start, g, tl, rc, io);
+  const unsigned parts = lds_parts(g, 8);
+  const unsigned per = (unsigned)div_up(2 * (int64_t)tl.threads, 64 * parts) * 64;
+  hipLaunchKernelGGL(k_desc_bwd, dim3(tile_grid(g), parts), dim3(per < kBwdThreads ? per : kBwdThreads),
+                     0, st, x, y, z, cell_start, g, tl, rc, io);
   return hipGetLastError();
 }
 

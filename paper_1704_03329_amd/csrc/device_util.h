@@ -168,6 +168,13 @@ __device__ __forceinline__ int wave_scan_i32(int v) {
   return v;
 }
 
+// The LDS writes of a wave's lanes are visible to its other lanes after this.
+__device__ __forceinline__ void wave_lds_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // Sum over a 256-thread block; the result is valid in thread 0.  Fixed
 // order (the wave sums above, then the four wave sums pairwise).
 __device__ __forceinline__ double block_sum256(double v, double* sh) {

@@ -162,8 +162,7 @@ struct TileList {
 // serial work sets the time; several workgroups then load the same tile and
 // share its particles (or, in the list build, its cells).  FP64 force pass,
 // one workgroup per brick against 8 parts of 8 lanes per particle: N = 1000
-// 18.0 -> 10.7 us, N = 4096 25.3 -> 11.2 us, N = 32768 23.8 -> 14.0 us;
-// descriptors and backward at N = 4096 59.5 -> 46.2 and 80.3 -> 34.8 us.  The
+// 18.0 -> 10.7 us, N = 4096 25.3 -> 11.2 us, N = 32768 23.8 -> 14.0 us.  The
 // second load costs a few us from the L2, so that systems with more bricks
 // than `want` keep one.
 inline int brick_parts(const Grid& g, int want, int most) {
@@ -349,7 +348,7 @@ hipError_t cna_signatures(const BondScan& q, int64_t n, const Grid& g, double rc
 // that a following desc_backward with zeroed = true needs no clearing launch.
 hipError_t desc_forward(const double* x, const double* y, const double* z,
                         const int32_t* cell_start, const Grid& g, const TileList& tl, float rc,
-                        const int32_t* perm, float* G, float* mom, hipStream_t st,
+                        const int32_t* perm, int64_t n, float* G, float* mom, hipStream_t st,
                         float* fx = nullptr, float* fy = nullptr, float* fz = nullptr);
 hipError_t desc_backward(const double* x, const double* y, const double* z,
                          const int32_t* cell_start, const Grid& g, const TileList& tl, float rc,

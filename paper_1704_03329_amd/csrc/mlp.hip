@@ -82,12 +82,6 @@ __device__ __forceinline__ float row16_sum(float v) {
   return v;
 }
 
-__device__ __forceinline__ void wave_lds_sync() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 // The raw features 8 grp .. 8 grp + 7 of row 16 tile + col (zero past the
 // 24 features); ok: the row exists.
 __device__ __forceinline__ void load_features(const MlpArgs& a, int64_t tile, int64_t ntiles,

@@ -70,3 +70,48 @@ def test_shared_bricks(name, precision):
         Fd = OD.forces_from_feature_grad(n, np.arange(n), table, grads, dEdG.double().cpu().numpy())
         got = torch.stack(f, 1).double().cpu().numpy()
         assert np.linalg.norm(got - Fd) <= 1e-4 * np.linalg.norm(Fd)
+
+
+# (sites per axis, spacing): a wave per particle in the descriptor passes
+WAVES = {
+    "up_to_130_in_range": ((10, 10, 12), 0.85),     # several rounds of 64 neighbours
+    "several_batches": ((23, 23, 23), 1.12),         # 27 bricks in 8 parts of about 56
+    "one_part_per_brick": ((23, 22, 27), 1.9),       # 150 bricks of about 90
+    "6_sites_per_part": ((9, 10, 9), 1.07),          # 8 bricks in 32 parts, the last ones empty
+}
+
+
+@pytest.mark.parametrize("name", list(WAVES))
+def test_wave_per_particle(name):
+    from paper_1704_03329_amd import potential as P
+    from paper_1704_03329_amd.sim import LJSim
+
+    gpu_device()
+    reps, a = WAVES[name]
+    g = [(np.arange(r) + 0.5) * a for r in reps]
+    zz, yy, xx = np.meshgrid(g[2], g[1], g[0], indexing="ij")
+    pos = mdinputs.perturb(np.stack([xx.ravel(), yy.ravel(), zz.ravel()], 1), 0.06 * a, 33)
+    box = np.array(reps, dtype=float) * a
+    n = pos.shape[0]
+    print(name, n, flush=True)
+    sim = LJSim(n, box, rc=2.5, skin=0.3, precision="fp32", max_nb=256)
+    x, y, z = split_dev(pos)
+    sim.build(x, y, z)
+    assert sim.check(raise_on_error=False)[0] == 0
+    G = torch.empty((n, 24), dtype=torch.float32, device="cuda")
+    mom = torch.empty((n, 50), dtype=torch.float32, device="cuda")
+    P.mdpl_desc_fwd(sim, x, y, z, G, mom)
+    # sampled rows against the oracle at the bars above; the forces of a
+    # gradient that only these rows have, with their neighbours' reactions
+    rows = np.arange(0, n, max(1, n // 400))
+    want, table, grads = OD.descriptors(pos, box, rows, with_grad=True)
+    got = G.double().cpu().numpy()[rows]
+    assert np.linalg.norm(got - want) <= 1e-5 * np.linalg.norm(want)
+    dEdG = torch.zeros((n, 24), dtype=torch.float32, device="cuda")
+    dEdG[torch.as_tensor(rows, device="cuda")] = torch.sin(
+        torch.arange(len(rows) * 24, device="cuda", dtype=torch.float32)).view(-1, 24)
+    f = [torch.empty(n, dtype=torch.float32, device="cuda") for _ in range(3)]
+    P.mdpl_desc_bwd(sim, x, y, z, dEdG, mom, *f)
+    Fd = OD.forces_from_feature_grad(n, rows, table, grads, dEdG.double().cpu().numpy()[rows])
+    got = torch.stack(f, 1).double().cpu().numpy()
+    assert np.linalg.norm(got - Fd) <= 1e-4 * np.linalg.norm(Fd)
