@@ -5,13 +5,15 @@
 //
 // One wave handles 16 atoms at a time.  v_mfma_f32_16x16x32_bf16 takes lane
 // l's A row l%16 and B column l%16 with K = 8(l/16)..+7 and returns rows
-// 4(l/16)..+3 of column l%16.  Activations change layout through a 4 KB LDS
-// scratch per wave.  The input gradient (EVAL) runs the transposed products
-// dh1 = dz2 W2 and dg = dz1 W1.  TRAIN also forms the loss
-// L = sum (y - t)^2 / B over a batch of B atoms and the weight gradients;
-// their 16x16x16 MFMAs take the accumulator fragments of the forward tiles
-// directly (rows = atoms are exactly the K index of those products).
-// Partials are written per wave and reduced in a fixed order.
+// 4(l/16)..+3 of column l%16.  The weights lie in LDS, W2 and W1 also
+// transposed for the input gradient (dh1 = dz2 W2 and dg = dz1 W1);
+// activations change layout through BF16 LDS rows of 72 halfwords, whose
+// 16-byte reads and 2-byte writes are free of bank conflicts.  Training also
+// forms the loss L = sum (y - t)^2 / B over a batch of B atoms and the weight
+// gradients, sums over the atoms: the workgroup's four waves leave the
+// operands of their 64 atoms in LDS with the atoms along K, and each wave
+// forms a quarter of every gradient.  Partials are written per workgroup and
+// reduced in a fixed order.
 #include <math.h>
 
 #include "device_util.h"
@@ -21,10 +23,14 @@
 namespace mdpl {
 
 typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8;
-typedef __attribute__((__vector_size__(4 * sizeof(short)))) short bf16x4;  // 16x16x16 operand bits
+typedef __attribute__((__vector_size__(2 * sizeof(__bf16)))) __bf16 bf16x2;
+typedef __attribute__((__vector_size__(2 * sizeof(float)))) float f32x2;
 typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4;
 typedef __attribute__((__vector_size__(4 * sizeof(unsigned)))) unsigned u32x4;
 typedef __attribute__((__vector_size__(2 * sizeof(unsigned)))) unsigned u32x2;
+// 16-byte loads of arrays that are only known to be aligned to their elements
+struct __attribute__((packed, aligned(4))) f32x4_a4 { f32x4 v; };
+struct __attribute__((packed, aligned(2))) u32x4_a2 { u32x4 v; };
 
 constexpr int kMlpThreads = 256;
 constexpr int kNIn = 24, kNPad = 32, kNH = 64;
@@ -39,30 +45,15 @@ __device__ __forceinline__ unsigned short f2bf(float f) {
 }
 __device__ __forceinline__ float bf2f(unsigned short h) { return __uint_as_float((unsigned)h << 16); }
 
-__device__ __forceinline__ bf16x8 pack8(const float v[8]) {
-  u32x4 w;
-#pragma unroll
-  for (int i = 0; i < 4; ++i) w[i] = (unsigned)f2bf(v[2 * i]) | ((unsigned)f2bf(v[2 * i + 1]) << 16);
-  return __builtin_bit_cast(bf16x8, w);
+// Two values to BF16, round to nearest even (v_cvt_pk_bf16_f32), a below b
+__device__ __forceinline__ unsigned pack2(float a, float b) {
+  return __builtin_bit_cast(unsigned, __builtin_convertvector((f32x2{a, b}), bf16x2));
 }
-__device__ __forceinline__ bf16x4 pack4(const float v[4]) {
-  bf16x4 w;
-#pragma unroll
-  for (int i = 0; i < 4; ++i) w[i] = (short)f2bf(v[i]);
-  return w;
+__device__ __forceinline__ u32x4 pack8(const float v[8]) {
+  return u32x4{pack2(v[0], v[1]), pack2(v[2], v[3]), pack2(v[4], v[5]), pack2(v[6], v[7])};
 }
-__device__ __forceinline__ bf16x8 load8(const unsigned short* p) {  // 8 consecutive bf16
-  u32x4 w;
-#pragma unroll
-  for (int i = 0; i < 4; ++i) w[i] = (unsigned)p[2 * i] | ((unsigned)p[2 * i + 1] << 16);
-  return __builtin_bit_cast(bf16x8, w);
-}
-__device__ __forceinline__ bf16x8 load8_strided(const unsigned short* p, int stride) {
-  u32x4 w;
-#pragma unroll
-  for (int i = 0; i < 4; ++i)
-    w[i] = (unsigned)p[(2 * i) * stride] | ((unsigned)p[(2 * i + 1) * stride] << 16);
-  return __builtin_bit_cast(bf16x8, w);
+__device__ __forceinline__ bf16x8 frag(const unsigned short* p) {  // 16-byte aligned LDS
+  return __builtin_bit_cast(bf16x8, *(const u32x4*)p);
 }
 
 // sigmoid with the hardware reciprocal (about 1 ulp; the network's BF16
@@ -88,350 +79,401 @@ __device__ __forceinline__ void load_features(const MlpArgs& a, int64_t tile, in
                                               int col, int grp, float g[8], bool& ok) {
   const int64_t ra = tile * 16 + col;
   ok = tile < ntiles && ra < a.n;
-  const int64_t ia = ok ? (a.index ? (int64_t)a.index[ra] : ra) : 0;
+  f32x4 lo = {0, 0, 0, 0}, hi = {0, 0, 0, 0};
+  if (ok && grp < 3) {
+    const int64_t ia = a.index ? (int64_t)a.index[ra] : ra;
+    const f32x4_a4* p = (const f32x4_a4*)(a.G + ia * kNIn + 8 * grp);
+    lo = p[0].v;
+    hi = p[1].v;
+  }
 #pragma unroll
-  for (int k = 0; k < 8; ++k) {
-    const int f = 8 * grp + k;
-    g[k] = (ok && f < kNIn) ? a.G[ia * kNIn + f] : 0.0f;
+  for (int k = 0; k < 4; ++k) {
+    g[k] = lo[k];
+    g[4 + k] = hi[k];
   }
 }
 
-template <bool TRAIN>
-__global__ __launch_bounds__(kMlpThreads) void k_mlp(MlpArgs a) {
-  __shared__ float scratch[kMlpThreads / 64][16][kNH + 1];
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  const int col = lane & 15, grp = lane >> 4;
-  float(*S)[kNH + 1] = scratch[wv];
-  const bool want_grad = TRAIN || a.dEdG != nullptr;
+// Rows of 64 (or, W1, 32) BF16 in LDS
+constexpr int kPitch = 72, kPitch1 = 40;
 
-  // weight fragments, held for the whole kernel
-  bf16x8 W1f[4], W2f[4][2], W2b[4][2], W1b[2][2];
-#pragma unroll
-  for (int nt = 0; nt < 4; ++nt) {
-    W1f[nt] = load8(a.w1 + (nt * 16 + col) * kNPad + 8 * grp);
-#pragma unroll
-    for (int kc = 0; kc < 2; ++kc) W2f[nt][kc] = load8(a.w2 + (nt * 16 + col) * kNH + kc * 32 + 8 * grp);
-  }
-  if (want_grad) {
-#pragma unroll
-    for (int nt = 0; nt < 4; ++nt)
-#pragma unroll
-      for (int kc = 0; kc < 2; ++kc)
-        W2b[nt][kc] = load8_strided(a.w2 + (kc * 32 + 8 * grp) * kNH + nt * 16 + col, kNH);
-#pragma unroll
-    for (int nt = 0; nt < 2; ++nt)
-#pragma unroll
-      for (int kc = 0; kc < 2; ++kc)
-        W1b[nt][kc] = load8_strided(a.w1 + (kc * 32 + 8 * grp) * kNPad + nt * 16 + col, kNPad);
-  }
-  float b1c[4], b2c[4], w3c[4];
-#pragma unroll
-  for (int nt = 0; nt < 4; ++nt) {
-    b1c[nt] = a.b1[nt * 16 + col];
-    b2c[nt] = a.b2[nt * 16 + col];
-    w3c[nt] = bf2f(a.w3[nt * 16 + col]);
-  }
-  const float b3 = a.b3[0];
-  // reciprocals of the feature scales this lane uses: its eight layer-1
-  // inputs (8 grp + k), and the features col and 16 + col of the gradients
-  float isd8[8], isd2[2];
-#pragma unroll
-  for (int k = 0; k < 8; ++k) {
-    const int f = 8 * grp + k;
-    isd8[k] = f < kNIn ? 1.0f / a.sd[f] : 0.0f;
-  }
-#pragma unroll
-  for (int j = 0; j < 2; ++j) {
-    const int f = j * 16 + col;
-    isd2[j] = f < kNIn ? 1.0f / a.sd[f] : 0.0f;
-  }
+// The weights of a workgroup: rows n (outputs), and transposed rows k.
+struct MlpLds {
+  unsigned short w1[kNH][kPitch1], w2[kNH][kPitch];
+  unsigned short w2t[kNH][kPitch], w1t[kNPad][kPitch];
+  unsigned short rows[kMlpThreads / 64][16][kPitch];  // a wave's activations, row-major
+};
 
-  // TRAIN accumulators
-  f32x4 gW2[4][4], gW1[4][2];
-  float gb1[4] = {0, 0, 0, 0}, gb2[4] = {0, 0, 0, 0}, gw3[4] = {0, 0, 0, 0};
-  float gb3 = 0.0f, loss = 0.0f;
-  if (TRAIN) {
+// Thread t loads 16 bytes of row t % 64 at a time (transposed writes by
+// consecutive lanes to consecutive halfwords).
+template <bool W1T>
+__device__ __forceinline__ void stage_weights(const MlpArgs& a, bool grad, MlpLds& m) {
+  const int n = threadIdx.x & 63, q = threadIdx.x >> 6;
+  const u32x4 v1 = ((const u32x4_a2*)(a.w1 + n * kNPad + 8 * q))->v;
+  u32x4 v2[2];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
+  for (int h = 0; h < 2; ++h) v2[h] = ((const u32x4_a2*)(a.w2 + n * kNH + 8 * (q + 4 * h)))->v;
+  *(u32x4*)&m.w1[n][8 * q] = v1;
 #pragma unroll
-      for (int j = 0; j < 4; ++j) gW2[i][j] = f32x4{0, 0, 0, 0};
-      gW1[i][0] = f32x4{0, 0, 0, 0};
-      gW1[i][1] = f32x4{0, 0, 0, 0};
+  for (int h = 0; h < 2; ++h) *(u32x4*)&m.w2[n][8 * (q + 4 * h)] = v2[h];
+  if (grad) {
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      if (W1T) m.w1t[8 * q + i][n] = (unsigned short)(v1[i / 2] >> (16 * (i & 1)));
+#pragma unroll
+      for (int h = 0; h < 2; ++h)
+        m.w2t[8 * (q + 4 * h) + i][n] = (unsigned short)(v2[h][i / 2] >> (16 * (i & 1)));
     }
   }
+  __syncthreads();
+}
 
+// Accumulator tile nt of a wave (rows 4 grp + r of column nt*16 + col) to its
+// BF16 rows; returns the four values packed in row order.
+__device__ __forceinline__ u32x2 put_tile(unsigned short (*S)[kPitch], int nt, int col, int grp,
+                                          const f32x4& v) {
+  const u32x2 p = {pack2(v[0], v[1]), pack2(v[2], v[3])};
+#pragma unroll
+  for (int r = 0; r < 4; ++r)
+    S[4 * grp + r][nt * 16 + col] = (unsigned short)(p[r >> 1] >> (16 * (r & 1)));
+  return p;
+}
+
+// What a lane keeps of the parameters: columns nt*16 + col.
+struct MlpCols {
+  float b1[4], b2[4], w3[4], b3;
+  float mu8[8], isd8[8];  // of its eight layer-1 inputs 8 grp + k
+};
+__device__ __forceinline__ MlpCols mlp_cols(const MlpArgs& a, int col, int grp) {
+  MlpCols c;
+#pragma unroll
+  for (int nt = 0; nt < 4; ++nt) {
+    c.b1[nt] = a.b1[nt * 16 + col];
+    c.b2[nt] = a.b2[nt * 16 + col];
+    c.w3[nt] = bf2f(a.w3[nt * 16 + col]);
+  }
+  c.b3 = a.b3[0];
+#pragma unroll
+  for (int k = 0; k < 8; ++k) {
+    const int f = 8 * grp + k < kNIn ? 8 * grp + k : 0;
+    c.mu8[k] = a.mu[f];
+    c.isd8[k] = 1.0f / a.sd[f];
+  }
+  return c;
+}
+
+// Layer 1 from the standardised features A1: h1 and the derivative of its
+// silu (d1), h1 to the wave's rows and, packed along the rows, to hp.
+__device__ __forceinline__ void layer1(const MlpLds& m, unsigned short (*S)[kPitch],
+                                       const MlpCols& c, int col, int grp, const u32x4& A1,
+                                       f32x4 (&d1)[4], u32x2 (&hp)[4]) {
+#pragma unroll
+  for (int nt = 0; nt < 4; ++nt) {
+    const f32x4 z = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+        __builtin_bit_cast(bf16x8, A1), frag(&m.w1[nt * 16 + col][8 * grp]), f32x4{0, 0, 0, 0}, 0, 0, 0);
+    f32x4 h;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const float zz = z[r] + c.b1[nt], sg = sigm(zz);
+      h[r] = zz * sg;
+      d1[nt][r] = sg * (1.0f + zz * (1.0f - sg));
+    }
+    hp[nt] = put_tile(S, nt, col, grp, h);
+  }
+}
+
+// acc[nt] = rows of S times W^T (W: 64 rows of pitch kPitch), NT column tiles
+template <int NT>
+__device__ __forceinline__ void mul64(unsigned short (*S)[kPitch], const unsigned short (*W)[kPitch],
+                                      int col, int grp, f32x4 (&acc)[NT]) {
+  const bf16x8 A0 = frag(&S[col][8 * grp]), A1 = frag(&S[col][32 + 8 * grp]);
+#pragma unroll
+  for (int nt = 0; nt < NT; ++nt) {
+    acc[nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A0, frag(&W[nt * 16 + col][8 * grp]),
+                                                      f32x4{0, 0, 0, 0}, 0, 0, 0);
+    acc[nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A1, frag(&W[nt * 16 + col][32 + 8 * grp]),
+                                                      acc[nt], 0, 0, 0);
+  }
+}
+
+// Layer 2 and the output y of rows 4 grp + r: z2 and its sigmoid.
+__device__ __forceinline__ void layer2(const MlpLds& m, unsigned short (*S)[kPitch],
+                                       const MlpCols& c, int col, int grp, f32x4 (&z2)[4],
+                                       f32x4 (&sg)[4], float (&y)[4]) {
+  mul64(S, m.w2, col, grp, z2);
+#pragma unroll
+  for (int r = 0; r < 4; ++r) y[r] = 0.0f;
+#pragma unroll
+  for (int nt = 0; nt < 4; ++nt)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      z2[nt][r] += c.b2[nt];
+      sg[nt][r] = sigm(z2[nt][r]);
+      y[r] += c.w3[nt] * z2[nt][r] * sg[nt][r];
+    }
+  // sum over the 16 columns held by the lanes of this group
+#pragma unroll
+  for (int r = 0; r < 4; ++r) y[r] = row16_sum(y[r]) + c.b3;
+}
+
+// Energies and, with dEdG, the input gradients.  A tile costs about 600 vector
+// instructions (64 of them exponentials and reciprocals) against 24 matrix
+// ones, so that vector issue bounds it: N = 262144 40 -> 32 us against
+// fragments of the transposed weights gathered from memory by 2-byte loads
+// and held in registers, and roundings and layout changes done value by value
+// in FP32; N = 4096, where the loads before the first tile counted, 10.3 ->
+// 5.4 us.
+__global__ __launch_bounds__(kMlpThreads) void k_mlp_eval(MlpArgs a) {
+  __shared__ __attribute__((aligned(16))) MlpLds m;
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  const int col = lane & 15, grp = lane >> 4;
+  unsigned short(*S)[kPitch] = m.rows[wv];
+  const bool want_grad = a.dEdG != nullptr;
   const int64_t ntiles = (a.n + 15) >> 4;
   const int64_t wave_id = (int64_t)blockIdx.x * (kMlpThreads / 64) + wv;
   const int64_t nwaves = (int64_t)gridDim.x * (kMlpThreads / 64);
-  // this lane's eight layer-1 features of a tile's row col, raw (the next
-  // tile's are loaded while the current one is computed)
-  float mu8[8];
-#pragma unroll
-  for (int k = 0; k < 8; ++k) {
-    const int f = 8 * grp + k;
-    mu8[k] = f < kNIn ? a.mu[f] : 0.0f;
-  }
   float gnext[8];
   bool oknext = false;
   load_features(a, wave_id, ntiles, col, grp, gnext, oknext);
+  const MlpCols c = mlp_cols(a, col, grp);
+  float sc[2];  // of the features col and 16 + col of the gradients
+#pragma unroll
+  for (int j = 0; j < 2; ++j) {
+    const int f = j * 16 + col;
+    sc[j] = f < kNIn ? a.e_sd * (1.0f / a.sd[f]) : 0.0f;
+  }
+  stage_weights<true>(a, want_grad, m);
   for (int64_t tile = wave_id; tile < ntiles; tile += nwaves) {
     const int64_t r0 = tile * 16;
-    // ---- layer 1: A fragment = standardised features of row r0 + col
+    // A fragment = standardised features of row r0 + col; the next tile's
+    // raw ones are loaded while this one is computed
     float gv[8];
 #pragma unroll
-    for (int k = 0; k < 8; ++k) gv[k] = oknext ? (gnext[k] - mu8[k]) * isd8[k] : 0.0f;
+    for (int k = 0; k < 8; ++k) gv[k] = oknext && grp < 3 ? (gnext[k] - c.mu8[k]) * c.isd8[k] : 0.0f;
     load_features(a, tile + nwaves, ntiles, col, grp, gnext, oknext);
     // keep those loads here, a tile ahead of their use
     asm volatile("" ::: "memory");
-    const bf16x8 A1 = pack8(gv);
-    f32x4 z1[4], h1[4];
+    f32x4 d1[4], z2[4], sg[4];
+    u32x2 hp[4];
+    float y[4];
+    layer1(m, S, c, col, grp, pack8(gv), d1, hp);
+    wave_lds_sync();
+    layer2(m, S, c, col, grp, z2, sg, y);
+    if (col == 0 && a.energy) {
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+        if (r0 + 4 * grp + r < a.n) a.energy[r0 + 4 * grp + r] = a.e_mean + a.e_sd * y[r];
+    }
+    wave_lds_sync();
+    if (!want_grad) continue;
+    // dz2 = w3 silu'(z2), dh1 = dz2 W2, dz1 = dh1 silu'(z1), dg = dz1 W1
 #pragma unroll
     for (int nt = 0; nt < 4; ++nt) {
-      z1[nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A1, W1f[nt], f32x4{0, 0, 0, 0}, 0, 0, 0);
+      f32x4 d;
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        z1[nt][r] += b1c[nt];
-        h1[nt][r] = z1[nt][r] * sigm(z1[nt][r]);
-        S[4 * grp + r][nt * 16 + col] = h1[nt][r];
-      }
+      for (int r = 0; r < 4; ++r)
+        d[r] = c.w3[nt] * sg[nt][r] * (1.0f + z2[nt][r] * (1.0f - sg[nt][r]));
+      put_tile(S, nt, col, grp, d);
     }
     wave_lds_sync();
-    bf16x8 A2[2];
-#pragma unroll
-    for (int kc = 0; kc < 2; ++kc) {
-      float v[8];
-#pragma unroll
-      for (int k = 0; k < 8; ++k) v[k] = S[col][kc * 32 + 8 * grp + k];
-      A2[kc] = pack8(v);
-    }
-    // ---- layer 2 and the output
-    f32x4 z2[4];
-    float ypart[4] = {0, 0, 0, 0};
-#pragma unroll
-    for (int nt = 0; nt < 4; ++nt) {
-      f32x4 acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A2[0], W2f[nt][0], f32x4{0, 0, 0, 0}, 0, 0, 0);
-      acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A2[1], W2f[nt][1], acc, 0, 0, 0);
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        acc[r] += b2c[nt];
-        ypart[r] += w3c[nt] * acc[r] * sigm(acc[r]);
-      }
-      z2[nt] = acc;
-    }
-    // sum over the 16 columns held by the lanes of this group
-#pragma unroll
-    for (int r = 0; r < 4; ++r) ypart[r] = row16_sum(ypart[r]) + b3;
-    // ---- upstream gradient dL/dy (TRAIN) or dy/dy = 1 (EVAL)
-    float dy[4];
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int64_t row = r0 + 4 * grp + r;
-      const bool ok = row < a.n;
-      if (TRAIN) {
-        const int64_t ir = ok ? (a.index ? (int64_t)a.index[row] : row) : 0;
-        // the target: the atom's energy standardised with the network's e_mean, e_sd
-        const float t = ok ? (float)((a.target[ir] - (double)a.e_mean) / (double)a.e_sd) : 0.0f;
-        const float diff = ok ? ypart[r] - t : 0.0f;
-        dy[r] = 2.0f * diff * a.inv_batch;
-        if (col == 0) loss += diff * diff * a.inv_batch;
-      } else {
-        dy[r] = ok ? 1.0f : 0.0f;
-        if (ok && col == 0 && a.energy) a.energy[row] = a.e_mean + a.e_sd * ypart[r];
-      }
-    }
-    if (!want_grad) {
-      wave_lds_sync();
-      continue;
-    }
-    // ---- dz2 = dy w3 silu'(z2)
-    f32x4 dz2[4];
-#pragma unroll
-    for (int nt = 0; nt < 4; ++nt)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const float zz = z2[nt][r];
-        const float sg = sigm(zz);
-        dz2[nt][r] = dy[r] * w3c[nt] * sg * (1.0f + zz * (1.0f - sg));
-      }
-    if (TRAIN) {
-      // weight gradients: dW2 = dz2^T h1, dw3 = sum dy h2, db2 = sum dz2, db3 = sum dy
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        float av[4];
-#pragma unroll
-        for (int r = 0; r < 4; ++r) av[r] = dz2[i][r];
-        const bf16x4 Ai = pack4(av);
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          float bv[4];
-#pragma unroll
-          for (int r = 0; r < 4; ++r) bv[r] = h1[j][r];
-          gW2[i][j] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(Ai, pack4(bv), gW2[i][j], 0, 0, 0);
-        }
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          gb2[i] += dz2[i][r];
-          const float zz = z2[i][r];
-          gw3[i] += dy[r] * zz * sigm(zz);
-        }
-      }
-      if (col == 0) gb3 += dy[0] + dy[1] + dy[2] + dy[3];
-    }
-    // ---- dh1 = dz2 W2 (A = dz2 rows, through LDS)
-    wave_lds_sync();
-#pragma unroll
-    for (int nt = 0; nt < 4; ++nt)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) S[4 * grp + r][nt * 16 + col] = dz2[nt][r];
-    wave_lds_sync();
-    bf16x8 D2[2];
-#pragma unroll
-    for (int kc = 0; kc < 2; ++kc) {
-      float v[8];
-#pragma unroll
-      for (int k = 0; k < 8; ++k) v[k] = S[col][kc * 32 + 8 * grp + k];
-      D2[kc] = pack8(v);
-    }
     f32x4 dz1[4];
+    mul64(S, m.w2t, col, grp, dz1);
+    wave_lds_sync();
 #pragma unroll
     for (int nt = 0; nt < 4; ++nt) {
-      f32x4 acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(D2[0], W2b[nt][0], f32x4{0, 0, 0, 0}, 0, 0, 0);
-      acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(D2[1], W2b[nt][1], acc, 0, 0, 0);
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const float zz = z1[nt][r];
-        const float sg = sigm(zz);
-        acc[r] *= sg * (1.0f + zz * (1.0f - sg));
-      }
-      dz1[nt] = acc;
+      for (int r = 0; r < 4; ++r) dz1[nt][r] *= d1[nt][r];
+      put_tile(S, nt, col, grp, dz1[nt]);
     }
-    if (TRAIN) {
-      // dW1 = dz1^T g, db1 = sum dz1; g in accumulator layout: rows 4 grp + r, column f
-      float gd[2][4];
-#pragma unroll
-      for (int j = 0; j < 2; ++j) {
-        const int f = j * 16 + col;
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const int64_t row = r0 + 4 * grp + r;
-          const bool ok = row < a.n && f < kNIn;
-          const int64_t ir = ok ? (a.index ? (int64_t)a.index[row] : row) : 0;
-          gd[j][r] = ok ? (a.G[ir * kNIn + f] - a.mu[f]) * isd2[j] : 0.0f;
-        }
-      }
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        float av[4];
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          av[r] = dz1[i][r];
-          gb1[i] += dz1[i][r];
-        }
-        const bf16x4 Ai = pack4(av);
-#pragma unroll
-        for (int j = 0; j < 2; ++j)
-          gW1[i][j] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(Ai, pack4(gd[j]), gW1[i][j], 0, 0, 0);
-      }
-      wave_lds_sync();
-      continue;
-    }
-    // ---- EVAL: dg = dz1 W1 (A = dz1 rows, through LDS)
     wave_lds_sync();
+    f32x4 dg[2];
+    mul64(S, m.w1t, col, grp, dg);
 #pragma unroll
-    for (int nt = 0; nt < 4; ++nt)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) S[4 * grp + r][nt * 16 + col] = dz1[nt][r];
-    wave_lds_sync();
-    bf16x8 D1[2];
-#pragma unroll
-    for (int kc = 0; kc < 2; ++kc) {
-      float v[8];
-#pragma unroll
-      for (int k = 0; k < 8; ++k) v[k] = S[col][kc * 32 + 8 * grp + k];
-      D1[kc] = pack8(v);
-    }
-#pragma unroll
-    for (int nt = 0; nt < 2; ++nt) {
-      f32x4 acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(D1[0], W1b[nt][0], f32x4{0, 0, 0, 0}, 0, 0, 0);
-      acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(D1[1], W1b[nt][1], acc, 0, 0, 0);
-      const int f = nt * 16 + col;
+    for (int j = 0; j < 2; ++j) {
+      const int f = j * 16 + col;
       if (f < kNIn) {
-        const float sc = a.e_sd * isd2[nt];
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
           const int64_t row = r0 + 4 * grp + r;
-          if (row < a.n) a.dEdG[row * kNIn + f] = acc[r] * sc;
+          if (row < a.n) a.dEdG[row * kNIn + f] = dg[j][r] * sc[j];
         }
       }
     }
     wave_lds_sync();
   }
+}
 
-  if (TRAIN) {
-    // the workgroup's waves leave their gradients in LDS and one partial per
-    // workgroup goes to memory, the waves added in order
-    __shared__ float wsum[kMlpThreads / 64][kNParam + 1];
-    float* __restrict__ P = wsum[wv];
-    // accumulator tile (i, j): lane holds rows (n) 4 grp + r of tile i, column j*16 + col
+// The four rows 4 grp .. 4 grp + 3 that the lane's wave computes of column n
+// of an operand, packed, to LDS rows along the atoms.
+typedef unsigned short MlpCross[kPitch];
+__device__ __forceinline__ void put_cross(MlpCross* X, int n, int wv, int grp, const u32x2& p) {
+  *(u32x2*)&X[n][16 * wv + 4 * grp] = p;
+}
+
+// Loss and weight gradients of a batch.  At batch 4096 (64 workgroups, one
+// tile per wave) latency bounds it: every load is issued before the first
+// use, an atom's target is standardised by one lane of a quad, and a wave
+// holds a quarter of the gradients (24 accumulators instead of 96 per lane,
+// and no sum over the waves): 14.7 -> 8.1 us.
+__global__ __launch_bounds__(kMlpThreads) void k_mlp_train(MlpArgs a) {
+  __shared__ __attribute__((aligned(16))) MlpLds m;
+  // operands of the weight gradients, column-major: 64 atoms along each row
+  __shared__ __attribute__((aligned(16))) MlpCross xh1[kNH], xdz2[kNH], xdz1[kNH], xg[kNPad];
+  constexpr int kWaves = kMlpThreads / 64, kVec = 3 * kNH + 2;
+  __shared__ float vec[kWaves][kVec];  // bias and w3 gradients, db3, loss
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  const int col = lane & 15, grp = lane >> 4;
+  unsigned short(*S)[kPitch] = m.rows[wv];
+  const int64_t ntiles = (a.n + 15) >> 4;
+  // a lane's features, and the target of row 4 grp + col % 4
+  float gnext[8];
+  bool oknext = false;
+  double tnext = 0.0;
+  auto load = [&](int64_t tile) {
+    load_features(a, tile, ntiles, col, grp, gnext, oknext);
+    const int64_t row = tile * 16 + 4 * grp + (col & 3);
+    if (row < a.n) tnext = a.target[a.index ? (int64_t)a.index[row] : row];
+  };
+  load((int64_t)blockIdx.x * kWaves + wv);
+  const MlpCols c = mlp_cols(a, col, grp);
+  stage_weights<false>(a, true, m);
+
+  f32x4 gW2[4], gW1[2];  // tile row wv of dW2 and dW1
+  float gb1[4] = {0, 0, 0, 0}, gb2[4] = {0, 0, 0, 0}, gw3[4] = {0, 0, 0, 0};
+  float gb3 = 0.0f, loss = 0.0f;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
+  for (int j = 0; j < 4; ++j) gW2[j] = f32x4{0, 0, 0, 0};
+  gW1[0] = gW1[1] = f32x4{0, 0, 0, 0};
+
+  for (int64_t base = (int64_t)blockIdx.x * kWaves; base < ntiles; base += (int64_t)gridDim.x * kWaves) {
+    const int64_t r0 = (base + wv) * 16;
+    float gv[8];
 #pragma unroll
-      for (int j = 0; j < 4; ++j)
+    for (int k = 0; k < 8; ++k) gv[k] = oknext && grp < 3 ? (gnext[k] - c.mu8[k]) * c.isd8[k] : 0.0f;
+    // the target: the atom's energy standardised with the network's e_mean, e_sd
+    const float tq = (float)((tnext - (double)a.e_mean) / (double)a.e_sd);
+    const float t[4] = {dpp_move<0x00>(tq), dpp_move<0x55>(tq), dpp_move<0xAA>(tq), dpp_move<0xFF>(tq)};
+    load(base + wv + (int64_t)gridDim.x * kWaves);
+    asm volatile("" ::: "memory");
+    const u32x4 A1 = pack8(gv);
 #pragma unroll
-        for (int r = 0; r < 4; ++r)
-          P[kOffW2 + (i * 16 + 4 * grp + r) * kNH + j * 16 + col] = gW2[i][j][r];
+    for (int k = 0; k < 8; ++k)
+      xg[8 * grp + k][16 * wv + col] = (unsigned short)(A1[k / 2] >> (16 * (k & 1)));
+    f32x4 d1[4], z2[4], sg[4];
+    u32x2 hp[4];
+    float y[4], dy[4];
+    layer1(m, S, c, col, grp, A1, d1, hp);
 #pragma unroll
-      for (int j = 0; j < 2; ++j)
+    for (int nt = 0; nt < 4; ++nt) put_cross(xh1, nt * 16 + col, wv, grp, hp[nt]);
+    wave_lds_sync();
+    layer2(m, S, c, col, grp, z2, sg, y);
+    wave_lds_sync();
 #pragma unroll
-        for (int r = 0; r < 4; ++r)
-          P[kOffW1 + (i * 16 + 4 * grp + r) * kNPad + j * 16 + col] = gW1[i][j][r];
+    for (int r = 0; r < 4; ++r) {
+      const float diff = r0 + 4 * grp + r < a.n ? y[r] - t[r] : 0.0f;
+      dy[r] = 2.0f * diff * a.inv_batch;
+      if (col == 0) loss += diff * diff * a.inv_batch;
     }
-    // column sums over the 4 lane groups
+    // dz2 = dy w3 silu'(z2), dw3 = sum dy h2, db2 = sum dz2, db3 = sum dy
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      float v1 = gb1[i], v2 = gb2[i], v3 = gw3[i];
-      v1 += __shfl_xor(v1, 16, 64);
-      v1 += __shfl_xor(v1, 32, 64);
-      v2 += __shfl_xor(v2, 16, 64);
-      v2 += __shfl_xor(v2, 32, 64);
-      v3 += __shfl_xor(v3, 16, 64);
-      v3 += __shfl_xor(v3, 32, 64);
-      if (grp == 0) {
-        P[kOffB1 + i * 16 + col] = v1;
-        P[kOffB2 + i * 16 + col] = v2;
-        P[kOffW3 + i * 16 + col] = v3;
+    for (int nt = 0; nt < 4; ++nt) {
+      f32x4 d;
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const float zz = z2[nt][r], s = sg[nt][r];
+        d[r] = dy[r] * c.w3[nt] * s * (1.0f + zz * (1.0f - s));
+        gb2[nt] += d[r];
+        gw3[nt] += dy[r] * zz * s;
       }
+      put_cross(xdz2, nt * 16 + col, wv, grp, put_tile(S, nt, col, grp, d));
     }
-    float t3 = gb3, tl = loss;
+    if (col == 0) gb3 += dy[0] + dy[1] + dy[2] + dy[3];
+    wave_lds_sync();
+    // dz1 = (dz2 W2) silu'(z1), db1 = sum dz1
+    f32x4 dz1[4];
+    mul64(S, m.w2t, col, grp, dz1);
 #pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-      t3 += __shfl_xor(t3, off, 64);
-      tl += __shfl_xor(tl, off, 64);
-    }
-    if (lane == 0) {
-      P[kOffB3] = t3;
-      P[kNParam] = tl;
+    for (int nt = 0; nt < 4; ++nt) {
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        dz1[nt][r] *= d1[nt][r];
+        gb1[nt] += dz1[nt][r];
+      }
+      put_cross(xdz1, nt * 16 + col, wv, grp,
+                u32x2{pack2(dz1[nt][0], dz1[nt][1]), pack2(dz1[nt][2], dz1[nt][3])});
     }
     __syncthreads();
-    float* __restrict__ out = a.partial + (int64_t)blockIdx.x * (kNParam + 1);
-    for (int k = threadIdx.x; k <= kNParam; k += kMlpThreads) {
-      float s = wsum[0][k];
+    // dW2 = dz2^T h1, dW1 = dz1^T g over the workgroup's 64 atoms
 #pragma unroll
-      for (int w = 1; w < kMlpThreads / 64; ++w) s += wsum[w][k];
-      out[k] = s;
+    for (int kc = 0; kc < 2; ++kc) {
+      const int o = kc * 32 + 8 * grp;
+      const bf16x8 A2 = frag(&xdz2[wv * 16 + col][o]), Ag = frag(&xdz1[wv * 16 + col][o]);
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+        gW2[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A2, frag(&xh1[j * 16 + col][o]), gW2[j], 0, 0, 0);
+#pragma unroll
+      for (int j = 0; j < 2; ++j)
+        gW1[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(Ag, frag(&xg[j * 16 + col][o]), gW1[j], 0, 0, 0);
     }
+    __syncthreads();
+  }
+
+  float* __restrict__ out = a.partial + (int64_t)blockIdx.x * (kNParam + 1);
+  // accumulator tile (wv, j): rows 4 grp + r of column j*16 + col
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    const int n = wv * 16 + 4 * grp + r;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) out[kOffW2 + n * kNH + j * 16 + col] = gW2[j][r];
+#pragma unroll
+    for (int j = 0; j < 2; ++j) out[kOffW1 + n * kNPad + j * 16 + col] = gW1[j][r];
+  }
+  // column sums over the 4 lane groups, then the waves in order
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    float v1 = gb1[i], v2 = gb2[i], v3 = gw3[i];
+    v1 += __shfl_xor(v1, 16, 64);
+    v1 += __shfl_xor(v1, 32, 64);
+    v2 += __shfl_xor(v2, 16, 64);
+    v2 += __shfl_xor(v2, 32, 64);
+    v3 += __shfl_xor(v3, 16, 64);
+    v3 += __shfl_xor(v3, 32, 64);
+    if (grp == 0) {
+      vec[wv][i * 16 + col] = v1;
+      vec[wv][kNH + i * 16 + col] = v2;
+      vec[wv][2 * kNH + i * 16 + col] = v3;
+    }
+  }
+  // db3 and the loss lie in lanes 0, 16, 32 and 48
+  gb3 += __shfl_xor(gb3, 16, 64);
+  gb3 += __shfl_xor(gb3, 32, 64);
+  loss += __shfl_xor(loss, 16, 64);
+  loss += __shfl_xor(loss, 32, 64);
+  if (lane == 0) {
+    vec[wv][3 * kNH] = gb3;
+    vec[wv][3 * kNH + 1] = loss;
+  }
+  __syncthreads();
+  if (threadIdx.x < kVec) {
+    const int k = threadIdx.x;
+    float s = vec[0][k];
+#pragma unroll
+    for (int w = 1; w < kWaves; ++w) s += vec[w][k];
+    const int at = k < kNH ? kOffB1 + k
+                           : (k < 2 * kNH ? kOffB2 + k - kNH
+                                          : (k < 3 * kNH ? kOffW3 + k - 2 * kNH : kOffB3 + k - 3 * kNH));
+    out[at] = s;
   }
 }
 
 hipError_t mlp_eval(const MlpArgs& a, hipStream_t st) {
-  // two waves per SIMD that each take many tiles: the weight fragments a
-  // wave loads first are then reused over ~8 tiles at N = 262,144 (2048
-  // blocks, two tiles per wave: 61 us; 1024: 48; 512: 43)
+  // two waves per SIMD that each take many tiles, so that the weights a
+  // workgroup stages first serve ~32 tiles at N = 262144 (512 blocks 32 us,
+  // 1024 with room for four waves per SIMD 34 us)
   int64_t tiles = (a.n + 15) >> 4;
   int64_t blocks = (tiles + 3) / 4;
   if (blocks > 512) blocks = 512;
   if (blocks < 1) blocks = 1;
-  hipLaunchKernelGGL(k_mlp<false>, dim3((unsigned)blocks), dim3(kMlpThreads), 0, st, a);
+  hipLaunchKernelGGL(k_mlp_eval, dim3((unsigned)blocks), dim3(kMlpThreads), 0, st, a);
   return hipGetLastError();
 }
 
@@ -446,7 +488,7 @@ int mlp_train_blocks(int64_t n) {
 int mlp_train_waves(int64_t n) { return mlp_train_blocks(n) * (kMlpThreads / 64); }
 
 hipError_t mlp_train_grad(const MlpArgs& a, hipStream_t st) {
-  hipLaunchKernelGGL(k_mlp<true>, dim3((unsigned)mlp_train_blocks(a.n)), dim3(kMlpThreads), 0, st,
+  hipLaunchKernelGGL(k_mlp_train, dim3((unsigned)mlp_train_blocks(a.n)), dim3(kMlpThreads), 0, st,
                      a);
   return hipGetLastError();
 }

@@ -26,7 +26,7 @@ struct MlpArgs {
   float* energy;             // EVAL: E per row (nullable)
   float* dEdG;               // EVAL: [row][24] (nullable)
   const double* target;      // TRAIN: per-atom energies (indexed like G), standardised in the kernel
-  float* partial;            // TRAIN: per-wave [kNParam + 1] (gradient, loss)
+  float* partial;            // TRAIN: per workgroup [kNParam + 1] (gradient, loss)
   float inv_batch;           // TRAIN: 1 / B
 };
 

@@ -107,6 +107,41 @@ def test_mlp_forward_and_input_grad_match_oracle(config):
     assert _rel(e.cpu().numpy() - m.e_mean, re - m.e_mean) <= 5e-2
 
 
+@pytest.mark.parametrize("rows", [1, 15, 16, 17, 63, 64, 65, 32768 + 21])
+def test_mlp_rows_over_sizes_and_alignment(rows):
+    """One tile of 16 rows with and without a remainder, one workgroup and
+    past it, more tiles than all waves take at once; features and weights
+    only aligned to their elements.  A row's outputs follow from the row
+    alone, whatever is evaluated with it: equal to the bit; the bar against
+    the oracle is that of the test above."""
+    print(f"network over {rows} rows", flush=True)
+    rng = np.random.default_rng(rows)
+    G = torch.from_numpy(rng.normal(size=(rows, 24)).astype(np.float32)).cuda()
+    wide = torch.from_numpy(rng.normal(size=(400, 24)).astype(np.float32)).cuda()
+    m = _model(wide, torch.from_numpy(np.linspace(-6, -3, 400)).cuda())
+    e, dG = m.energy(G, with_grad=True)
+    only, _ = m.energy(G)
+    assert torch.equal(only, e)
+    some = np.unique(np.linspace(0, rows - 1, min(rows, 500)).astype(int))
+    re, rdG = _oracle_eval(m, G.double().cpu().numpy()[some])
+    assert _rel(e.cpu().numpy()[some], re) <= 2e-2
+    assert _rel(dG.cpu().numpy()[some], rdG) <= 2e-2
+    # the last 16-row tile's rows one after the other, from the front
+    last = torch.cat([G[16 * ((rows - 1) // 16):], wide[:3]])
+    e2, dG2 = m.energy(last, with_grad=True)
+    k = last.shape[0] - 3
+    assert torch.equal(e2[:k], e[-k:]) and torch.equal(dG2[:k], dG[-k:])
+    shifted = torch.empty(G.numel() + 1, dtype=torch.float32, device="cuda")[1:].view(rows, 24)
+    shifted.copy_(G)
+    for name in ("w1", "w2", "w3"):
+        w = getattr(m, name)
+        odd = torch.empty(w.numel() + 1, dtype=w.dtype, device="cuda")[1:]
+        odd.copy_(w)
+        setattr(m, name, odd)
+    e3, dG3 = m.energy(shifted, with_grad=True)
+    assert torch.equal(e3, e) and torch.equal(dG3, dG)
+
+
 def test_mlp_forces_match_oracle(config):
     from paper_1704_03329_amd.sim import soa
 
