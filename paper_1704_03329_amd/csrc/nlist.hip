@@ -8,15 +8,19 @@
 // with floating-point contraction off, on the caller's FP64 values, so the
 // list is bit-identical to the all-pairs definition.
 //
-// The builder: one workgroup per brick stages its tile (stored positions,
-//    no images) in LDS, one wave per home cell tests the 27 tile cells of its
-//    stencil (a full list: each cell's particles of the lower half along x
-//    first, so that a particle skips the half of the next or previous cell
-//    along x that lies beyond the list radius, 5/6 of each stencil row); entries are 16-bit tile byte offsets (16 x slot), column-major, so the force
-//    pass reads one coalesced word per four neighbours.  A half list (each
-//    pair once, Newton's third law) keeps j in the list of i only if j's tile
-//    index is larger (tile.h): four of the nine stencil rows whole, and the
-//    row of i's cell from i on.
+// The builder: one workgroup per brick (several for small systems) stages its
+//    tile in LDS and tests the 27 tile cells of each particle's stencil (a
+//    full list: each cell's particles of the lower half along x first, so
+//    that a particle skips the half of the next or previous cell along x that
+//    lies beyond the list radius, 5/6 of each stencil row); entries are
+//    16-bit tile byte offsets, column-major, so the force pass reads one
+//    coalesced word per four neighbours.  Large systems: a lane per particle,
+//    distances on the matrix cores (lane_row); small or sparse ones and half
+//    lists: a wave per home cell or less (scan_range, row_bits), and the
+//    lists are the same, entry for entry.  A half list (each pair once,
+//    Newton's third law) keeps j in the list of i only if j's tile index is
+//    larger (tile.h): four of the nine stencil rows whole, and the row of i's
+//    cell from i on.
 #include <math.h>
 
 #include <type_traits>
@@ -49,7 +53,9 @@ namespace mdpl {
 // conditional minimum image on the stored FP64 positions).  The list is
 // therefore bit-identical to the all-pairs definition.
 constexpr float kFarF = 1e30f;  // dummy slot: its d2f overflows to +inf
+constexpr float kFarLane = 1e15f;  // out of reach, but its square is finite
 constexpr int kBuildWant = 512;  // workgroups of a build that shares its bricks
+constexpr int kLaneThreads = 512;
 
 struct RowScan {
   float xi, yi, zi;            // FP32 tile coordinates of the particle
@@ -203,8 +209,261 @@ __device__ __forceinline__ void row_store(const RowBits& bits, int ub, uint32_t 
   }
 }
 
+// A lane per particle (large systems).  What bounds it is vector issue and
+// the latency of the screen's chain from table to decision, about 6500 vector
+// instructions for the ~420 candidates and 80 entries of 64 particles: the
+// screen costs 2.6 of them per candidate (four rank-1 products on the matrix
+// cores, against 12 in scan_range), and the entries are appended four
+// positions at a time without a loop (a loop over the set bits of each word,
+// whose trips follow the fullest of 64 lanes, took half of the time).
+// N = 10^6 408 -> 280 us, 262144 135 -> 101 us, 125000 (list radius 3.3)
+// 133 -> 83 us against one wave per home cell.
+//
+// A list is in the order in which the
+// cell kernel's lanes find its entries: of each row's candidates i = 0, 1, ...
+// in blocks of 4 K, K = 64 / (particles of the cell), first those with
+// i % K = 0 of a block, then those with i % K = 1, and so on.  The tables give
+// for K <= kLaneK the candidate at position p of that order, as list entry
+// and, for every fourth position, as byte offset into the 4-byte tile arrays
+// (the three that follow lie K apart each), and the positions that exist in
+// an incomplete last block of `rem` candidates.
+constexpr int kLaneK = 8, kLaneRow = 256;  // largest K; candidates of a row
+struct LaneTables {
+  uint16_t pos[kLaneK][kLaneRow];
+  uint16_t group[kLaneK][kLaneRow / 4];
+  uint32_t valid[kLaneK][4 * kLaneK];
+};
+constexpr LaneTables lane_tables() {
+  LaneTables t{};
+  for (int K = 1; K <= kLaneK; ++K) {
+    for (int p = 0; p < kLaneRow; ++p) {
+      const int i = p / (4 * K) * (4 * K) + p % 4 * K + p / 4 % K;
+      t.pos[K - 1][p] = (uint16_t)(i << kFullShift);
+      if (p % 4 == 0) t.group[K - 1][p / 4] = (uint16_t)(4 * i);
+    }
+    for (int rem = 0; rem < 4 * K; ++rem)
+      for (int p = 0; p < 4 * K; ++p)
+        if (p % 4 * K + p / 4 < rem) t.valid[K - 1][rem] |= 1u << p;
+  }
+  return t;
+}
+__device__ const LaneTables kLaneTables = lane_tables();
+
+__device__ __forceinline__ int wave_max_i32(int v) {
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) {
+    const int o = __shfl_xor(v, off, 64);
+    v = o > v ? o : v;
+  }
+  return v;
+}
+
+// a / b for 0 <= a <= 2 kLaneRow, 1 <= b <= 4 kLaneK from m = 65536 / b + 1
+__device__ __forceinline__ int div_small(int a, int m) { return (int)(__umul24(a, m) >> 16); }
+
+// A list as it grows: its newest entries, up to three, in a 64-bit word that
+// is stored when it is full.  Four positions are appended at a time, without
+// branches: their accepted entries are moved together by byte permutations
+// from a table, shifted behind those held, and what does not fit starts the
+// next word.
+struct Compress {
+  uint2 sel[16];  // per nibble of decisions: selectors of entries 0, 1 and 2, 3
+};
+constexpr Compress compress_table() {
+  Compress t{};
+  for (unsigned nib = 0; nib < 16; ++nib) {
+    uint32_t sel[2] = {0x0c0c0c0cu, 0x0c0c0c0cu};  // zero bytes
+    for (unsigned j = 0, m = 0; j < 4; ++j)
+      if (nib >> j & 1) {
+        sel[m / 2] = m % 2 ? (sel[m / 2] & 0xffffu) | (0x0100u + 0x0202u * j) << 16
+                           : (sel[m / 2] & 0xffff0000u) | (0x0100u + 0x0202u * j);
+        ++m;
+      }
+    t.sel[nib].x = sel[0];
+    t.sel[nib].y = sel[1];
+  }
+  return t;
+}
+__device__ const Compress kCompress = compress_table();
+
+// OFF: unsigned of the width that the list's byte offsets need.
+template <typename OFF>
+struct ListOut {
+  uint64_t acc;
+  uint32_t held;      // entries in acc
+  OFF at;             // where the next word goes
+  OFF pitch, room;    // bytes between words; those of all words of all lists
+  char* list;         // of the first slot
+  // e01, e23: entries of the four positions, 16 bits each
+  __device__ __forceinline__ void push4(uint32_t nib, uint2 sel, uint32_t e01, uint32_t e23) {
+    const uint64_t c = (uint64_t)__builtin_amdgcn_perm(e23, e01, sel.y) << 32 |
+                       __builtin_amdgcn_perm(e23, e01, sel.x);
+    const uint32_t sh = held << 4;
+    acc |= c << sh;
+    const uint64_t rest = (c >> (48 - sh)) >> 16;
+    const uint32_t sum = held + __popc(nib);
+    const bool full = sum > 3;
+    if (full && at < room) *(uint64_t*)(list + at) = acc;
+    at += full ? pitch : 0;
+    acc = full ? rest : acc;
+    held = sum & 3;
+  }
+  // Pads the last word; returns the entries found.  `first`: where the list
+  // begins; a list cut at its capacity is padded there.
+  __device__ __forceinline__ int finish(OFF first, int max_nb, uint32_t pad) {
+    const int m = 4 * (int)((double)(at - first) / (double)pitch + 0.5) + (int)held;
+    if (held && at < room)
+      *(uint64_t*)(list + at) = acc | (0x0001000100010001ull * pad) << (16 * held);
+    if (m > max_nb && (max_nb & 3)) {
+      uint16_t* last = (uint16_t*)(list + first + (OFF)(max_nb >> 2) * pitch);
+      for (int k = max_nb & 3; k < 4; ++k) last[k] = (uint16_t)pad;
+    }
+    return m;
+  }
+};
+
+// The particle of a lane for the matrix cores: e = |x_i - x_j|^2 - r^2 of four
+// particles and four candidates is (|x_i|^2 - r^2) + 1 |x_j|^2 - 2 x_i x_j -
+// 2 y_i y_j - 2 z_i z_j, a start value and four rank-1 products.  In
+// v_mfma_f32_4x4x1 every quad of lanes forms such a 4 x 4 block: lane l of
+// the quad holds candidate l of the left operand and particle l of the right
+// one and receives its own particle's four results.
+typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4;
+struct LanePoint {
+  float ax, ay, az;  // -2 x_i
+  f32x4 c;           // |x_i|^2 - r^2, four times
+  int self, slot, K;
+};
+// The definition's test of slot i and the particle at tile index u.
+template <typename TS>
+__device__ __forceinline__ bool exact_pair(const TS& t, const Grid& g, const double* __restrict__ x,
+                                        const double* __restrict__ y,
+                                        const double* __restrict__ z, int i, int u, double r2) {
+  const int cell = t.cell[u];
+  const int j = t.src[cell] + (u - t.prefix[cell]);
+  return exact_d2(x[i], y[i], z[i], x[j], y[j], z[j], g.box[0], g.box[1], g.box[2],
+                  0.5 * g.box[0], 0.5 * g.box[1], 0.5 * g.box[2]) < r2;
+}
+
+// One stencil row of n candidates from tile index ub on against the lane's
+// particle, appended to its list (live: 0 in lanes that only hold candidates
+// for their quad).  The lanes of a quad have particles of one cell, and of
+// one half of it, so that ub, n and K agree.  K4 = 4 K, m4K and mK: the
+// divisors of div_small for 4 K and K; selfrow: the row holds the particle
+// itself.  The decisions of 32 positions are formed first, a bit each, then
+// the accepted ones are appended.  The exact test decides inside the guard
+// band, as in scan_range; the band is wider (build_tile_nlist).  Positions
+// past the row read the tile's arrays (or what follows them in LDS) and are
+// masked out.
+template <typename TS, typename OFF>
+__device__ __forceinline__ void lane_row(const TS& t, const LaneTables& tab, const Compress& pack,
+                                         const Grid& g, const double* __restrict__ x,
+                                         const double* __restrict__ y,
+                                         const double* __restrict__ z, double r2, int ub, int n,
+                                         const LanePoint& pt, float guard, int mK, int m4K,
+                                         bool selfrow, uint32_t live, ListOut<OFF>& out) {
+  const int K = pt.K, k4 = 4 * K;
+  const int nfull = div_small(n, m4K) * k4, rem = n - nfull;
+  const uint32_t part = tab.valid[K - 1][rem];
+  const int end = nfull + 4 * (rem < K ? rem : K);  // positions to look at
+  int pself = -1;
+  if (selfrow) {
+    const int i = pt.self - ub, b = div_small(i, mK);  // i = b K + k
+    pself = (b >> 2) * k4 + 4 * (i - b * K) + (b & 3);
+  }
+  const uint16_t* const pos = tab.pos[K - 1];
+  const uint32_t mine = 4 * ub + (threadIdx.x & 3) * k4;  // the lane's candidate of a group
+  for (int c0 = 0; __any(c0 < end); c0 += 32) {
+    const uint4 grp = *(const uint4*)&tab.group[K - 1][c0 / 4];
+    const uint32_t gw[4] = {grp.x, grp.y, grp.z, grp.w};
+    uint32_t word = 0;
+    float near[4];
+    // 16 positions at a time, so that loads and products overlap
+#pragma unroll
+    for (int h = 1; h >= 0; --h) {
+      near[2 * h] = near[2 * h + 1] = 3e38f;
+      if (h == 0 || __any(c0 + 16 < end)) {
+        float x[4], y[4], z[4], sq[4];
+        f32x4 e[4];
+#pragma unroll
+        for (int b = 0; b < 4; ++b) {
+          const uint32_t w = gw[2 * h + b / 2], off = mine + (b & 1 ? w >> 16 : w & 0xffffu);
+          x[b] = *(const float*)((const char*)t.x + off);
+          y[b] = *(const float*)((const char*)t.y + off);
+          z[b] = *(const float*)((const char*)t.z + off);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int b = 0; b < 4; ++b) {
+          sq[b] = __builtin_fmaf(z[b], z[b], __builtin_fmaf(y[b], y[b], x[b] * x[b]));
+          e[b] = __builtin_amdgcn_mfma_f32_4x4x1f32(x[b], pt.ax, pt.c, 0, 0, 0);
+        }
+#pragma unroll
+        for (int b = 0; b < 4; ++b) e[b] = __builtin_amdgcn_mfma_f32_4x4x1f32(y[b], pt.ay, e[b], 0, 0, 0);
+#pragma unroll
+        for (int b = 0; b < 4; ++b) e[b] = __builtin_amdgcn_mfma_f32_4x4x1f32(z[b], pt.az, e[b], 0, 0, 0);
+#pragma unroll
+        for (int b = 0; b < 4; ++b) e[b] = __builtin_amdgcn_mfma_f32_4x4x1f32(sq[b], 1.0f, e[b], 0, 0, 0);
+#pragma unroll
+        for (int b = 3; b >= 0; --b) {
+#pragma unroll
+          for (int j = 3; j >= 0; --j)
+            word = __builtin_amdgcn_alignbit(word, __float_as_uint(e[b][j]), 31);
+          float& n = near[2 * h + b / 2];
+          n = fminf(fminf(n, __builtin_fabsf(e[b][0])), __builtin_fabsf(e[b][1]));
+          n = fminf(fminf(n, __builtin_fabsf(e[b][2])), __builtin_fabsf(e[b][3]));
+        }
+      }
+    }
+    const int d = nfull - c0;  // positions of whole blocks in this word
+    uint32_t valid = ~0u;
+    if (d < 32) valid = d >= 0 ? ((1u << d) - 1u) | part << d : (d > -32 ? part >> -d : 0u);
+    valid &= live;
+    if (fminf(fminf(near[0], near[1]), fminf(near[2], near[3])) <= guard) {
+      // the definition decides those inside the guard band
+      uint32_t v = 0;
+#pragma unroll
+      for (int h = 0; h < 4; ++h) v |= near[h] <= guard ? 0xffu << (8 * h) : 0u;
+      for (v &= valid; v; v &= v - 1) {
+        const int b = __builtin_ctz(v);
+        const int u = ub + (pos[c0 + b] >> kFullShift);
+        const float dx = t.x[pt.self] - t.x[u], dy = t.y[pt.self] - t.y[u],
+                    dz = t.z[pt.self] - t.z[u];
+        const float e = __builtin_fmaf(dz, dz, __builtin_fmaf(dy, dy, __builtin_fmaf(dx, dx, -(float)r2)));
+        if (!(__builtin_fabsf(e) <= guard + guard)) continue;
+        const bool in = exact_pair(t, g, x, y, z, pt.slot, u, r2);
+        word = (word & ~(1u << b)) | (in ? 1u << b : 0u);
+      }
+    }
+    word &= valid;
+    const int ps = pself - c0;
+    if (ps >= 0 && ps < 32) word &= ~(1u << ps);
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      if (!__any(word & (0xffffu << (16 * h)))) continue;
+      uint32_t nib[4];
+      uint2 sel[4];
+#pragma unroll
+      for (int b = 0; b < 4; ++b) {
+        nib[b] = (word >> (16 * h + 4 * b)) & 15u;
+        sel[b] = pack.sel[nib[b]];
+      }
+#pragma unroll
+      for (int b = 0; b < 4; ++b) {
+        // entries are byte offsets into the tile arrays, as the table's
+        const uint32_t w = gw[2 * h + b / 2], off = 4 * ub + (b & 1 ? w >> 16 : w & 0xffffu);
+        const uint32_t two = off << 16 | off;
+        out.push4(nib[b], sel[b], two + ((uint32_t)k4 << 16), two + ((uint32_t)(3 * k4) << 16 | 2 * k4));
+      }
+    }
+  }
+}
+
 // One wave per home cell (up to 16 per workgroup); at most 64 VGPRs so that
 // two 1024-thread workgroups share a CU.  TS: the tile (full or half list).
+//
+// LANES: a lane per particle (lane_row) in every brick whose cells and rows
+// the tables cover, else as without.
 //
 // RW > 1 (small systems, full lists): blockIdx.y is the workgroup's part of
 // the brick, `cells` home cells, and RW waves share a cell, each taking 9/RW
@@ -214,8 +473,9 @@ __device__ __forceinline__ void row_store(const RowBits& bits, int ub, uint32_t 
 // wave.  One wave's scan of all nine rows, a serial chain, is what such
 // builds wait for: N = 1000 118 -> 22 us, N = 4096 73 -> 18 us, N = 32768
 // 82 -> 42 us.
-template <typename TS, bool HALF, bool A24, int RW>
-__global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(RW == 9 ? 4 : 8))) void
+template <typename TS, bool HALF, bool A24, int RW, bool LANES>
+__global__ __launch_bounds__(LANES ? kLaneThreads : 1024)
+__attribute__((amdgpu_waves_per_eu(RW == 9 ? 4 : (LANES ? 6 : 8)))) void
 k_build_tile_nlist(
     const double* __restrict__ x, const double* __restrict__ y, const double* __restrict__ z,
     const int32_t* __restrict__ cs, Grid g, double r2,
@@ -254,6 +514,15 @@ k_build_tile_nlist(
   const double ox = (double)(bx * g.B[0] - 1) * (Lx / g.nc[0]);
   const double oy = (double)(by * g.B[1] - 1) * (Ly / g.nc[1]);
   const double oz = (double)(bz * g.B[2] - 1) * (Lz / g.nc[2]);
+  // with a lane per particle the tile's centre: the screen forms |x|^2
+  const double half_tile = LANES ? 0.5 : 0.0;
+  const double tx = ox + half_tile * ((g.B[0] + 2) * (Lx / g.nc[0]));
+  const double ty = oy + half_tile * ((g.B[1] + 2) * (Ly / g.nc[1]));
+  const double tz = oz + half_tile * ((g.B[2] + 2) * (Lz / g.nc[2]));
+  auto near_tile = [](double v) {  // and finite, or far from everything
+    const float f = (float)v;
+    return !LANES || __builtin_fabsf(f) < kFarLane ? f : kFarLane;
+  };
   tile_slot_cells(ntc, total, t);
   {
     const int nt = total < TS::kCap ? total : TS::kCap;
@@ -263,14 +532,14 @@ k_build_tile_nlist(
       t.z[TS::kDummy] = kFarF;
     }
     // (several slots per thread in flight where the workgroups are small)
-#pragma unroll RW == 9 ? 4 : 1
+#pragma unroll RW == 9 || LANES ? 4 : 1
     for (int u = threadIdx.x; u < nt; u += blockDim.x) {
       const int c = t.cell[u];
       const int src = t.src[c] + (u - t.prefix[c]);
       const int code = t.code[c];
-      t.x[u] = (float)((x[src] + (double)((code & 3) - 1) * Lx) - ox);
-      t.y[u] = (float)((y[src] + (double)(((code >> 2) & 3) - 1) * Ly) - oy);
-      t.z[u] = (float)((z[src] + (double)(((code >> 4) & 3) - 1) * Lz) - oz);
+      t.x[u] = near_tile((x[src] + (double)((code & 3) - 1) * Lx) - tx);
+      t.y[u] = near_tile((y[src] + (double)(((code >> 2) & 3) - 1) * Ly) - ty);
+      t.z[u] = near_tile((z[src] + (double)(((code >> 4) & 3) - 1) * Lz) - tz);
     }
     __syncthreads();
   }
@@ -418,6 +687,93 @@ k_build_tile_nlist(
       scan_cell(lc, 9 / RW * r, 9 / RW * (r + 1), rcnt[r], std::false_type());
     }
   } else {
+    if constexpr (LANES) {
+      // The particles of each cell's lower and upper half in quads of lanes
+      // (acnt: tile cell, particle of the cell, and whether the lane only
+      // fills its quad); every cell's K and rows must be within the tables.
+      __shared__ __attribute__((aligned(16))) LaneTables tab;
+      __shared__ Compress pack;
+      __shared__ int quads[64], nlanes;
+      if (threadIdx.x < 16) pack.sel[threadIdx.x] = kCompress.sel[threadIdx.x];
+      for (int k = threadIdx.x; k < (int)(sizeof(LaneTables) / 16); k += blockDim.x)
+        ((uint4*)&tab)[k] = ((const uint4*)&kLaneTables)[k];
+      auto home_cell = [&](int lc) {  // tile cell, or -1 past the grid
+        const int lx = lc % g.B[0], ly = (lc / g.B[0]) % g.B[1], lz = lc / (g.B[0] * g.B[1]);
+        if (bx * g.B[0] + lx >= g.nc[0] || by * g.B[1] + ly >= g.nc[1] || bz * g.B[2] + lz >= g.nc[2])
+          return -1;
+        return ((lz + 1) * (g.B[1] + 2) + (ly + 1)) * TX + (lx + 1);
+      };
+      if (wave == 0) {
+        const int tc = lane < g.V ? home_cell(lane) : -1;
+        const int ncell = tc >= 0 ? t.prefix[tc + 1] - t.prefix[tc] : 0;
+        const int low = xh && tc >= 0 ? tlow[tc] : 0;
+        const int want = ((low + 3) & ~3) + ((ncell - low + 3) & ~3), upto = wave_scan_i32(want);
+        quads[lane] = upto - want;
+        if (lane == 63) nlanes = upto;
+      }
+      __syncthreads();
+      const int T = nlanes;
+      bool bad = nbrick > kBrickMax || total > TS::kCap || T > kBrickMax || g.V > 64;
+      for (int lc = wave; lc < g.V; lc += nwaves) {
+        const int tc = home_cell(lc);
+        if (tc < 0) continue;
+        const int ncell = t.prefix[tc + 1] - t.prefix[tc];
+        bad |= ncell > 64 || (ncell && ncell < (64 + kLaneK) / (kLaneK + 1));
+        if (lane < 9 && ncell) {
+          const int tcl = tc + (lane / 3 - 1) * TXY + (lane % 3 - 1) * TX - 1;
+          bad |= t.prefix[tcl + 3] - t.prefix[tcl] > kLaneRow;
+        }
+        const int low = xh ? tlow[tc] : 0, plow = (low + 3) & ~3;
+        for (int p = lane; p < plow + ((ncell - low + 3) & ~3); p += 64) {
+          const int last = p < plow ? low - 1 : ncell - 1, a = p < plow ? p : low + p - plow;
+          if (quads[lc] + p < kBrickMax)
+            acnt[quads[lc] + p] = tc | (a < last ? a : last) << 8 | (a > last ? 1 : 0) << 24;
+        }
+      }
+      if (!__syncthreads_or(bad)) {
+        int most = 0;
+        for (int l0 = 64 * wave; l0 < T; l0 += 64 * nwaves) {
+          const bool has = l0 + lane < T;
+          const int code = acnt[has ? l0 + lane : l0], tc0 = code & 255, a = (code >> 8) & 0xffff;
+          const bool ok = has && !(code >> 24);
+          const int first = t.prefix[tc0], na = t.prefix[tc0 + 1] - first;
+          const int s = t.src[tc0] + a;
+          LanePoint pt;
+          pt.K = 64 / na;
+          pt.self = first + a;
+          pt.slot = s;
+          const float px = t.x[pt.self], py = t.y[pt.self], pz = t.z[pt.self];
+          pt.ax = -2.0f * px;
+          pt.ay = -2.0f * py;
+          pt.az = -2.0f * pz;
+          const float c = (float)(((double)px * px + (double)py * py + (double)pz * pz) - r2);
+          pt.c = f32x4{c, c, c, c};
+          const bool lower = xh && a < tlow[tc0], upper = xh && !lower;
+          const int mK = 65536 / pt.K + 1, m4K = 16384 / pt.K + 1;
+          typedef std::conditional_t<A24, uint32_t, uint64_t> Off;
+          const Off pitch = (Off)tl.stride * 8;
+          ListOut<Off> out{0, 0, (Off)s * 8, pitch, (Off)((max_nb + 3) >> 2) * pitch, (char*)half};
+          for (int row = 0; row < 9; ++row) {
+            const int tcl = tc0 + (row / 3 - 1) * TXY + (row % 3 - 1) * TX - 1;
+            const int ub = t.prefix[tcl] + (upper ? tlow[tcl] : 0);
+            const int ue = lower ? t.prefix[tcl + 2] + tlow[tcl + 2] : t.prefix[tcl + 3];
+            lane_row(t, tab, pack, g, x, y, z, r2, ub, has ? ue - ub : 0, pt, guard, mK, m4K,
+                     row == 4, ok ? ~0u : 0u, out);
+          }
+          if (ok) {
+            const int m = out.finish((Off)s * 8, max_nb, (uint32_t)TS::kDummy << kFullShift);
+            tl.cnt[s] = m < max_nb ? m : max_nb;
+            if (m > max_nb) atomicOr(flags, MDPL_FLAG_NL_OVERFLOW);
+            most = m > most ? m : most;
+          }
+        }
+        most = wave_max_i32(most);
+        if (lane == 0 && most > 0) atomicMax(maxcount, most);
+        return;
+      }
+      for (int a = threadIdx.x; a < kBrickMax; a += blockDim.x) acnt[a] = 0;
+      __syncthreads();
+    }
     for (int lc = wave; lc < g.V; lc += nwaves) scan_cell(lc, 0, 9, acnt, std::false_type());
   }
   __syncthreads();
@@ -434,11 +790,7 @@ k_build_tile_nlist(
     if (count > max_nb) atomicOr(flags, MDPL_FLAG_NL_OVERFLOW);
     most = count > most ? count : most;
   }
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) {
-    const int o = __shfl_xor(most, off, 64);
-    most = o > most ? o : most;
-  }
+  most = wave_max_i32(most);
   if ((threadIdx.x & 63) == 0 && most > 0) atomicMax(maxcount, most);
 }
 
@@ -459,7 +811,7 @@ hipError_t build_tile_nlist(const double* x, const double* y, const double* z,
   const float guard = (float)(8.0 * err);
   const dim3 grid(tile_grid(g));
   if (tl.half) {
-    hipLaunchKernelGGL((k_build_tile_nlist<TileHalf32, true, false, 1>), grid, dim3(threads), 0, st,
+    hipLaunchKernelGGL((k_build_tile_nlist<TileHalf32, true, false, 1, false>), grid, dim3(threads), 0, st,
                        x, y, z, cell_start, g, r2, guard, tl, flags, maxcount, g.V);
     return hipGetLastError();
   }
@@ -470,20 +822,45 @@ hipError_t build_tile_nlist(const double* x, const double* y, const double* z,
   parts = (int)div_up(g.V, cells);
   const int rw = cells * 9 <= 16 ? 9 : (cells * 3 <= 16 ? 3 : 1);
   const bool a24 = tl.stride * 8 < (int64_t)(1 << 24);
+  // a lane per particle where cells hold enough of them, but not over 64
+  // (those of a full brick; the stride is the padded number of all): waves
+  // for its quads, but at most 8, so that two workgroups share a CU evenly
+  // (N = 10^6: 5 waves 330 us, 7 316, 8 305, 9 353, 12 337)
+  const int64_t full = tl.stride * g.V / ((int64_t)g.nc[0] * g.nc[1] * g.nc[2]);
+  unsigned lane_threads = 0;
+  if (full >= 10 * (int64_t)g.V && full <= 48 * (int64_t)g.V) {
+    lane_threads = (unsigned)div_up(full * 6 / 5, 64) * 64;
+    lane_threads = lane_threads < 256 ? 256 : (lane_threads > kLaneThreads ? kLaneThreads : lane_threads);
+  }
+  // its screen on the matrix cores: with coordinates up to span / 2 from the
+  // tile's centre, |x|^2 <= 3 span^2 / 4, the squares are within 3 and 4 ulp
+  // of it, and each of four accumulations of terms below 6 span^2 / 4 rounds
+  // (2 ulp allowed): 17.3 span^2 2^-24 on top of err
+  const float lane_guard = (float)(8.0 * err + 2.0 * 17.3 * span * span * u32);
   if (a24 && parts > 1 && rw == 9)
-    hipLaunchKernelGGL((k_build_tile_nlist<TileShared32, false, true, 9>), dim3(grid.x, parts),
+    hipLaunchKernelGGL((k_build_tile_nlist<TileShared32, false, true, 9, false>), dim3(grid.x, parts),
                        dim3(cells * 9 * 64), 0, st, x, y, z, cell_start, g, r2, guard, tl,
                        flags, maxcount, cells);
   else if (a24 && parts > 1 && rw == 3)
-    hipLaunchKernelGGL((k_build_tile_nlist<TileShared32, false, true, 3>), dim3(grid.x, parts),
+    hipLaunchKernelGGL((k_build_tile_nlist<TileShared32, false, true, 3, false>), dim3(grid.x, parts),
                        dim3(cells * 3 * 64), 0, st, x, y, z, cell_start, g, r2, guard, tl,
                        flags, maxcount, cells);
+  else if (lane_threads && a24)
+    hipLaunchKernelGGL((k_build_tile_nlist<TileShared32, false, true, 1, true>), grid,
+                       dim3(lane_threads), 0, st, x, y, z, cell_start, g, r2, lane_guard, tl, flags,
+                       maxcount, g.V);
+  else if (lane_threads)
+    hipLaunchKernelGGL((k_build_tile_nlist<TileShared32, false, false, 1, true>), grid,
+                       dim3(lane_threads), 0, st, x, y, z, cell_start, g, r2, lane_guard, tl, flags,
+                       maxcount, g.V);
   else if (a24)
-    hipLaunchKernelGGL((k_build_tile_nlist<TileShared32, false, true, 1>), grid, dim3(threads), 0,
-                       st, x, y, z, cell_start, g, r2, guard, tl, flags, maxcount, g.V);
+    hipLaunchKernelGGL((k_build_tile_nlist<TileShared32, false, true, 1, false>), grid,
+                       dim3(threads), 0, st, x, y, z, cell_start, g, r2, guard, tl, flags,
+                       maxcount, g.V);
   else
-    hipLaunchKernelGGL((k_build_tile_nlist<TileShared32, false, false, 1>), grid, dim3(threads), 0,
-                       st, x, y, z, cell_start, g, r2, guard, tl, flags, maxcount, g.V);
+    hipLaunchKernelGGL((k_build_tile_nlist<TileShared32, false, false, 1, false>), grid,
+                       dim3(threads), 0, st, x, y, z, cell_start, g, r2, guard, tl, flags,
+                       maxcount, g.V);
   return hipGetLastError();
 }
 
