@@ -407,11 +407,15 @@ __device__ __forceinline__ bool lane_group(int p0, int npart, int t, LaneGroup& 
   lg.T = T;
   return true;
 }
-// Workgroup size of the plain FP32 pass (its LDS fits three workgroups per CU).
+// Workgroup size of the plain FP32 pass: its LDS fits three workgroups per CU.
+// Where the chip has at most two of them per CU, 1024 threads each keep its
+// wave slots full and halve the tile load's turns (N = 125000 at list radius
+// 3.3, 512 bricks: 32.8 -> 29.3 us; N = 262144, 512 bricks: 37.2 -> 31.3 us;
+// at 520 bricks a third of the chip would wait for a second turn).
 #ifndef MDPL_PLAIN_THREADS
 #define MDPL_PLAIN_THREADS 512
 #endif
-constexpr int kPlainThreads = MDPL_PLAIN_THREADS;
+constexpr int kPlainThreads = MDPL_PLAIN_THREADS, kPlainFew = 512;
 constexpr int kPartThreads = 512;  // of a part, where a brick has several (lane slots in turns)
 
 // Plain FP32 pass: the pair loop of every particle of the brick (its own
@@ -793,8 +797,8 @@ hipError_t lj_force(const double* x, const double* y, const double* z, const int
                            g, tl, c, k, out);
       else
         hipLaunchKernelGGL((k_lj_force32_plain<float>), grid,
-                           dim3(one ? kPlainThreads : kPartThreads), 0, st, x, y, z, cell_start, g,
-                           tl, c, k, out);
+                           dim3(!one ? kPartThreads : (grid.x <= kPlainFew ? 1024 : kPlainThreads)), 0, st, x,
+                           y, z, cell_start, g, tl, c, k, out);
       break;
     }
     default:
