@@ -69,6 +69,7 @@ struct mdpl_sim {
   double *px, *py, *pz;  // spare positions: target of the fused drift (run)
   int32_t* offsets;      // n + 1 (export)
   double* partials;      // per-block partials
+  double* fpart;         // the force passes' sums per workgroup (shared_bricks)
   int nblk;
   uint32_t* flags;
   int32_t* maxcount;
@@ -195,12 +196,36 @@ int64_t partial_rows(int64_t n, const Grid& g, int parts) {
   return a > b ? a : b;
 }
 
+// Several workgroups per brick: the rows of their sums and the rule's maxima
+// lie in the sort's buffers, all but the sorted keys, which are free until
+// the next sort (a force pass's sums are reduced right after it, and a new
+// list drops the maxima), so that the workspace has the same size.  As many
+// parts as fit; one where the sort is the radix sort, whose keys may end in
+// either buffer.
+void shared_bricks(mdpl_sim* s) {
+  s->fpart = s->partials;
+  s->tl.parts = 1;
+  if ((int64_t)s->g.nkeys > 8 * s->n) return;
+  const size_t room = 3 * align256(4 * (size_t)s->n);
+  for (int parts = force_parts(&s->p, s->g); parts > 1; --parts) {
+    const size_t rows = align256(8 * (size_t)(3 * partial_rows(s->n, s->g, parts) + 2));
+    const size_t maxima = align256(8 * (size_t)track_slots(s->n, s->g, parts));
+    if (rows + 2 * maxima > room) continue;
+    char* w = (char*)s->sort.vals[0];  // then keys[1] and vals[1]
+    s->tl.parts = parts;
+    s->nvpart = (int)track_slots(s->n, s->g, parts);
+    s->fpart = (double*)w;
+    s->vpart[0] = (double*)(w + rows);
+    s->vpart[1] = (double*)(w + rows + maxima);
+    return;
+  }
+}
+
 size_t lj_ws_bytes(const mdpl_lj_params* p, const Grid& g) {
   const int64_t n = p->n;
   const int64_t npad = div_up(n, 256) * 256;
   const size_t fb = p->precision == MDPL_FP32 ? 4 : 8;
-  const int parts = force_parts(p, g);
-  const int64_t nblk = partial_rows(n, g, parts);
+  const int64_t nblk = partial_rows(n, g, 1);
   size_t b = sort_bytes(n);
   b += align256(4 * (size_t)(g.nkeys + 1));    // cell_start
   b += align256(4 * (size_t)n);                // perm
@@ -216,7 +241,7 @@ size_t lj_ws_bytes(const mdpl_lj_params* p, const Grid& g) {
   b += align256(4 * (size_t)(g.nkeys + 1));                 // lower-x-half counts
   b += align256(4 * (size_t)(n + 1));          // offsets
   b += align256(8 * (size_t)(3 * nblk + 2));   // partials
-  b += 2 * align256(8 * (size_t)track_slots(n, g, parts));  // the rule's per-workgroup maxima
+  b += 2 * align256(8 * (size_t)track_slots(n, g, 1));  // the rule's per-workgroup maxima
   b += align256(256);                          // flags, maxcount, max_disp, pe_w_tmp, rule, last row
   b += align256(4 * 8 * (size_t)g.nbricks);   // brick order of the tile kernels
   return b;
@@ -310,7 +335,7 @@ mdpl_status launch_force(mdpl_sim* s, const double* x, const double* y, const do
   out.fz = fz;
   out.scatter = scatter;
   out.e_atom = e_atom;
-  out.partials = s->partials;
+  out.partials = s->fpart;
   out.scale = 1.0;
   out.scale_dev = nullptr;
   out.fuse = kick != nullptr;
@@ -355,7 +380,7 @@ mdpl_status launch_force(mdpl_sim* s, const double* x, const double* y, const do
       o.csrc = s->max_disp;
       o.cdst = disp_dst;
     }
-    HIP_TRY(reduce_row(s->partials, nb, out.fuse ? 3 : 2, ncomp, o, s->st));
+    HIP_TRY(reduce_row(s->fpart, nb, out.fuse ? 3 : 2, ncomp, o, s->st));
   }
   return MDPL_OK;
 }
@@ -442,12 +467,12 @@ mdpl_status mdpl_sim_create(const mdpl_lj_params* p, void* workspace, size_t byt
   if (s->tl.half || s->tl.cells || !(p->box[0] / s->g.nc[0] > rext * (1.0 + 1e-9)))
     s->tl.xlow = nullptr;
   s->offsets = take<int32_t>(w, 4 * (size_t)(n + 1));
-  s->tl.parts = force_parts(p, s->g);
-  s->nblk = (int)partial_rows(n, s->g, s->tl.parts);
+  s->nblk = (int)partial_rows(n, s->g, 1);
   s->partials = take<double>(w, 8 * (size_t)(3 * s->nblk + 2));
-  s->nvpart = (int)track_slots(n, s->g, s->tl.parts);
+  s->nvpart = (int)track_slots(n, s->g, 1);
   s->vpart[0] = take<double>(w, 8 * (size_t)s->nvpart);
   s->vpart[1] = take<double>(w, 8 * (size_t)s->nvpart);
+  shared_bricks(s);
   char* small = take<char>(w, 256);
   {
     const std::vector<int32_t> order = brick_order(s->g);
@@ -586,7 +611,7 @@ mdpl_status mdpl_lj_backward(mdpl_sim* s, const double* x, const double* y, cons
   out.fz = gz;
   out.scatter = s->perm;
   out.e_atom = nullptr;
-  out.partials = s->partials;
+  out.partials = s->fpart;
   out.scale = -1.0;
   out.scale_dev = grad_e;
   out.fuse = false;

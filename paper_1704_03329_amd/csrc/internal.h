@@ -193,7 +193,7 @@ struct LJConst {
 // stream.  No atomics and no device-scope fences are needed (the launch
 // boundary orders the maxima before their reduction).  The host publishes a
 // pending record with k_publish when it must decide at once; the rebuild
-// (k_reorder) sets bound back to zero and drops the pending record.
+// (MoveState) sets bound back to zero and drops the pending record.
 struct KickRecord {
   int64_t stamp;  // global step index of the positions the drift produced (-1: empty)
   double bound;   // sum of dt * max|v| since the last build, this step included
