@@ -463,7 +463,7 @@ __device__ __forceinline__ void lane_row(const TS& t, const LaneTables& tab, con
 // two 1024-thread workgroups share a CU.  TS: the tile (full or half list).
 //
 // LANES: a lane per particle (lane_row) in every brick whose cells and rows
-// the tables cover, else as without.
+// the tables cover, else as without; blockIdx.y as for RW > 1.
 //
 // RW > 1 (small systems, full lists): blockIdx.y is the workgroup's part of
 // the brick, `cells` home cells, and RW waves share a cell, each taking 9/RW
@@ -488,11 +488,12 @@ k_build_tile_nlist(
   const int brick = brick_of_block(g);
   if (brick >= g.nbricks) return;
   // the workgroup's home cells (local indices within the brick) and slots
-  const int lc0 = RW > 1 ? (int)blockIdx.y * cells : 0;
-  const int lc1 = RW > 1 && lc0 + cells < g.V ? lc0 + cells : g.V;
+  constexpr bool kParts = RW > 1 || LANES;
+  const int lc0 = kParts ? (int)blockIdx.y * cells : 0;
+  const int lc1 = kParts && lc0 + cells < g.V ? lc0 + cells : g.V;
   const int s0 = cs[brick * g.V], s1 = cs[(brick + 1) * g.V];
-  const int p0 = RW > 1 ? cs[brick * g.V + lc0] : s0, p1 = RW > 1 ? cs[brick * g.V + lc1] : s1;
-  if (RW > 1 && blockIdx.y && p0 == p1) return;  // part 0 leaves the tables
+  const int p0 = kParts ? cs[brick * g.V + lc0] : s0, p1 = kParts ? cs[brick * g.V + lc1] : s1;
+  if (kParts && blockIdx.y && p0 == p1) return;  // part 0 leaves the tables
   const bool xh = !HALF && tl.xlow != nullptr;
   const int total = tile_cells(g, brick, cs, t, HALF, tl.xlow, xh ? tlow : nullptr);
   if (!HALF && tl.tab && blockIdx.y == 0)
@@ -704,7 +705,7 @@ k_build_tile_nlist(
         return ((lz + 1) * (g.B[1] + 2) + (ly + 1)) * TX + (lx + 1);
       };
       if (wave == 0) {
-        const int tc = lane < g.V ? home_cell(lane) : -1;
+        const int tc = lane >= lc0 && lane < lc1 ? home_cell(lane) : -1;
         const int ncell = tc >= 0 ? t.prefix[tc + 1] - t.prefix[tc] : 0;
         const int low = xh && tc >= 0 ? tlow[tc] : 0;
         const int want = ((low + 3) & ~3) + ((ncell - low + 3) & ~3), upto = wave_scan_i32(want);
@@ -714,7 +715,7 @@ k_build_tile_nlist(
       __syncthreads();
       const int T = nlanes;
       bool bad = nbrick > kBrickMax || total > TS::kCap || T > kBrickMax || g.V > 64;
-      for (int lc = wave; lc < g.V; lc += nwaves) {
+      for (int lc = lc0 + wave; lc < lc1; lc += nwaves) {
         const int tc = home_cell(lc);
         if (tc < 0) continue;
         const int ncell = t.prefix[tc + 1] - t.prefix[tc];
@@ -774,7 +775,7 @@ k_build_tile_nlist(
       for (int a = threadIdx.x; a < kBrickMax; a += blockDim.x) acnt[a] = 0;
       __syncthreads();
     }
-    for (int lc = wave; lc < g.V; lc += nwaves) scan_cell(lc, 0, 9, acnt, std::false_type());
+    for (int lc = lc0 + wave; lc < lc1; lc += nwaves) scan_cell(lc, 0, 9, acnt, std::false_type());
   }
   __syncthreads();
   // every slot gets its count (zero past kBrickMax, flagged above)
@@ -825,11 +826,19 @@ hipError_t build_tile_nlist(const double* x, const double* y, const double* z,
   // a lane per particle where cells hold enough of them, but not over 64
   // (those of a full brick; the stride is the padded number of all): waves
   // for its quads, but at most 8, so that two workgroups share a CU evenly
-  // (N = 10^6: 5 waves 330 us, 7 316, 8 305, 9 353, 12 337)
+  // (N = 10^6: 5 waves 330 us, 7 316, 8 305, 9 353, 12 337).  Few bricks are
+  // shared here too: whole builds with the sort, N = 64000 (128 bricks of 3^3
+  // cells) 82 -> 68 us, but two parts of 208 such bricks 82 -> 90; N = 42875 at
+  // list radius 3.3 (216 of 2^3) 104 -> 82 us in two parts, 113 with three
+  // waves per cell, which stay ahead for 3^3 bricks (N = 32768 55 against 62).
   const int64_t full = tl.stride * g.V / ((int64_t)g.nc[0] * g.nc[1] * g.nc[2]);
+  const bool small_bricks = g.V <= 8;
   unsigned lane_threads = 0;
+  int lane_cells = g.V, lane_parts = 1;
   if (full >= 10 * (int64_t)g.V && full <= 48 * (int64_t)g.V) {
-    lane_threads = (unsigned)div_up(full * 6 / 5, 64) * 64;
+    lane_cells = (int)div_up(g.V, brick_parts(g, small_bricks ? kBuildWant : kBuildWant / 2, g.V));
+    lane_parts = (int)div_up(g.V, lane_cells);
+    lane_threads = (unsigned)div_up(full * 6 / 5 * lane_cells / g.V, 64) * 64;
     lane_threads = lane_threads < 256 ? 256 : (lane_threads > kLaneThreads ? kLaneThreads : lane_threads);
   }
   // its screen on the matrix cores: with coordinates up to span / 2 from the
@@ -841,18 +850,18 @@ hipError_t build_tile_nlist(const double* x, const double* y, const double* z,
     hipLaunchKernelGGL((k_build_tile_nlist<TileShared32, false, true, 9, false>), dim3(grid.x, parts),
                        dim3(cells * 9 * 64), 0, st, x, y, z, cell_start, g, r2, guard, tl,
                        flags, maxcount, cells);
-  else if (a24 && parts > 1 && rw == 3)
+  else if (a24 && parts > 1 && rw == 3 && !(lane_threads && small_bricks))
     hipLaunchKernelGGL((k_build_tile_nlist<TileShared32, false, true, 3, false>), dim3(grid.x, parts),
                        dim3(cells * 3 * 64), 0, st, x, y, z, cell_start, g, r2, guard, tl,
                        flags, maxcount, cells);
   else if (lane_threads && a24)
-    hipLaunchKernelGGL((k_build_tile_nlist<TileShared32, false, true, 1, true>), grid,
+    hipLaunchKernelGGL((k_build_tile_nlist<TileShared32, false, true, 1, true>), dim3(grid.x, lane_parts),
                        dim3(lane_threads), 0, st, x, y, z, cell_start, g, r2, lane_guard, tl, flags,
-                       maxcount, g.V);
+                       maxcount, lane_cells);
   else if (lane_threads)
-    hipLaunchKernelGGL((k_build_tile_nlist<TileShared32, false, false, 1, true>), grid,
+    hipLaunchKernelGGL((k_build_tile_nlist<TileShared32, false, false, 1, true>), dim3(grid.x, lane_parts),
                        dim3(lane_threads), 0, st, x, y, z, cell_start, g, r2, lane_guard, tl, flags,
-                       maxcount, g.V);
+                       maxcount, lane_cells);
   else if (a24)
     hipLaunchKernelGGL((k_build_tile_nlist<TileShared32, false, true, 1, false>), grid,
                        dim3(threads), 0, st, x, y, z, cell_start, g, r2, guard, tl, flags,

@@ -22,6 +22,9 @@ CASES = {
     "thin": ((6, 6, 6), (13, 13, 14), (3, 3, 3)),
     # 30 - 45 per cell (K = 1, 2): bricks of 2^3 and 1
     "dense": ((4, 4, 5), (13, 13, 16), (3, 3, 2)),
+    # 100 bricks of 3^3, each shared by two workgroups; 216 of 2^3 likewise
+    "shared": ((5, 5, 4), (13, 13, 11), (3, 3, 3)),
+    "shared_small": ((4, 4, 4), (13, 13, 12), (3, 3, 3)),
 }
 
 
