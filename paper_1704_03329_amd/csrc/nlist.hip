@@ -232,6 +232,7 @@ struct LaneTables {
   uint16_t pos[kLaneK][kLaneRow];
   uint16_t group[kLaneK][kLaneRow / 4];
   uint32_t valid[kLaneK][4 * kLaneK];
+  int32_t over[kLaneK], over4[kLaneK];  // div_small's multipliers for K and 4 K
 };
 constexpr LaneTables lane_tables() {
   LaneTables t{};
@@ -241,6 +242,8 @@ constexpr LaneTables lane_tables() {
       t.pos[K - 1][p] = (uint16_t)(i << kFullShift);
       if (p % 4 == 0) t.group[K - 1][p / 4] = (uint16_t)(4 * i);
     }
+    t.over[K - 1] = 65536 / K + 1;
+    t.over4[K - 1] = 65536 / (4 * K) + 1;
     for (int rem = 0; rem < 4 * K; ++rem)
       for (int p = 0; p < 4 * K; ++p)
         if (p % 4 * K + p / 4 < rem) t.valid[K - 1][rem] |= 1u << p;
@@ -698,8 +701,10 @@ k_build_tile_nlist(
       if (threadIdx.x < 16) pack.sel[threadIdx.x] = kCompress.sel[threadIdx.x];
       for (int k = threadIdx.x; k < (int)(sizeof(LaneTables) / 16); k += blockDim.x)
         ((uint4*)&tab)[k] = ((const uint4*)&kLaneTables)[k];
+      const int mB0 = 65536 / g.B[0] + 1, mB1 = 65536 / g.B[1] + 1;
       auto home_cell = [&](int lc) {  // tile cell, or -1 past the grid
-        const int lx = lc % g.B[0], ly = (lc / g.B[0]) % g.B[1], lz = lc / (g.B[0] * g.B[1]);
+        const int yz = div_small(lc, mB0), lz = div_small(yz, mB1);
+        const int lx = lc - yz * g.B[0], ly = yz - lz * g.B[1];
         if (bx * g.B[0] + lx >= g.nc[0] || by * g.B[1] + ly >= g.nc[1] || bz * g.B[2] + lz >= g.nc[2])
           return -1;
         return ((lz + 1) * (g.B[1] + 2) + (ly + 1)) * TX + (lx + 1);
@@ -740,7 +745,8 @@ k_build_tile_nlist(
           const int first = t.prefix[tc0], na = t.prefix[tc0 + 1] - first;
           const int s = t.src[tc0] + a;
           LanePoint pt;
-          pt.K = 64 / na;
+          // 64 / na: na is 8 to 64, and 64 / na at least 1 / 64 off the next integer
+          pt.K = (int)(64.0f * __builtin_amdgcn_rcpf((float)na) + 0.001f);
           pt.self = first + a;
           pt.slot = s;
           const float px = t.x[pt.self], py = t.y[pt.self], pz = t.z[pt.self];
@@ -750,7 +756,7 @@ k_build_tile_nlist(
           const float c = (float)(((double)px * px + (double)py * py + (double)pz * pz) - r2);
           pt.c = f32x4{c, c, c, c};
           const bool lower = xh && a < tlow[tc0], upper = xh && !lower;
-          const int mK = 65536 / pt.K + 1, m4K = 16384 / pt.K + 1;
+          const int mK = tab.over[pt.K - 1], m4K = tab.over4[pt.K - 1];
           typedef std::conditional_t<A24, uint32_t, uint64_t> Off;
           const Off pitch = (Off)tl.stride * 8;
           ListOut<Off> out{0, 0, (Off)s * 8, pitch, (Off)((max_nb + 3) >> 2) * pitch, (char*)half};
