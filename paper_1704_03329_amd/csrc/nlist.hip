@@ -227,7 +227,7 @@ __device__ __forceinline__ void row_store(const RowBits& bits, int ub, uint32_t 
 // and, for every fourth position, as byte offset into the 4-byte tile arrays
 // (the three that follow lie K apart each), and the positions that exist in
 // an incomplete last block of `rem` candidates.
-constexpr int kLaneK = 8, kLaneRow = 256;  // largest K; candidates of a row
+constexpr int kLaneK = 8, kLaneRow = 256;  // largest K; positions of a row
 struct LaneTables {
   uint16_t pos[kLaneK][kLaneRow];
   uint16_t group[kLaneK][kLaneRow / 4];
@@ -727,7 +727,8 @@ k_build_tile_nlist(
         bad |= ncell > 64 || (ncell && ncell < (64 + kLaneK) / (kLaneK + 1));
         if (lane < 9 && ncell) {
           const int tcl = tc + (lane / 3 - 1) * TXY + (lane % 3 - 1) * TX - 1;
-          bad |= t.prefix[tcl + 3] - t.prefix[tcl] > kLaneRow;
+          // (the positions of an incomplete last block reach past the row)
+          bad |= t.prefix[tcl + 3] - t.prefix[tcl] > kLaneRow - 4 * kLaneK;
         }
         const int low = xh ? tlow[tc] : 0, plow = (low + 3) & ~3;
         for (int p = lane; p < plow + ((ncell - low + 3) & ~3); p += 64) {
