@@ -27,6 +27,7 @@
 
 #include "device_util.h"
 #include "internal.h"
+#include "list_out.h"
 #include "tile.h"
 
 namespace mdpl {
@@ -228,6 +229,7 @@ __device__ __forceinline__ void row_store(const RowBits& bits, int ub, uint32_t 
 // (the three that follow lie K apart each), and the positions that exist in
 // an incomplete last block of `rem` candidates.
 constexpr int kLaneK = 8, kLaneRow = 256;  // largest K; positions of a row
+static_assert(kListRow == kLaneRow - 4 * kLaneK, "an incomplete last block reaches past the row");
 struct LaneTables {
   uint16_t pos[kLaneK][kLaneRow];
   uint16_t group[kLaneK][kLaneRow / 4];
@@ -264,66 +266,7 @@ __device__ __forceinline__ int wave_max_i32(int v) {
 // a / b for 0 <= a <= 2 kLaneRow, 1 <= b <= 4 kLaneK from m = 65536 / b + 1
 __device__ __forceinline__ int div_small(int a, int m) { return (int)(__umul24(a, m) >> 16); }
 
-// A list as it grows: its newest entries, up to three, in a 64-bit word that
-// is stored when it is full.  Four positions are appended at a time, without
-// branches: their accepted entries are moved together by byte permutations
-// from a table, shifted behind those held, and what does not fit starts the
-// next word.
-struct Compress {
-  uint2 sel[16];  // per nibble of decisions: selectors of entries 0, 1 and 2, 3
-};
-constexpr Compress compress_table() {
-  Compress t{};
-  for (unsigned nib = 0; nib < 16; ++nib) {
-    uint32_t sel[2] = {0x0c0c0c0cu, 0x0c0c0c0cu};  // zero bytes
-    for (unsigned j = 0, m = 0; j < 4; ++j)
-      if (nib >> j & 1) {
-        sel[m / 2] = m % 2 ? (sel[m / 2] & 0xffffu) | (0x0100u + 0x0202u * j) << 16
-                           : (sel[m / 2] & 0xffff0000u) | (0x0100u + 0x0202u * j);
-        ++m;
-      }
-    t.sel[nib].x = sel[0];
-    t.sel[nib].y = sel[1];
-  }
-  return t;
-}
 __device__ const Compress kCompress = compress_table();
-
-// OFF: unsigned of the width that the list's byte offsets need.
-template <typename OFF>
-struct ListOut {
-  uint64_t acc;
-  uint32_t held;      // entries in acc
-  OFF at;             // where the next word goes
-  OFF pitch, room;    // bytes between words; those of all words of all lists
-  char* list;         // of the first slot
-  // e01, e23: entries of the four positions, 16 bits each
-  __device__ __forceinline__ void push4(uint32_t nib, uint2 sel, uint32_t e01, uint32_t e23) {
-    const uint64_t c = (uint64_t)__builtin_amdgcn_perm(e23, e01, sel.y) << 32 |
-                       __builtin_amdgcn_perm(e23, e01, sel.x);
-    const uint32_t sh = held << 4;
-    acc |= c << sh;
-    const uint64_t rest = (c >> (48 - sh)) >> 16;
-    const uint32_t sum = held + __popc(nib);
-    const bool full = sum > 3;
-    if (full && at < room) *(uint64_t*)(list + at) = acc;
-    at += full ? pitch : 0;
-    acc = full ? rest : acc;
-    held = sum & 3;
-  }
-  // Pads the last word; returns the entries found.  `first`: where the list
-  // begins; a list cut at its capacity is padded there.
-  __device__ __forceinline__ int finish(OFF first, int max_nb, uint32_t pad) {
-    const int m = 4 * (int)((double)(at - first) / (double)pitch + 0.5) + (int)held;
-    if (held && at < room)
-      *(uint64_t*)(list + at) = acc | (0x0001000100010001ull * pad) << (16 * held);
-    if (m > max_nb && (max_nb & 3)) {
-      uint16_t* last = (uint16_t*)(list + first + (OFF)(max_nb >> 2) * pitch);
-      for (int k = max_nb & 3; k < 4; ++k) last[k] = (uint16_t)pad;
-    }
-    return m;
-  }
-};
 
 // The particle of a lane for the matrix cores: e = |x_i - x_j|^2 - r^2 of four
 // particles and four candidates is (|x_i|^2 - r^2) + 1 |x_j|^2 - 2 x_i x_j -
@@ -727,8 +670,7 @@ k_build_tile_nlist(
         bad |= ncell > 64 || (ncell && ncell < (64 + kLaneK) / (kLaneK + 1));
         if (lane < 9 && ncell) {
           const int tcl = tc + (lane / 3 - 1) * TXY + (lane % 3 - 1) * TX - 1;
-          // (the positions of an incomplete last block reach past the row)
-          bad |= t.prefix[tcl + 3] - t.prefix[tcl] > kLaneRow - 4 * kLaneK;
+          bad |= t.prefix[tcl + 3] - t.prefix[tcl] > kListRow;
         }
         const int low = xh ? tlow[tc] : 0, plow = (low + 3) & ~3;
         for (int p = lane; p < plow + ((ncell - low + 3) & ~3); p += 64) {
@@ -853,6 +795,8 @@ hipError_t build_tile_nlist(const double* x, const double* y, const double* z,
   // of it, and each of four accumulations of terms below 6 span^2 / 4 rounds
   // (2 ulp allowed): 17.3 span^2 2^-24 on top of err
   const float lane_guard = (float)(8.0 * err + 2.0 * 17.3 * span * span * u32);
+  // A lane's offsets: 64 bits cost a build of 1.5 * 10^6 particles 458 -> 471 us,
+  // numbering the words in 32 bits 468 (and one of 10^6 325 -> 332).
   if (a24 && parts > 1 && rw == 9)
     hipLaunchKernelGGL((k_build_tile_nlist<TileShared32, false, true, 9, false>), dim3(grid.x, parts),
                        dim3(cells * 9 * 64), 0, st, x, y, z, cell_start, g, r2, guard, tl,
@@ -861,7 +805,7 @@ hipError_t build_tile_nlist(const double* x, const double* y, const double* z,
     hipLaunchKernelGGL((k_build_tile_nlist<TileShared32, false, true, 3, false>), dim3(grid.x, parts),
                        dim3(cells * 3 * 64), 0, st, x, y, z, cell_start, g, r2, guard, tl,
                        flags, maxcount, cells);
-  else if (lane_threads && a24)
+  else if (lane_threads && list_offsets_32(tl.stride * 8))
     hipLaunchKernelGGL((k_build_tile_nlist<TileShared32, false, true, 1, true>), dim3(grid.x, lane_parts),
                        dim3(lane_threads), 0, st, x, y, z, cell_start, g, r2, lane_guard, tl, flags,
                        maxcount, lane_cells);
