@@ -139,11 +139,12 @@ struct Screen {
     int z2 = cz + row / 3 - 1, y2 = cy + row % 3 - 1;
     z2 += z2 < 0 ? n2 : (z2 >= n2 ? -n2 : 0);
     y2 += y2 < 0 ? n1 : (y2 >= n1 ? -n1 : 0);
-    const uint32_t first = (uint32_t)((z2 * n1 + y2) * n0);
+    // (64-bit offsets: a grid may have 2^30 cells, and cs one entry more)
+    const int32_t* const row0 = q.cs + (z2 * n1 + y2) * n0;
     t = e = 0;
     if (wrap ? edge : ok) {
-      t = at32(q.cs, first + (wrap ? wc : lo));
-      e = at32(q.cs, first + (wrap ? wc : hi) + 1);
+      t = row0[wrap ? wc : lo];
+      e = row0[(wrap ? wc : hi) + 1];
     }
   }
   __device__ __forceinline__ bool run() {
