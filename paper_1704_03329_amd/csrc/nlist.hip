@@ -54,7 +54,9 @@ namespace mdpl {
 // conditional minimum image on the stored FP64 positions).  The list is
 // therefore bit-identical to the all-pairs definition.
 constexpr float kFarF = 1e30f;  // dummy slot: its d2f overflows to +inf
-constexpr float kFarLane = 1e15f;  // out of reach, but its square is finite
+// Out of reach, and its square is finite: 2^50, so that the terms of two such
+// particles cancel without rounding and leave the pair to the exact test.
+constexpr float kFarLane = 1125899906842624.0f;
 constexpr int kBuildWant = 512;  // workgroups of a build that shares its bricks
 constexpr int kLaneThreads = 512;
 
