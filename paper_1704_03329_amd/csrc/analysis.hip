@@ -165,7 +165,8 @@ struct Screen {
           const float d2 = __builtin_fmaf(az, az, __builtin_fmaf(ay, ay, ax * ax));
           // written whether noted or not: the next note overwrites it
           col[(KEEP && cnt >= CAP ? CAP - 1 : cnt) * kQPitch] = u + j;
-          cnt += (int)((d2 <= r2) & (left > j) & (self != j));
+          // (a copy that is NaN is noted: only the exact test can tell)
+          cnt += (int)(!(d2 > r2) & (left > j) & (self != j));
         }
         t += 4;
       }
@@ -363,9 +364,9 @@ __device__ __forceinline__ void sort_network(uint32_t (&c)[N]) {
 // box.  Returns the bond count, or -1 where the exact test of a pair
 // of neighbours is needed (nothing is written then, col stays as it was).
 template <int N>
-__device__ __forceinline__ int cna_lane(const BondScan& q, const Grid& g, double rc2, int s, int c,
-                                        uint32_t* __restrict__ col, const CnaOut& out,
-                                        bool unfolded) {
+__device__ __forceinline__ int cna_lane(const BondScan& q, const Grid& g, double rc2, float band,
+                                        int s, int c, uint32_t* __restrict__ col,
+                                        const CnaOut& out, bool unfolded) {
   const double xi = q.sx[s], yi = q.sy[s], zi = q.sz[s];
   // N(i): the exact bond test of every noted candidate, four loaded at once
   // (more would only cost registers)
@@ -403,8 +404,8 @@ __device__ __forceinline__ int cna_lane(const BondScan& q, const Grid& g, double
   // The members bonded to each other, from the FP32 separations (each
   // component within 2^-24 rc of the FP64 one, their difference within 3 2^-24
   // rc, so that a squared distance near rc^2 is within (6 sqrt(3) + 4) 2^-24
-  // rc^2 < 9 10^-7 rc^2 of the exact one).  A pair within 2 10^-6 rc^2 of the
-  // cutoff needs the exact test, as do positions outside
+  // rc^2 < 9 10^-7 rc^2 of the exact one).  A pair within band = 2 10^-6 rc^2 of
+  // the cutoff needs the exact test, as do positions outside
   // the box (whose images the conditional wrap of the definition may miss).
   const float r2 = (float)rc2;
   // Every member takes the sign bits of its pairs one by one, partners in
@@ -430,7 +431,7 @@ __device__ __forceinline__ int cna_lane(const BondScan& q, const Grid& g, double
   // would all have to live until then)
 #pragma unroll
   for (int k = 0; k < N; ++k) asm volatile("" : "+v"(adj[k]));
-  if (near <= 2e-6f * r2 || odd) return -1;
+  if (near <= band || odd) return -1;
   // the masks in the lane's column: row b is bond b's common neighbours until
   // its triplet replaces them
 #pragma unroll
@@ -656,7 +657,7 @@ __device__ inline void cna_wave(const BondScan& q, const Grid& g, double rc2, in
 // lists and graphs kept most lanes waiting.
 constexpr int kCnaThreads = 256;
 __global__ __launch_bounds__(kCnaThreads) __attribute__((amdgpu_waves_per_eu(3)))
-void k_cna(BondScan q, int64_t n, Grid g, double rc2, float r2s, CnaOut out,
+void k_cna(BondScan q, int64_t n, Grid g, double rc2, float r2s, float band, CnaOut out,
            const int32_t* __restrict__ outside, int32_t* __restrict__ maxcount) {
   __shared__ uint32_t queue[kCnaThreads / 64][kCnaQueue * kQPitch];
   __shared__ uint32_t lists[kCnaThreads / 64][64];
@@ -675,11 +676,11 @@ void k_cna(BondScan q, int64_t n, Grid g, double rc2, float r2s, CnaOut out,
   const bool unfolded = *outside != 0;
   int ni = -1;
   if (mine) {
-    if (cm <= 12) ni = cna_lane<12>(q, g, rc2, s, c, wq + lane, out, unfolded);
-    else if (cm <= 14) ni = cna_lane<14>(q, g, rc2, s, c, wq + lane, out, unfolded);
-    else if (cm <= 18) ni = cna_lane<18>(q, g, rc2, s, c, wq + lane, out, unfolded);
-    else if (cm <= 24) ni = cna_lane<24>(q, g, rc2, s, c, wq + lane, out, unfolded);
-    else ni = cna_lane<kCnaQueue>(q, g, rc2, s, c, wq + lane, out, unfolded);
+    if (cm <= 12) ni = cna_lane<12>(q, g, rc2, band, s, c, wq + lane, out, unfolded);
+    else if (cm <= 14) ni = cna_lane<14>(q, g, rc2, band, s, c, wq + lane, out, unfolded);
+    else if (cm <= 18) ni = cna_lane<18>(q, g, rc2, band, s, c, wq + lane, out, unfolded);
+    else if (cm <= 24) ni = cna_lane<24>(q, g, rc2, band, s, c, wq + lane, out, unfolded);
+    else ni = cna_lane<kCnaQueue>(q, g, rc2, band, s, c, wq + lane, out, unfolded);
   }
   int most = ni > 0 ? ni : 0;
   uint64_t todo = __ballot(ok && ni < 0);
@@ -707,8 +708,10 @@ hipError_t cna_signatures(const BondScan& q, int64_t n, const Grid& g, double rc
                           uint32_t* trip, int32_t* nnb, uint8_t* label, const int32_t* outside,
                           int32_t* maxcount, hipStream_t st) {
   const CnaOut out{trip, nnb, label, max_nb, max_nb % 4 == 0 && ((uintptr_t)trip & 15) == 0};
+  // (what the FP32 pairs cannot decide is left to the exact test)
+  const float band = screen_fits(g, sqrt(rc2)) ? 2e-6f * (float)rc2 : 3.4e38f;
   hipLaunchKernelGGL(k_cna, dim3((unsigned)div_up(n, kCnaThreads)), dim3(kCnaThreads), 0, st, q, n,
-                     g, rc2, screen_r2(g, rc2), out, outside, maxcount);
+                     g, rc2, screen_r2(g, rc2), band, out, outside, maxcount);
   return hipGetLastError();
 }
 

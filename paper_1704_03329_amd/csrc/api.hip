@@ -1078,7 +1078,7 @@ static mdpl_status analysis_prep(const double* x, const double* y, const double*
   double* sz = take<double>(w, 8 * (size_t)n);
   *small = take<int32_t>(w, 64);
   int32_t *skeys, *perm;
-  HIP_TRY(sort_analysis(x, y, z, n, *g, sb, cs, &skeys, &perm, sx, sy, sz, f0, f1, f2, *small, st));
+  HIP_TRY(sort_analysis(x, y, z, n, *g, sb, cs, &skeys, &perm, sx, sy, sz, f0, f1, f2, *small, rc, st));
   *q = BondScan{sx, sy, sz, f0, f1, f2, skeys, cs, perm};
   return MDPL_OK;
 }

@@ -813,6 +813,7 @@ struct MoveAnalysis {
   float *px, *py, *pz;
   int32_t *perm, *outside;
   double L[3];
+  double reach;  // see sort_analysis
   __device__ __forceinline__ void operator()(int64_t s, int32_t j) const {
     const double a = x[j], b = y[j], c = z[j];
     const double fa = fold(a, L[0]), fb = fold(b, L[1]), fc = fold(c, L[2]);
@@ -820,7 +821,9 @@ struct MoveAnalysis {
     ox[s] = a;
     oy[s] = b;
     oz[s] = c;
-    px[s] = (float)fa;
+    const bool near = __builtin_fabs(a) <= reach * L[0] && __builtin_fabs(b) <= reach * L[1] &&
+                      __builtin_fabs(c) <= reach * L[2];
+    px[s] = near ? (float)fa : __builtin_nanf("");
     py[s] = (float)fb;
     pz[s] = (float)fc;
     if (fa != a || fb != b || fc != c) *outside = 1;
@@ -830,11 +833,12 @@ struct MoveAnalysis {
 hipError_t sort_analysis(const double* x, const double* y, const double* z, int64_t n,
                          const Grid& g, SortBufs& s, int32_t* cell_start, int32_t** skeys,
                          int32_t** perm, double* ox, double* oy, double* oz, float* px, float* py,
-                         float* pz, int32_t* small, hipStream_t st) {
+                         float* pz, int32_t* small, double rc, hipStream_t st) {
   // the values' second buffer: free again when the move writes it (the radix
   // path may have sorted the values into it: each slot reads its own first)
   *perm = s.vals[0];
-  const MoveAnalysis m{x, y, z, ox, oy, oz, px, py, pz, *perm, small, {g.box[0], g.box[1], g.box[2]}};
+  const MoveAnalysis m{x, y, z, ox, oy, oz, px, py, pz, *perm, small, {g.box[0], g.box[1], g.box[2]},
+                       screen_fits(g, rc) ? 1048576.0 : -1.0};
   return sort_and_move(x, y, z, n, g, s, cell_start, nullptr, small, skeys, m, MoveCheck{}, st);
 }
 

@@ -103,13 +103,22 @@ hipError_t skin_check(const MoveCheck& mc, int64_t n, hipStream_t st);
 hipError_t sort_build(const double* x, const double* y, const double* z, int64_t n, const Grid& g,
                       SortBufs& s, int32_t* cell_start, int32_t* xlow, int32_t** skeys,
                       int32_t* perm, double* ox, double* oy, double* oz, hipStream_t st);
+// Whether FP32 holds the analyses' coordinates and their squares (the
+// definition's FP64 test is all that is left where it does not).
+inline bool screen_fits(const Grid& g, double rc) {
+  double m = 0.0;
+  for (int k = 0; k < 3; ++k) m = g.box[k] > m ? g.box[k] : m;
+  return rc > 1e-15 && rc < 1e15 && m < 1e18;
+}
 // Analyses: positions as stored, FP32 copies folded into the box, keys and
 // caller indices in the sort buffers; small (16 words) is cleared, word 0
-// then set if folding moved any position.
+// then set if folding moved any position.  px is NaN where the copy would not
+// do: FP32 does not fit the cutoff rc, or the position is more than 2^20
+// boxes away, where folding rounds by more than 2^-32 of the box.
 hipError_t sort_analysis(const double* x, const double* y, const double* z, int64_t n,
                          const Grid& g, SortBufs& s, int32_t* cell_start, int32_t** skeys,
                          int32_t** perm, double* ox, double* oy, double* oz, float* px, float* py,
-                         float* pz, int32_t* small, hipStream_t st);
+                         float* pz, int32_t* small, double rc, hipStream_t st);
 // Runs: all ten arrays, positions folded and copied to xb, yb, zb; *bound
 // becomes zero; mc: the displacement check, made before xb changes.
 hipError_t sort_state(const StateArrays& src, const StateArrays& dst, int64_t n, int fbytes,
