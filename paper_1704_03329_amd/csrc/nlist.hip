@@ -786,7 +786,9 @@ hipError_t build_tile_nlist(const double* x, const double* y, const double* z,
   const bool small_bricks = g.V <= 8;
   unsigned lane_threads = 0;
   int lane_cells = g.V, lane_parts = 1;
-  if (full >= 10 * (int64_t)g.V && full <= 48 * (int64_t)g.V) {
+  // (and lengths whose squares are far from those of kFarLane and of FP32's least)
+  const bool lengths = span < 0x1p36 && rext > 0x1p-36;
+  if (lengths && full >= 10 * (int64_t)g.V && full <= 48 * (int64_t)g.V) {
     lane_cells = (int)div_up(g.V, brick_parts(g, small_bricks ? kBuildWant : kBuildWant / 2, g.V));
     lane_parts = (int)div_up(g.V, lane_cells);
     lane_threads = (unsigned)div_up(full * 6 / 5 * lane_cells / g.V, 64) * 64;
