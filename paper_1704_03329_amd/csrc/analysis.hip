@@ -31,6 +31,7 @@
 
 #include "device_util.h"
 #include "internal.h"
+#include "bond_screen.h"
 
 namespace mdpl {
 
@@ -47,7 +48,7 @@ __device__ __forceinline__ T at32(const T* __restrict__ a, uint32_t i) {
   return ((const T*)((const char*)a + i * (uint32_t)sizeof(T)))[J];
 }
 
-// The definition's minimum-image separation (exact_sep) of candidates that
+// The definition's minimum-image separation (of exact_d2) of candidates that
 // rarely need the wrap: it is formed only where a lane of the wave does.
 __device__ __forceinline__ double bond_sep(double xi, double yi, double zi, double xj, double yj,
                                            double zj, const Grid& g, double& dx, double& dy,
@@ -63,25 +64,6 @@ __device__ __forceinline__ double bond_sep(double xi, double yi, double zi, doub
     dz = dz > hz ? dz - Lz : (dz < -hz ? dz + Lz : dz);
   }
   return sq_sum(dx, dy, dz);
-}
-
-// FP32 distance bound of the screen.  Coordinates |X| < M = 2^p (2^p above
-// every box edge plus one cell, at most a third of an edge) are within
-// 2^(p-25) of their FP64 values (fold and shift add their rounding, some
-// 1e-16 M, covered by the factor 2 below), so that a separation component
-// below 2 rc is within D = 2^(p-24) + 2^-24 2 rc, and the FP32 squared
-// distance of a bond within e = 2 sqrt(3) rc D + 3 D^2 + 4 2^-24 rc^2 of the
-// exact one.  Candidates up to rc^2 + 2 e are noted.
-static float screen_r2(const Grid& g, double rc2) {
-  double m = 0.0;
-  for (int k = 0; k < 3; ++k) {
-    const double e = g.box[k] + g.side[k];
-    m = e > m ? e : m;
-  }
-  const double ulp = 1.0 / 16777216.0, rc = sqrt(rc2);  // 2^-24
-  const double d = exp2(ceil(log2(m * (1.0 + 1e-9)))) * ulp + 2.0 * rc * ulp;
-  const double err = 2.0 * sqrt(3.0) * rc * d + 3.0 * d * d + 4.0 * ulp * rc2;
-  return nextafterf((float)(rc2 + 2.0 * err), 3.0e38f);
 }
 
 // The screen of one particle per lane over its nine stencil rows.  A row's
@@ -119,17 +101,16 @@ struct Screen {
     rows = 9 * per;
     // the cell across the edge and the particle's image next to it
     wc = cx == 0 ? n0 - 1 : 0;
-    xw = cx == 0 ? x + (float)g.box[0] : x - (float)g.box[0];
+    xw = screen_image(x, g.box[0], cx == 0 ? -1 : 1);
     range();
   }
   // y and z images of the particle next to row r
   __device__ __forceinline__ void image(float& xs, float& ys, float& zs) const {
     const int row = per == 2 ? r >> 1 : r;
     const int z2 = cz + row / 3 - 1, y2 = cy + row % 3 - 1;
-    const float Ly = (float)g.box[1], Lz = (float)g.box[2];
     xs = per == 2 && (r & 1) ? xw : x;
-    ys = y2 < 0 ? y + Ly : (y2 >= g.nc[1] ? y - Ly : y);
-    zs = z2 < 0 ? z + Lz : (z2 >= g.nc[2] ? z - Lz : z);
+    ys = screen_image(y, g.box[1], y2 < 0 ? -1 : (y2 >= g.nc[1] ? 1 : 0));
+    zs = screen_image(z, g.box[2], z2 < 0 ? -1 : (z2 >= g.nc[2] ? 1 : 0));
   }
   // candidates [t, e) of row r
   __device__ __forceinline__ void range() {
@@ -161,8 +142,7 @@ struct Screen {
         const int left = e - t, self = s - t;
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-          const float ax = xs - dx[j], ay = ys - dy[j], az = zs - dz[j];
-          const float d2 = __builtin_fmaf(az, az, __builtin_fmaf(ay, ay, ax * ax));
+          const float d2 = screen_d2(xs - dx[j], ys - dy[j], zs - dz[j]);
           // written whether noted or not: the next note overwrites it
           col[(KEEP && cnt >= CAP ? CAP - 1 : cnt) * kQPitch] = u + j;
           // (a copy that is NaN is noted: only the exact test can tell)
@@ -306,7 +286,7 @@ __global__ __launch_bounds__(kBoaThreads) void k_boa(BondScan q, int64_t n, Grid
 hipError_t boa_q(const BondScan& q, int64_t n, const Grid& g, double rc2, float* q4, float* q5,
                  float* q6, int32_t* nnb, hipStream_t st) {
   const dim3 grid((unsigned)div_up(n, kBoaThreads)), block(kBoaThreads);
-  const float r2s = screen_r2(g, rc2);
+  const float r2s = screen_r2(g.box, g.side, rc2);
   if (q5)
     hipLaunchKernelGGL(k_boa<true>, grid, block, 0, st, q, n, g, rc2, r2s, q4, q5, q6, nnb);
   else
@@ -711,7 +691,7 @@ hipError_t cna_signatures(const BondScan& q, int64_t n, const Grid& g, double rc
   // (what the FP32 pairs cannot decide is left to the exact test)
   const float band = screen_fits(g, sqrt(rc2)) ? 2e-6f * (float)rc2 : 3.4e38f;
   hipLaunchKernelGGL(k_cna, dim3((unsigned)div_up(n, kCnaThreads)), dim3(kCnaThreads), 0, st, q, n,
-                     g, rc2, screen_r2(g, rc2), band, out, outside, maxcount);
+                     g, rc2, screen_r2(g.box, g.side, rc2), band, out, outside, maxcount);
   return hipGetLastError();
 }
 

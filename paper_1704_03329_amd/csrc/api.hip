@@ -753,7 +753,7 @@ mdpl_status wait_record(mdpl_sim* s, int64_t target) {
 // still flags a list used too long).  Draining the stream leaves the GPU idle
 // for some 25 us: in hot fluids the prediction from far behind reached the
 // threshold at the end of every reuse period (N = 125,000 under the bath: 6
-// drains in 36 steps, 1889 -> @RA@ us; N = 4096: 9 in 100, 16.6 -> @R4@ us a step).
+// drains in 36 steps; N = 4096: 9 in 100, now none, 16.6 -> 15.2 us a step).
 mdpl_status rule_decide(mdpl_sim* s, bool* need) {
   const int64_t k = s->gstep;
   const double dt = s->p.dt, skin = s->p.skin;

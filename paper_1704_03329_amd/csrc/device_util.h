@@ -55,24 +55,6 @@ __device__ __forceinline__ double exact_d2(double xi, double yi, double zi, doub
   return (dx * dx + dy * dy) + dz * dz;
 }
 
-// Same, also returning the separation vector.
-__device__ __forceinline__ double exact_sep(double xi, double yi, double zi, double xj, double yj,
-                                            double zj, double Lx, double Ly, double Lz, double hx,
-                                            double hy, double hz, double& dx, double& dy,
-                                            double& dz) {
-#pragma clang fp contract(off)
-  dx = xi - xj;
-  if (dx > hx) dx = dx - Lx;
-  else if (dx < -hx) dx = dx + Lx;
-  dy = yi - yj;
-  if (dy > hy) dy = dy - Ly;
-  else if (dy < -hy) dy = dy + Ly;
-  dz = zi - zj;
-  if (dz > hz) dz = dz - Lz;
-  else if (dz < -hz) dz = dz + Lz;
-  return (dx * dx + dy * dy) + dz * dz;
-}
-
 // (dx*dx + dy*dy) + dz*dz with each operation rounded (no contraction)
 __device__ __forceinline__ double sq_sum(double dx, double dy, double dz) {
 #pragma clang fp contract(off)
