@@ -316,6 +316,13 @@ struct CnaOut {
   int quads;   // 1: the rows of trip are 16-byte aligned
 };
 
+// Whether a position lies more than a quarter of the box outside it: two that
+// do not are at most 1.5 edges apart, and the definition's one wrap finds the
+// nearest image.
+__device__ __forceinline__ bool far_image(const Grid& g, double x, double y, double z) {
+  return !(within_reach(x, g.box[0]) && within_reach(y, g.box[1]) && within_reach(z, g.box[2]));
+}
+
 // All ones where bit m of v is set, else zero.
 __device__ __forceinline__ uint32_t bit_mask(uint32_t v, int m) {
   return (uint32_t)((int32_t)(v << (31 - m)) >> 31);
@@ -347,8 +354,8 @@ __device__ __forceinline__ void sort_network(uint32_t (&c)[N]) {
 
 // The signature of one particle per lane, up to N noted candidates each
 // (col[0 .. c), N a constant so that separations and masks stay in
-// registers); unfolded: some particle's stored position lies outside the
-// box.  Returns the bond count, or -1 where the exact test of a pair
+// registers); unfolded: some particle's stored position lies far outside the
+// box (far_image).  Returns the bond count, or -1 where the exact test of a pair
 // of neighbours is needed (nothing is written then, col stays as it was).
 template <int N>
 __device__ __forceinline__ int cna_lane(const BondScan& q, const Grid& g, double rc2, float band,
@@ -379,9 +386,7 @@ __device__ __forceinline__ int cna_lane(const BondScan& q, const Grid& g, double
       const double d2 = bond_sep(xi, yi, zi, xt[j], yt[j], zt[j], g, dx, dy, dz);
       const bool bond = (k < c) & (d2 < rc2);
       bonds |= bond ? 1u << k : 0u;
-      if (unfolded)
-        odd |= bond & !((xt[j] >= 0.0) & (xt[j] < g.box[0]) & (yt[j] >= 0.0) &
-                        (yt[j] < g.box[1]) & (zt[j] >= 0.0) & (zt[j] < g.box[2]));
+      if (unfolded) odd |= bond & far_image(g, xt[j], yt[j], zt[j]);
       X[k] = bond ? (float)dx : 1e18f;
       Y[k] = bond ? (float)dy : 1e18f;
       Z[k] = bond ? (float)dz : 1e18f;
@@ -392,7 +397,7 @@ __device__ __forceinline__ int cna_lane(const BondScan& q, const Grid& g, double
   // component within 2^-24 rc of the FP64 one, their difference within 3 2^-24
   // rc, so that a squared distance near rc^2 is within (6 sqrt(3) + 4) 2^-24
   // rc^2 < 9 10^-7 rc^2 of the exact one).  A pair within band = 2 10^-6 rc^2 of
-  // the cutoff needs the exact test, as do positions outside
+  // the cutoff needs the exact test, as do positions far outside
   // the box (whose images the conditional wrap of the definition may miss).
   const float r2 = (float)rc2;
   // Every member takes the sign bits of its pairs one by one, partners in
@@ -566,71 +571,132 @@ __device__ inline int bonds_noted(const BondScan& q, const Grid& g, double rc2, 
   return __popcll(m);
 }
 
+// Bit m of the 64-bit mask (lo, hi), all ones where it is set.
+__device__ __forceinline__ uint32_t bit_mask64(uint32_t lo, uint32_t hi, int m) {
+  return bit_mask(m < 32 ? lo : hi, m & 31);
+}
+
 // The signature of slot s by the whole wave, lane b its bond b (ni <= 64 of
-// them, slots in list), every pair of neighbours by the exact test.
-__device__ inline void cna_wave(const BondScan& q, const Grid& g, double rc2, int s, int ni,
-                                const uint32_t* __restrict__ list, const CnaOut& out) {
+// them, slots in list).  Members of the loops are the same for all lanes, so
+// that their values come by v_readlane.  The pairs of neighbours as in
+// cna_lane, all of them by the exact test where that leaves one open.
+// Fcc of 108,000 atoms with 41 bonds each 2160 -> 1066 us, fluid with 55 2830
+// -> 1370 (every value by a shuffle, every pair by the exact test).
+__device__ inline void cna_wave(const BondScan& q, const Grid& g, double rc2, float band, int s,
+                                int ni, const uint32_t* __restrict__ list, const CnaOut& out,
+                                bool unfolded) {
   const int b = (int)threadIdx.x & 63;
   const bool bond = b < ni;
-  const double Lx = g.box[0], Ly = g.box[1], Lz = g.box[2];
   const uint32_t t = bond ? list[b] : (uint32_t)s;
   const double xt = q.sx[t], yt = q.sy[t], zt = q.sz[t];
-  uint64_t adj = 0;
-  for (int m = 0; m < ni; ++m) {
-    const double x2 = __shfl(xt, m, 64), y2 = __shfl(yt, m, 64), z2 = __shfl(zt, m, 64);
-    const bool in = exact_d2(x2, y2, z2, xt, yt, zt, Lx, Ly, Lz, 0.5 * Lx, 0.5 * Ly, 0.5 * Lz) < rc2;
-    adj |= in && bond && m != b ? 1ull << m : 0ull;
+  double dx, dy, dz;
+  (void)bond_sep(q.sx[s], q.sy[s], q.sz[s], xt, yt, zt, g, dx, dy, dz);
+  const float X = bond ? (float)dx : 1e18f, Y = bond ? (float)dy : 1e18f;
+  const float Z = bond ? (float)dz : 1e18f, r2 = (float)rc2;
+  auto lane_f = [](float v, int m) {
+    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), m));
+  };
+  uint32_t lo = 0, hi = 0;  // bit m: bonded to member m
+  float near = 3e38f;
+  for (int m = ni - 1; m >= 0; --m) {
+    const float ax = X - lane_f(X, m), ay = Y - lane_f(Y, m), az = Z - lane_f(Z, m);
+    const float e = __builtin_fmaf(az, az, __builtin_fmaf(ay, ay, __builtin_fmaf(ax, ax, -r2)));
+    near = fminf(near, __builtin_fabsf(e));  // (the member itself: r2)
+    hi = __builtin_amdgcn_alignbit(hi, lo, 31);
+    lo = __builtin_amdgcn_alignbit(lo, __float_as_uint(e), 31);
   }
-  // degree sum inside C = adj of the members in `of`, and the members reached
-  auto sweep = [&](uint64_t of, uint64_t& reach) {
+  if (__any(bond & ((near <= band) | (unfolded && far_image(g, xt, yt, zt))))) {
+    const double Lx = g.box[0], Ly = g.box[1], Lz = g.box[2];
+    uint64_t adj = 0;
+    for (int m = 0; m < ni; ++m) {
+      const double x2 = __shfl(xt, m, 64), y2 = __shfl(yt, m, 64), z2 = __shfl(zt, m, 64);
+      const bool in =
+          exact_d2(x2, y2, z2, xt, yt, zt, Lx, Ly, Lz, 0.5 * Lx, 0.5 * Ly, 0.5 * Lz) < rc2;
+      adj |= in ? 1ull << m : 0ull;
+    }
+    lo = (uint32_t)adj;
+    hi = (uint32_t)(adj >> 32);
+  }
+  lo &= bond ? ~(b < 32 ? 1u << b : 0u) : 0u;
+  hi &= bond ? ~(b >= 32 ? 1u << (b - 32) : 0u) : 0u;
+  // over the members m of the mask (olo, ohi), with C the lane's common
+  // neighbours: what m is bonded to in C, and the bonds counted from m's end
+  auto sweep = [&](uint32_t& olo, uint32_t& ohi, uint32_t& rlo, uint32_t& rhi) {
     int deg = 0;
     for (int m = 0; m < ni; ++m) {
-      const uint64_t in = (uint64_t)__shfl((unsigned long long)adj, m, 64) & adj;
-      if ((of >> m) & 1) {
-        deg += __popcll(in);
-        reach |= in;
-      }
+      const uint32_t of = bit_mask64(olo, ohi, m);
+      const uint32_t ilo = (uint32_t)__builtin_amdgcn_readlane((int)lo, m) & lo & of;
+      const uint32_t ihi = (uint32_t)__builtin_amdgcn_readlane((int)hi, m) & hi & of;
+      deg += __popc(ilo) + __popc(ihi);
+      rlo |= ilo;
+      rhi |= ihi;
     }
     return deg;
   };
-  uint64_t ends = 0;
-  const int deg = sweep(adj, ends), nb = deg >> 1;
-  uint64_t rem = ends;
-  int best = 0;
-  while (__any(rem != 0)) {
-    uint64_t comp = rem & (~rem + 1);
-    int e2 = 0;
-    bool grows = rem != 0;
+  uint32_t elo = 0, ehi = 0;  // members of C with a bond inside C
+  const int deg = sweep(lo, hi, elo, ehi), nb = deg >> 1, v = __popc(elo) + __popc(ehi);
+  int best = nb == 2 && v == 4 ? 1 : nb;
+  // three or more edges on up to four members are connected
+  const bool open = nb > 2 && v > 4;
+  uint32_t remlo = open ? elo : 0u, remhi = open ? ehi : 0u;
+  if (open) best = 0;
+  while (__any((remlo | remhi) != 0)) {
+    // the component of the lowest member left, grown within each sweep too
+    uint32_t clo = remlo & (~remlo + 1), chi = remlo ? 0u : remhi & (~remhi + 1);
+    bool grows = (clo | chi) != 0;
     while (__any(grows)) {
-      uint64_t next = comp;
-      e2 = sweep(comp, next);
-      grows = next != comp;
-      comp = next;
+      const uint32_t before_lo = clo, before_hi = chi;
+      (void)sweep(clo, chi, clo, chi);
+      grows = (clo != before_lo || chi != before_hi) && (clo != remlo || chi != remhi);
     }
-    best = (e2 >> 1) > best ? e2 >> 1 : best;
-    rem &= ~comp;
+    const bool part = clo != elo || chi != ehi;
+    int e2 = part ? 0 : deg;
+    if (__any(part && (clo | chi))) {
+      uint32_t unused_lo = 0, unused_hi = 0;
+      const int some = sweep(clo, chi, unused_lo, unused_hi);
+      e2 = part ? some : deg;
+    }
+    best = open && (e2 >> 1) > best ? e2 >> 1 : best;
+    remlo &= ~clo;
+    remhi &= ~chi;
   }
-  const uint32_t code = pack_triplet(__popcll(adj), nb, best);
-  int rank = 0;  // the number of smaller (code, lane) pairs
-  for (int m = 0; m < ni; ++m) {
-    const uint32_t c = __shfl(code, m, 64);
-    rank += c < code || (c == code && m < b) ? 1 : 0;
-  }
+  const uint32_t code = pack_triplet(__popc(lo) + __popc(hi), nb, best);
+  const uint32_t key = code << 6 | (uint32_t)b;  // (a count is at most 63: 26 bits and 6)
+  int rank = 0;
+  for (int m = 0; m < ni; ++m)
+    rank += (uint32_t)__builtin_amdgcn_readlane((int)key, m) < key ? 1 : 0;
   const int c421 = __popcll(__ballot(bond && code == pack_triplet(4, 2, 1)));
   const int c422 = __popcll(__ballot(bond && code == pack_triplet(4, 2, 2)));
   const int c444 = __popcll(__ballot(bond && code == pack_triplet(4, 4, 4)));
   const int c666 = __popcll(__ballot(bond && code == pack_triplet(6, 6, 6)));
   const int32_t o = q.perm[s];
-  const bool all = ni <= out.max_nb;
-  if (bond && all) out.trip[(int64_t)o * out.max_nb + rank] = code;
+  if (bond) out.trip[(int64_t)o * out.max_nb + rank] = code;
   if (b == 0) {
     uint8_t lab = 0;
     if (ni == 12 && c421 == 12) lab = 1;
     else if (ni == 12 && c421 == 6 && c422 == 6) lab = 2;
     else if (ni == 14 && c666 == 8 && c444 == 6) lab = 3;
-    out.label[o] = all ? lab : 0;
+    out.label[o] = lab;
     out.nnb[o] = ni;
   }
+}
+
+// The bonds of the lane's particle, counted: the screen's candidates in turns
+// of a column each.
+__device__ inline int count_bonds(const BondScan& q, const Grid& g, double rc2, float r2s, int s,
+                                  uint32_t* __restrict__ col) {
+  const double xi = q.sx[s], yi = q.sy[s], zi = q.sz[s];
+  Screen<kCnaQueue, false> screen(q, g, s, true, r2s, col);
+  int found = 0;
+  for (bool done = false; !done; screen.cnt = 0) {
+    done = screen.run();
+    for (int k = 0; k < screen.cnt; ++k) {
+      const uint32_t t = col[k * kQPitch];
+      double dx, dy, dz;
+      found += bond_sep(xi, yi, zi, at32(q.sx, t), at32(q.sy, t), at32(q.sz, t), g, dx, dy, dz) < rc2;
+    }
+  }
+  return found;
 }
 
 // A particle per lane: the screen, then the signatures with the wave's
@@ -642,17 +708,20 @@ __device__ inline void cna_wave(const BondScan& q, const Grid& g, double rc2, in
 // polycrystal: 1029 us against 3492 us for a list in memory (1079) and one
 // lane per particle with its masks in LDS (2413), whose loops over ragged
 // lists and graphs kept most lanes waiting.
+// Where many lanes have a full column and the capacity is no larger, nearly
+// all of them have too many bonds for a signature: counted side by side first.
+constexpr int kCountLanes = 16;  // a count costs about 13 particles' turns of the wave
 constexpr int kCnaThreads = 256;
 __global__ __launch_bounds__(kCnaThreads) __attribute__((amdgpu_waves_per_eu(3)))
-void k_cna(BondScan q, int64_t n, Grid g, double rc2, float r2s, float band, CnaOut out,
+void k_cna(BondScan q, int64_t n, int per, Grid g, double rc2, float r2s, float band, CnaOut out,
            const int32_t* __restrict__ outside, int32_t* __restrict__ maxcount) {
   __shared__ uint32_t queue[kCnaThreads / 64][kCnaQueue * kQPitch];
   __shared__ uint32_t lists[kCnaThreads / 64][64];
   const int lane = (int)threadIdx.x & 63;
-  const int base = (int)(blockIdx.x * kCnaThreads + ((int)threadIdx.x & ~63));
+  const int base = (int)(blockIdx.x * (kCnaThreads / 64) + (threadIdx.x >> 6)) * per;
   if (base >= n) return;
   const int s = base + lane;
-  const bool ok = s < n;
+  const bool ok = lane < per && s < n;
   uint32_t* const wq = queue[threadIdx.x >> 6];
   Screen<kCnaQueue, true> screen(q, g, s, ok, r2s, wq + lane);
   (void)screen.run();
@@ -669,6 +738,16 @@ void k_cna(BondScan q, int64_t n, Grid g, double rc2, float r2s, float band, Cna
     else if (cm <= 24) ni = cna_lane<24>(q, g, rc2, band, s, c, wq + lane, out, unfolded);
     else ni = cna_lane<kCnaQueue>(q, g, rc2, band, s, c, wq + lane, out, unfolded);
   }
+  if (out.max_nb <= kCnaQueue && __popcll(__ballot(ok && !mine)) >= kCountLanes) {
+    if (ok && !mine) {
+      const int found = count_bonds(q, g, rc2, r2s, s, wq + lane);
+      if (found > out.max_nb) {  // no triplets, no signature
+        const int32_t o = q.perm[s];
+        out.nnb[o] = ni = found;
+        out.label[o] = 0;
+      }
+    }
+  }
   int most = ni > 0 ? ni : 0;
   uint64_t todo = __ballot(ok && ni < 0);
   while (todo) {
@@ -678,9 +757,9 @@ void k_cna(BondScan q, int64_t n, Grid g, double rc2, float r2s, float band, Cna
     uint32_t* const list = lists[threadIdx.x >> 6];
     const int nw = cp < kCnaQueue ? bonds_noted(q, g, rc2, base + p, cp, wq + p, list)
                                   : bonds_of(q, g, rc2, base + p, list);
-    if (nw <= 64) {
-      cna_wave(q, g, rc2, base + p, nw, list, out);
-    } else if (lane == 0) {
+    if (nw <= out.max_nb) {  // (of at most 64)
+      cna_wave(q, g, rc2, band, base + p, nw, list, out, unfolded);
+    } else if (lane == 0) {  // the list is incomplete: no triplets, no signature
       const int32_t o = q.perm[base + p];
       out.nnb[o] = nw;
       out.label[o] = 0;
@@ -697,8 +776,18 @@ hipError_t cna_signatures(const BondScan& q, int64_t n, const Grid& g, double rc
   const CnaOut out{trip, nnb, label, max_nb, max_nb % 4 == 0 && ((uintptr_t)trip & 15) == 0};
   // (what the FP32 pairs cannot decide is left to the exact test)
   const float band = screen_fits(g, sqrt(rc2)) ? 2e-6f * (float)rc2 : 3.4e38f;
-  hipLaunchKernelGGL(k_cna, dim3((unsigned)div_up(n, kCnaThreads)), dim3(kCnaThreads), 0, st, q, n,
-                     g, rc2, screen_r2(g.box, g.side, rc2), band, out, outside, maxcount);
+  // Particles of a wave: fewer where waves of 64 would not fill the chip (four
+  // SIMDs on each of 256 CUs) and most particles are expected to have a full
+  // column, so that their turns one after another set the time (864 atoms with
+  // 41 bonds 904 -> 163 us; with 19 bonds 64 lanes stay ahead, 79 against 121).
+  const double sites = (double)n / (g.box[0] * g.box[1] * g.box[2]);
+  const double expected = 4.19 * sites * rc2 * sqrt(rc2);
+  int per = 64;
+  while (expected > kCnaQueue && per > 8 && div_up(n, per) < 1024) per /= 2;
+  const int64_t waves = div_up(n, per);
+  hipLaunchKernelGGL(k_cna, dim3((unsigned)div_up(waves, kCnaThreads / 64)), dim3(kCnaThreads), 0,
+                     st, q, n, per, g, rc2, screen_r2(g.box, g.side, rc2), band, out, outside,
+                     maxcount);
   return hipGetLastError();
 }
 

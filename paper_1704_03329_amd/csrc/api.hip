@@ -1052,7 +1052,7 @@ static size_t analysis_bytes(int64_t n, const Grid& g, int max_nb) {
 }
 
 // Validates, carves the workspace, sorts the particles by cell and gathers
-// their positions; small: word 0 set if a position lies outside the box, word 1 zero.
+// their positions; small: word 0 set if a position is out of within_reach, word 1 zero.
 static mdpl_status analysis_prep(const double* x, const double* y, const double* z, int64_t n,
                                  const double* box, double rc, int max_nb, void* ws, size_t bytes,
                                  hipStream_t st, Grid* g, BondScan* q, int32_t** small) {

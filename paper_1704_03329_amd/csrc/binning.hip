@@ -826,7 +826,7 @@ struct MoveAnalysis {
     px[s] = near ? (float)fa : __builtin_nanf("");
     py[s] = (float)fb;
     pz[s] = (float)fc;
-    if (fa != a || fb != b || fc != c) *outside = 1;
+    if (!(within_reach(a, L[0]) && within_reach(b, L[1]) && within_reach(c, L[2]))) *outside = 1;
   }
 };
 

@@ -61,6 +61,11 @@ __device__ __forceinline__ double sq_sum(double dx, double dy, double dz) {
   return (dx * dx + dy * dy) + dz * dz;
 }
 
+// A coordinate at most a quarter of the box edge L outside the box.
+__device__ __forceinline__ bool within_reach(double x, double L) {
+  return x >= -0.25 * L && x <= 1.25 * L;
+}
+
 // Cross-lane moves on DPP (data-parallel primitives: a lane reads another
 // lane's register within the same instruction, no LDS round trip as with
 // __shfl).  CTRL: 0xB1 = quad_perm [1,0,3,2] (lane ^ 1), 0x4E = quad_perm

@@ -112,7 +112,7 @@ inline bool screen_fits(const Grid& g, double rc) {
 }
 // Analyses: positions as stored, FP32 copies folded into the box, keys and
 // caller indices in the sort buffers; small (16 words) is cleared, word 0
-// then set if folding moved any position.  px is NaN where the copy would not
+// then set if any position is out of within_reach.  px is NaN where the copy would not
 // do: FP32 does not fit the cutoff rc, or the position is more than 2^20
 // boxes away, where folding rounds by more than 2^-32 of the box.
 hipError_t sort_analysis(const double* x, const double* y, const double* z, int64_t n,
@@ -346,7 +346,7 @@ struct BondScan {
 };
 hipError_t boa_q(const BondScan& q, int64_t n, const Grid& g, double rc2, float* q4, float* q5,
                  float* q6, int32_t* nnb, hipStream_t st);
-// outside (device): not zero if a stored position lies outside the box;
+// outside (device): not zero if a stored position is out of within_reach;
 // maxcount (device, zero beforehand) receives the largest bond count.
 hipError_t cna_signatures(const BondScan& q, int64_t n, const Grid& g, double rc2, int max_nb,
                           uint32_t* trip, int32_t* nnb, uint8_t* label, const int32_t* outside,
