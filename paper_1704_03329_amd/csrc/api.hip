@@ -102,6 +102,7 @@ struct mdpl_sim {
   int pend_n;              // workgroups of the last drifting launch, its record not yet published (0: none)
   int64_t pend_step;       // the step index of that record
   int track_cur;           // slot of the next drifting launch's maxima
+  int force_groups;        // workgroups of the last force pass (launch_force)
   int64_t n_rebuilds, n_early, n_syncs;
 };
 
@@ -358,6 +359,7 @@ mdpl_status launch_force(mdpl_sim* s, const double* x, const double* y, const do
   }
   int nb = 0;
   HIP_TRY(lj_force(x, y, z, s->cell_start, s->g, s->tl, s->c, kind, energy, out, s->n, s->st, &nb));
+  s->force_groups = (s->g.order ? s->g.norder : ((s->g.nbricks + 7) / 8) * 8) * (nb / s->g.nbricks);
   if (e1) {
     HIP_TRY(hipEventRecord(e1, s->st));
     s->tm.ev[timing_slot].push_back(e0);
@@ -527,6 +529,7 @@ mdpl_status mdpl_sim_create(const mdpl_lj_params* p, void* workspace, size_t byt
   s->pend_n = 0;
   s->pend_step = 0;
   s->track_cur = 0;
+  s->force_groups = 0;
   hipError_t e = hipMemsetAsync(small, 0, 256, s->st);
   if (e != hipSuccess) {
     g_last_hip_error = (int32_t)e;
@@ -897,7 +900,6 @@ mdpl_status run_loop(mdpl_sim* s, StateArrays user, int64_t nsteps, int32_t samp
     s->pend_step = s->track.step;
     s->track_cur ^= 1;
   };
-  const int force_groups = (s->g.order ? s->g.norder : ((s->g.nbricks + 7) / 8) * 8) * s->tl.parts;
 
   mdpl_status r = MDPL_OK;
   if (!cont) {
@@ -967,7 +969,7 @@ mdpl_status run_loop(mdpl_sim* s, StateArrays user, int64_t nsteps, int32_t samp
               en ? row(step) : nullptr, en ? row(step) + 3 : nullptr);
     if (r != MDPL_OK) return r;
     if (fused) {
-      drifted(force_groups);
+      drifted(s->force_groups);
       swap_positions();
     }
   }

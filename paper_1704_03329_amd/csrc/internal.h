@@ -158,7 +158,7 @@ struct TileList {
   int64_t stride;   // words per group row (>= n)
   int max_nb;       // multiple of 4
   int threads;      // workgroup size of the tile kernels
-  int parts;        // workgroups per brick of the force passes and the descriptors (brick_parts)
+  int parts;        // most workgroups per brick of the force passes and the descriptors (brick_parts)
   int half;         // 1: each pair once (Newton's third law), tiles of kTileMaxHalf slots
   int cells;        // 1: no list; the pair loop scans the cell stencil (nbr and cnt unused)
   // per cell key, its particles in the lower half of the cell along x (they
@@ -277,7 +277,8 @@ struct ForceOut {
   uint32_t* flags;        // MDPL_FLAG_NONFINITE on a non-finite velocity; tile overflow (no list)
   KickTrack track;        // fused drift: the step's largest speed (rebuild rule)
 };
-// Partials are written per brick and part (nblocks_out = bricks x parts).
+// Partials are written per brick and part (nblocks_out = bricks x parts, tl.parts
+// of them or fewer).
 hipError_t lj_force(const double* x, const double* y, const double* z, const int32_t* cell_start,
                     const Grid& g, const TileList& tl, const LJConst& c, int precision, bool energy,
                     const ForceOut& out, int64_t n, hipStream_t st, int* nblocks_out);

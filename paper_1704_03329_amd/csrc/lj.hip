@@ -772,8 +772,18 @@ static void launch_force(bool energy, hipStream_t st, const double* x, const dou
 }
 
 hipError_t lj_force(const double* x, const double* y, const double* z, const int32_t* cell_start,
-                    const Grid& g, const TileList& tl, const LJConst& c, int precision, bool energy,
-                    const ForceOut& out, int64_t n, hipStream_t st, int* nblocks_out) {
+                    const Grid& g, const TileList& list, const LJConst& c, int precision,
+                    bool energy, const ForceOut& out, int64_t n, hipStream_t st,
+                    int* nblocks_out) {
+  // Two or three parts of a brick (129 to 256 bricks) only pay in the plain FP32
+  // pass (N = 39304 17.5 -> 16.0 us): in the others those workgroups are more
+  // than the CUs hold at once.  FP64, two parts: N = 39304 17.4 -> 18.8 us, with
+  // energies 20.8 -> 23.9, N = 91125 27.8 -> 29.9 and 29.3 -> 35.1; three: N =
+  // 76800 27.0 -> 26.8 and 28.7 -> 32.5 (both passes take the same lanes per
+  // particle: their forces are equal to the bit).  FP32 with energies 21.1 ->
+  // 21.8 (two), 29.4 -> 31.4 (three).
+  TileList tl = list;
+  if (tl.parts < 4 && (precision != 1 || energy)) tl.parts = 1;
   if (nblocks_out) *nblocks_out = g.nbricks * tl.parts;
   if (tl.cells) return lj_force_cells(x, y, z, cell_start, g, c, precision, energy, out, st);
   if (tl.half) return lj_force_half(x, y, z, cell_start, g, tl, c, precision, energy, out, n, st);
